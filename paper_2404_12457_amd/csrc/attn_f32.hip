@@ -1,185 +1,301 @@
-// fp32 prefix-cached paged prefill attention (no matrix cores: the fp32 variant
-// must hold 1e-4 against an fp64 reference, so products are plain fp32 FMAs).
+// fp32 prefix-cached paged prefill attention on the fp32 matrix cores of gfx950.
 //
 // out[t,h,:] = softmax_j(scale * q[t,h,:].K_j) V_j over j = 0..prefix+i, where the
 // first `prefix` keys are gathered from 16-token pool blocks through the request's
 // block table (paper Sec. 5.1: non-contiguous blocks referenced by tree nodes) and
 // the rest are the request's own fresh K/V (Sec. 3.2: only the request tokens are
-// computed).  One workgroup = (request, q head, 16 new tokens); keys stream through
-// LDS in chunks of 32; each wave owns 4 token rows and keeps an online softmax
-// (running max, running sum, rescaled accumulator) per row.
-#include "ragc_internal.h"
+// computed).  Inputs, products, softmax and sums are fp32 throughout.
+//
+// Mapping.  One workgroup = (request, kv head, 16 rows); a row is a (new token, q head of
+// the group) pair, token-major, so the heads of a GQA group share every K/V read.  Its NW
+// waves take every NW-th tile of 16 keys -- one pool block -- with an online softmax state
+// of their own each, and the states are combined through LDS at the end: no barrier and no
+// shared tile in the key loop.
+//
+// The operands of v_mfma_f32_16x16x4_f32 (16 keys x 16 rows x 4 of the contraction):
+//   S^T[key][row] = K . Q^T    A: lane (key l16, group kg) holds K[key][16 j + 4 kg + e], a
+//                              16-byte read per j; B: Q with the same order of the contraction
+//   O^T[d][row]  += V^T . P^T  A: lane (l16, kg) holds V[4 kg + i][64 c + 4 l16 + e], a 16-byte
+//                              read per (c, i) serves four products (e); B: P^T, which is the
+//                              accumulator of S^T as it stands (lane: row l16, keys 4 kg + i)
+// and a lane ends up with 16 consecutive output columns of its row.  Each wave copies its own
+// tile straight into its own part of LDS (global_load_lds), K during the P.V products of the
+// tile before, V during the Q.K products.
+//
+// What bounds it: the matrix cores, 64 flop per cycle and SIMD (157 TFLOP/s on the chip; a large
+// library product reaches 133).  A 16-key tile at head_dim 128 is 64 products, 2048 cycles, and
+// the loop runs at 0.8 of that with two waves per SIMD; the rest of a small call is the 5 us
+// before the first tile and after the last.  Measured: 4 requests of 512-1024 cached and 32-100
+// new tokens, 32/8 heads: 195 -> 39 us (plain FMAs from shared tiles before); one request of
+// 256 + 32 tokens, 4 heads of 64: 27 -> 9 us.  Read from global memory in operand order instead
+// of through LDS, K costs a cache access per lane (41 on average per load instruction, 2600
+// cycles per tile and CU) and the first of these takes 43 us; with K staged through registers
+// and three waves per SIMD, 42 us.
+#include "attn_bf16_common.h"
+#include "attn_work.h"
 
 namespace ragc {
 namespace {
 
-constexpr int TR = 16;  // new tokens per workgroup
-constexpr int KC = 32;  // keys per LDS chunk
+constexpr int TR = kAttnF32RowsPerItem;  // rows per workgroup
+constexpr int KT = kBlock;               // keys per tile
+constexpr float kRaise = 8.f;            // log2 units a row's reference exponent may lag behind its maximum
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, AttnWork wk) {
+    constexpr int KJ = D / 16;             // 16-byte reads of a K row per lane
+    constexpr int VC = D / 64;             // 16-byte reads of a V row per lane
+    constexpr int CPR = D / 4;             // 16-byte chunks per row
+    constexpr int ROWB = D * 4;            // bytes per row
+    constexpr int PLANEB = KT * ROWB;      // one tile of K (or V)
+    constexpr int RPI = 64 / CPR;          // rows one copy instruction covers
+    constexpr int NI = KT / RPI;           // copy instructions per plane and tile
+    constexpr int OSTRIDE = D + 4;         // floats per output row in LDS
+    static_assert(TR * OSTRIDE * 4 <= 2 * PLANEB, "a wave's output fits its tile buffers");
+    __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * PLANEB];
+    __shared__ float Ms[NW][TR], Ls[NW][TR];
 
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnLaunch a) {
-    __shared__ __attribute__((aligned(16))) float Ks[KC][D + 4];  // rows padded by one 16-byte chunk: 16-byte reads of 16 keys hit all banks
-    __shared__ __attribute__((aligned(16))) float Vs[KC][D];
-    __shared__ __attribute__((aligned(16))) float Qs[TR][D];
-    __shared__ __attribute__((aligned(16))) float Ps[4][KC][4];  // per wave: p of its 4 rows, per key
-
-    const int r = blockIdx.z;
-    const int h = blockIdx.y;
-    const int tile = gridDim.x - 1 - blockIdx.x;  // long key ranges first
-    const int N = a.b.new_len[r];
-    const int t0 = tile * TR;
-    if (t0 >= N) return;
-    const int P = a.b.prefix_len[r];
-    const int s0 = a.b.new_start[r];
-    const int g = h / a.group;
-    const int rows = min(TR, N - t0);
-    const int kv_limit = P + t0 + rows;  // keys [0, kv_limit) are visible to some row
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     const int Hkv = a.b.kv_heads;
+    int g, entry;
+    split_block_id(blockIdx.x, Hkv, &g, &entry);
+    entry += wk.entry0;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const WorkItem it = find_item(wk, entry, a.group, TR, lane);
+    const int P = it.prefix, N = it.new_len, s0 = it.new_start, G = a.group;
+    const uint32_t g_magic = a.group_magic;
+    auto div_g = [&](uint32_t x) { return g_magic ? (int)__umulhi(x, g_magic) : (int)x; };  // exact while x * G < 2^32
+    const long long row0 = (long long)it.tile * TR;
+    const int rows_here = (int)min((long long)TR, (long long)N * G - row0);
+    const int tok0 = row0 * G >> 32 ? (int)(row0 / G) : div_g((uint32_t)row0);  // row 0 of the tile: token tok0,
+    const int h0 = (int)(row0 - (long long)tok0 * G);                          // head h0 of the group
 
     const float* __restrict__ q = static_cast<const float*>(a.q);
     const float* __restrict__ k_new = static_cast<const float*>(a.k_new);
     const float* __restrict__ v_new = static_cast<const float*>(a.v_new);
     const float* __restrict__ pool_k = static_cast<const float*>(a.b.pool_k);
     const float* __restrict__ pool_v = static_cast<const float*>(a.b.pool_v);
-    const int32_t* __restrict__ table = a.b.block_table + (long long)r * a.b.table_stride;
+    const int32_t* __restrict__ table = a.b.block_table + (long long)it.req * a.b.table_stride;
 
-    constexpr int C4 = D / 4;  // float4 chunks per row
-    for (int idx = tid; idx < TR * C4; idx += 256) {
-        const int row = idx / C4, c4 = idx % C4;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < rows) v = *reinterpret_cast<const float4*>(q + ((long long)(s0 + t0 + row) * a.q_heads + h) * D + c4 * 4);
-        *reinterpret_cast<float4*>(&Qs[row][c4 * 4]) = v;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int kv_limit = P + tok0 + div_g(h0 + rows_here - 1) + 1;  // keys [0, kv_limit) are visible to some row
+    const int ntiles = (kv_limit + KT - 1) / KT;
+    const int nsteps = ntiles > w ? (ntiles - w + NW - 1) / NW : 0;  // this wave takes tiles w, w + NW, ...
+    const int my_row = h0 + min(l16, rows_here - 1);  // rows past the end repeat the last one and are not stored
+    const int my_tok = tok0 + div_g(my_row);
+    const int my_head = g * G + my_row - div_g(my_row) * G;
+    const int my_vis = P + my_tok + 1;
+    const int vis_min = P + tok0 + 1;  // tiles below need no mask
+
+    // block ids of this wave's tiles, 64 steps at a time, one per lane
+    int blk_base = 0;
+    int blk_vec = nsteps > 0 ? table[min(w + lane * NW, ntiles - 1)] : 0;
+    f32x4 qreg[KJ];
+    {
+        const float* qp = q + ((long long)(s0 + my_tok) * a.q_heads + my_head) * D + kg * 4;
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) qreg[j] = *reinterpret_cast<const f32x4*>(qp + j * 16);
     }
 
-    // fused append: the first q head of each group stores this tile's fresh K/V rows
-    if (a.fused_append && h % a.group == 0) {
-        float* wk = static_cast<float*>(a.pool_k_w);
-        float* wv = static_cast<float*>(a.pool_v_w);
-        for (int idx = tid; idx < rows * C4; idx += 256) {
-            const int row = idx / C4, c4 = idx % C4;
-            const int pos = P + t0 + row;
-            const long long src = ((long long)(s0 + t0 + row) * Hkv + g) * D + c4 * 4;
+    // every ordinary load has completed before the copies start to be counted
+    asm volatile("" ::"v"(blk_vec));
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) asm volatile("" ::"v"(qreg[j]));
+    wait_vmcnt<0>();
+
+    // Copies: lane i of instruction n brings row RPI n + i / CPR of the tile.  K rows are stored with their chunk
+    // index XORed with the row (on the global side), so that the 16 keys of an operand read hit different banks.
+    typedef __attribute__((address_space(3))) char lds_char;
+    typedef const __attribute__((address_space(3))) f32x4 lds_f32x4;
+    lds_char* const kbuf = (lds_char*)smem + w * (2 * PLANEB);
+    lds_char* const vbuf = kbuf + PLANEB;
+    const uint32_t k_addr = (uint32_t)(uintptr_t)kbuf, v_addr = k_addr + PLANEB;
+    const int new_row = Hkv * D;                                    // elements between fresh rows
+    const long long new_off = ((long long)(s0 - P) * Hkv + g) * D;  // of the fresh row at position 0
+    auto copy_tile = [&](int step, bool is_k) {
+        const int base = (w + step * NW) * KT;
+        const long long boff = (long long)__builtin_amdgcn_readlane(blk_vec, step - blk_base) * a.b.block_stride + (long long)g * kBlock * D;
+        const float* pool = is_k ? pool_k : pool_v;
+        const float* fresh = is_k ? k_new : v_new;
+        const uint32_t dst = is_k ? k_addr : v_addr;
+        if (base + KT <= P) {  // one pool block: uniform base, per-lane constant offset
+            const uint64_t src = uniform_u64(pool + boff);
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+                const int row = RPI * n + lane / CPR, chunk = lane % CPR;
+                dma_16B_per_lane(src, (uint32_t)(row * ROWB + (is_k ? chunk ^ row : chunk) * 16), dst + n * 1024);
+            }
+        } else if (base >= P && base + KT <= kv_limit) {  // fresh rows, all inside the horizon
+            const uint64_t src = uniform_u64(fresh + new_off + (long long)base * new_row);
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+                const int row = RPI * n + lane / CPR, chunk = lane % CPR;
+                dma_16B_per_lane(src, (uint32_t)(row * new_row * 4 + (is_k ? chunk ^ row : chunk) * 16), dst + n * 1024);
+            }
+        } else {  // the prefix or the horizon ends inside: source per row; keys past the horizon repeat the last visible one
+#pragma unroll 1
+            for (int n = 0; n < NI; ++n) {
+                const int row = RPI * n + lane / CPR, chunk = is_k ? (lane % CPR) ^ row : lane % CPR;
+                const int key = base + row;
+                const float* src = key < P ? pool + boff + row * D : fresh + new_off + (long long)min(key, kv_limit - 1) * new_row;
+                dma_16B_per_lane(src + chunk * 4, dst + n * 1024);
+            }
+        }
+    };
+    int koff[KJ];  // this lane's K reads
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) koff[j] = l16 * ROWB + (((4 * j + kg) ^ l16) << 4);
+    const int voff = kg * 4 * ROWB + l16 * 16;
+
+    f32x4 oacc[VC][4];
+#pragma unroll
+    for (int c = 0; c < VC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[c][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;  // l: this lane's keys only
+    const float sc = a.scale_log2e;
+
+    auto do_tile = [&](int step, auto more_c) {
+        constexpr bool MORE = decltype(more_c)::value;  // another tile follows
+        wait_vmcnt<NI>();  // K is here, V may be under way
+        f32x4 s_even = {0.f, 0.f, 0.f, 0.f}, s_odd = s_even;  // two chains: a product waits for the one before it
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const f32x4 kr = *reinterpret_cast<lds_f32x4*>(kbuf + koff[j]);
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+                s_even = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e], qreg[j][e], s_even, 0, 0, 0);
+                s_odd = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e + 1], qreg[j][e + 1], s_odd, 0, 0, 0);
+            }
+        }
+        if (MORE) {
+            if (step + 1 - blk_base >= 64) {
+                blk_base = step + 1;
+                blk_vec = table[min(w + (step + 1 + lane) * NW, ntiles - 1)];
+                asm volatile("" ::"v"(blk_vec));  // the wait for this load stays inside the branch
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this tile's K has been read
+            copy_tile(step + 1, true);
+        }
+        f32x4 s;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = (s_even[i] + s_odd[i]) * sc;
+        const int base = (w + step * NW) * KT;
+        if (base + KT > vis_min) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (base + kg * 4 + i >= my_vis) s[i] = -INFINITY;
+        }
+        // the reference exponent of a row is raised only when a score exceeds it by more than 2^8 (or on the
+        // row's first visible key); the four lanes of a row keep the same one
+        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        if (__builtin_amdgcn_ballot_w64(mx > m_run + kRaise) != 0) {
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const bool raise = mx > m_run + kRaise;
+            const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - mx) : 1.f;  // first visible key: exp2(-inf) = 0
+            m_run = raise ? mx : m_run;
+            l_run *= alpha;
+#pragma unroll
+            for (int c = 0; c < VC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) oacc[c][e][i] *= alpha;
+        }
+        const float m_sub = m_run == -INFINITY ? 0.f : m_run;  // a row without a visible key yet: exp2(-inf - 0) = 0
+        wait_vmcnt<MORE ? NI : 0>();  // V is here, the next K may be under way
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_sub);
+        l_run += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < VC; ++c) {
+                const f32x4 vr = *reinterpret_cast<lds_f32x4*>(vbuf + voff + i * ROWB + c * 256);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    oacc[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[e], p[i], oacc[c][e], 0, 0, 0);
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this tile's V has been read
+        if (MORE) copy_tile(step + 1, false);
+    };
+    if (nsteps > 0) {
+        copy_tile(0, true);
+        copy_tile(0, false);
+        for (int step = 0; step + 1 < nsteps; ++step) do_tile(step, std::true_type{});
+        do_tile(nsteps - 1, std::false_type{});
+    }
+
+    // fused append: this workgroup owns the tokens whose first row (head 0 of the group) it holds
+    if (a.fused_append) {
+        const int tok_lo = tok0 + (h0 != 0), tok_hi = min(N - 1, tok0 + div_g(h0 + TR - 1));
+        float* wk_pool = static_cast<float*>(a.pool_k_w);
+        float* wv_pool = static_cast<float*>(a.pool_v_w);
+        for (int idx = tid; idx < (tok_hi - tok_lo + 1) * (D / 4); idx += 64 * NW) {
+            const int tok = tok_lo + idx / (D / 4), c4 = idx % (D / 4);
+            const int pos = P + tok;
+            const long long src = ((long long)(s0 + tok) * Hkv + g) * D + c4 * 4;
             const long long dst = (long long)table[pos >> 4] * a.b.block_stride + ((long long)g * kBlock + (pos & 15)) * D + c4 * 4;
-            *reinterpret_cast<float4*>(wk + dst) = *reinterpret_cast<const float4*>(k_new + src);
-            *reinterpret_cast<float4*>(wv + dst) = *reinterpret_cast<const float4*>(v_new + src);
+            *reinterpret_cast<f32x4*>(wk_pool + dst) = *reinterpret_cast<const f32x4*>(k_new + src);
+            *reinterpret_cast<f32x4*>(wv_pool + dst) = *reinterpret_cast<const f32x4*>(v_new + src);
         }
     }
 
-    float m[4], l[4], o[4][D / 64];
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        m[rr] = -INFINITY;
-        l[rr] = 0.f;
-#pragma unroll
-        for (int dd = 0; dd < D / 64; ++dd) o[rr][dd] = 0.f;
+    // combine the waves' states (each left in the wave's own part of LDS): out = sum_w O_w 2^(m_w - m) / sum_w l_w 2^(m_w - m)
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    float* const Os = reinterpret_cast<float*>(smem);
+    constexpr int OWAVE = 2 * PLANEB / 4;
+    if (kg == 0) {
+        Ms[w][l16] = m_run;
+        Ls[w][l16] = l_run;
     }
-
-    for (int c0 = 0; c0 < kv_limit; c0 += KC) {
-        __syncthreads();
-        for (int idx = tid; idx < KC * C4; idx += 256) {
-            const int row = idx / C4, c4 = idx % C4;
-            const int kj = c0 + row;
-            float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
-            if (kj < kv_limit) {
-                if (kj < P) {
-                    const long long off = (long long)table[kj >> 4] * a.b.block_stride + ((long long)g * kBlock + (kj & 15)) * D + c4 * 4;
-                    kk = *reinterpret_cast<const float4*>(pool_k + off);
-                    vv = *reinterpret_cast<const float4*>(pool_v + off);
-                } else {
-                    const long long off = ((long long)(s0 + kj - P) * Hkv + g) * D + c4 * 4;
-                    kk = *reinterpret_cast<const float4*>(k_new + off);
-                    vv = *reinterpret_cast<const float4*>(v_new + off);
-                }
-            }
-            *reinterpret_cast<float4*>(&Ks[row][c4 * 4]) = kk;
-            *reinterpret_cast<float4*>(&Vs[row][c4 * 4]) = vv;
-        }
-        __syncthreads();
-
-        // scores of the wave's 4 rows at once: lane = (key, half of the head dim); every K chunk read
-        // from LDS serves the 4 rows.  Rows past the end carry q = 0 and are never stored; a row
-        // whose visible keys all lie in earlier chunks gets p = 0 and alpha = 1 below.
-        const int key = lane & 31, dh = lane >> 5;
-        float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int d4 = 0; d4 < D / 8; ++d4) {
-            const float4 kk = *reinterpret_cast<const float4*>(&Ks[key][dh * (D / 2) + d4 * 4]);
+    for (int c = 0; c < VC; ++c)
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const float4 qq = *reinterpret_cast<const float4*>(&Qs[w * 4 + rr][dh * (D / 2) + d4 * 4]);
-                part[rr] += qq.x * kk.x + qq.y * kk.y + qq.z * kk.z + qq.w * kk.w;
-            }
-        }
-        float alpha[4];
-        float4 p4;
-        float* pp = reinterpret_cast<float*>(&p4);
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const int visible = P + t0 + w * 4 + rr + 1;  // keys [0, visible): prefix, earlier new tokens, itself
-            float sc = (part[rr] + __shfl_xor(part[rr], 32, 64)) * a.scale_log2e;
-            if (c0 + key >= visible) sc = -INFINITY;
-            const float m_new = fmaxf(m[rr], wave_max(sc));
-            alpha[rr] = exp2f(m[rr] - m_new);  // first chunk: exp2(-inf) = 0
-            pp[rr] = exp2f(sc - m_new);
-            l[rr] = l[rr] * alpha[rr] + wave_sum(dh == 0 ? pp[rr] : 0.f);
-            m[rr] = m_new;
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (dh == 0) *reinterpret_cast<float4*>(&Ps[w][key][0]) = p4;
-        __builtin_amdgcn_wave_barrier();
-        // O += P V: lane = column of V; every V element read from LDS serves the 4 rows
-#pragma unroll
-        for (int dd = 0; dd < D / 64; ++dd) {
-            float acc[4];
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) acc[rr] = o[rr][dd] * alpha[rr];
-#pragma unroll 8
-            for (int j = 0; j < KC; ++j) {
-                const float v = Vs[j][lane + 64 * dd];
-                const float4 pj = *reinterpret_cast<const float4*>(&Ps[w][j][0]);
-                acc[0] += pj.x * v;
-                acc[1] += pj.y * v;
-                acc[2] += pj.z * v;
-                acc[3] += pj.w * v;
-            }
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) o[rr][dd] = acc[rr];
-        }
-    }
-
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<f32x4*>(Os + (w * OWAVE + l16 * OSTRIDE + 64 * c + 16 * kg + 4 * i)) =
+                f32x4{oacc[c][0][i], oacc[c][1][i], oacc[c][2][i], oacc[c][3][i]};
+    __syncthreads();
     float* __restrict__ out = static_cast<float*>(a.out);
+    for (int idx = tid; idx < TR * (D / 4); idx += 64 * NW) {
+        const int r = idx / (D / 4), c4 = idx % (D / 4);
+        if (r >= rows_here) break;
+        float m = -INFINITY;
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int il = w * 4 + rr;
-        if (il >= rows) continue;
-        const float inv = 1.f / l[rr];
+        for (int x = 0; x < NW; ++x) m = fmaxf(m, Ms[x][r]);
+        float l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int dd = 0; dd < D / 64; ++dd)
-            out[((long long)(s0 + t0 + il) * a.q_heads + h) * D + lane + 64 * dd] = o[rr][dd] * inv;
+        for (int x = 0; x < NW; ++x) {
+            const float wgt = Ms[x][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(Ms[x][r] - m);  // a wave may have seen no key of the row
+            l += Ls[x][r] * wgt;
+            const f32x4 ox = *reinterpret_cast<const f32x4*>(Os + (x * OWAVE + r * OSTRIDE + c4 * 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] += ox[e] * wgt;
+        }
+        const float inv = 1.f / l;
+        const int dtok = div_g(h0 + r), head = g * G + h0 + r - dtok * G;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] *= inv;
+        *reinterpret_cast<f32x4*>(out + ((long long)(s0 + tok0 + dtok) * a.q_heads + head) * D + c4 * 4) = o;
     }
 }
 
 }  // namespace
 
-hipError_t launch_attn_f32(const AttnLaunch& a, hipStream_t s) {
-    if (a.max_new <= 0 || a.b.num_reqs <= 0) return hipSuccess;
-    dim3 grid((a.max_new + TR - 1) / TR, a.q_heads, a.b.num_reqs);
-    if (a.b.head_dim == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, a);
+hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s) {
+    if (entries <= 0) return hipSuccess;
+    const dim3 grid((unsigned)entries * a.b.kv_heads);
+    const bool d64 = a.b.head_dim == 64;
+    if (waves == 4) {
+        if (d64) hipLaunchKernelGGL((attn_f32_kernel<64, 4>), grid, dim3(256), 0, s, a, wk);
+        else hipLaunchKernelGGL((attn_f32_kernel<128, 4>), grid, dim3(256), 0, s, a, wk);
+    } else {
+        if (d64) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, s, a, wk);
+        else hipLaunchKernelGGL((attn_f32_kernel<128, 8>), grid, dim3(512), 0, s, a, wk);
+    }
     return hipGetLastError();
 }
 

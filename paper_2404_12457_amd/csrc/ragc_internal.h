@@ -44,7 +44,27 @@ struct AttnLaunch {
     int32_t total_new;
 };
 
-hipError_t launch_attn_f32(const AttnLaunch& a, hipStream_t s);
+// The requests of one attention launch, in the kernel arguments: request i of the list owns the work
+// entries [first, first of the next one), one per row tile, and carries its lengths, so a workgroup
+// needs no device array before it can look up its first block ids.
+constexpr int kAttnMaxReqs = 192;
+struct AttnReq {
+    int32_t first;
+    int32_t prefix_len;
+    int32_t new_len;
+    int32_t new_start;
+};
+struct AttnWork {
+    int32_t n_reqs;
+    int32_t entry0;  // first entry of this launch (one launch holds so many workgroups)
+    AttnReq req[kAttnMaxReqs];
+    uint16_t id[kAttnMaxReqs];  // which request of the batch
+};
+
+constexpr int kAttnF32RowsPerItem = 16;
+constexpr int kAttnF32MaxWorkgroups = 1 << 22;  // of one launch: grid times workgroup size stays below 2^32 threads
+// waves: 4 or 8 per workgroup
+hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
 
 // bf16 path: the host orders the (request, row tile) work items by cost and passes
 // them in the kernel argument buffer (no device staging); long lists go out in

@@ -557,3 +557,23 @@ def test_validation_mode_finds_what_the_kernels_cannot_check(H):
     # without the flag the same aliasing batch is the caller's responsibility: only the range check of the host table runs
     torch.cuda.synchronize()
     assert torch.equal(_bits(dw.pool_k), before)  # none of the refused calls wrote anything
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (4, 4, 64, [(0, 1), (15, 1), (16, 15), (17, 16), (31, 17), (64, 33)]),           # row tile and block edges, one row per token
+    (6, 2, 128, [(0, 5), (47, 6), (48, 11), (300, 40)]),                             # group of 3: a token straddles row tiles
+    (32, 1, 64, [(130, 1), (5, 3)]),                                                 # a token spans two row tiles
+    (8, 8, 128, [(9000, 3), (1100, 130)]),                                           # more tiles per wave than one window of block ids
+    (2, 2, 64, [((7 * i) % 50, i % 3) for i in range(130)]),                         # more requests than lanes, some of them empty
+    (1, 1, 64, [(i % 37, 1 + i % 2) for i in range(400)]),                           # more requests than one launch lists
+    (16, 8, 128, [(200, 60), (17, 700), (90, 16)]),                                  # enough workgroups for four waves each
+], ids=lambda v: str(v) if isinstance(v, int) else f"R{len(v)}")
+def test_fp32_matrix_core_kernel_at_its_edges(H, hq, hkv, d, lens):
+    """fp32 against the fp64 oracle (1e-4, relative 1e-5: fp32 rounding of scores up to ~20 gives exponents
+    off by ~2e-6, of sums over the keys less), and the fused append byte for byte."""
+    w = W.make_small("f32", hq, hkv, d, lens, seed=7700 + len(lens), q_gain=2.0)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "f32")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "f32")))
