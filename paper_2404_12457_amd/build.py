@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libragc.so")
 CALIB_LIB = os.path.join(HERE, "libragc_calib.so")
-SOURCES = ["ragc_api.cpp", "ragc_ctl.cpp", "kv_ops.hip", "attn_f32.hip", "attn_bf16.hip"]
+SOURCES = ["ragc_api.cpp", "ragc_ctl.cpp", "kv_ops.hip", "attn_f32.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
     # packed fp32 math is kept off on this target (see the build notes)

@@ -22,14 +22,8 @@
 // overlaps the other's MFMAs.  With many work items NG = 1 and two workgroups share
 // a CU instead.
 //
-// A launch whose work items all have at most 32 rows (decode steps) is compiled with DEC: the
-// first two waves of a group share those rows and take one 32-key half of every tile each.
-//
-// A batch with few work items is also split along the keys ACROSS workgroups: a work item
-// then appears S times in the list, each copy walks 1/S of the key tiles and leaves its
-// unnormalised O and its (max, sum) per row in the caller's workspace, and attn_bf16_merge_kernel
-// combines the S partial results of every row.  This is what keeps a single request, or a
-// decode step, from running on a fraction of the chip.
+// Launches too small to fill the chip with such items go to attn_bf16_rows_kernel, which can also
+// split them along the keys across workgroups.
 //
 // The products are computed transposed so that a lane owns ONE query row:
 //   S^T[key][row] = K . Q^T      A = K tile (LDS, 16-byte reads), B = Q (registers)
@@ -40,22 +34,16 @@
 // row; the other 16 sit in lane+32, so a row max costs one half-swap.  The running
 // max is only raised (and O, l rescaled) when a tile exceeds it by more than 2^8.
 #include "attn_bf16_common.h"
+#include "attn_work.h"
 
 namespace ragc {
 namespace {
 
 constexpr int TM = kAttnRowsPerItem;  // rows per work item
 
-// SPLIT: the list holds several copies of every item, each with a share of the key tiles (a
-// separate instantiation, so that the common unsplit kernel carries none of it).
-template <int D, int NG, int RING, bool SPLIT, bool DEC>
-__global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, AttnWorkList wl) {
-    // DEC: every work item of the launch has at most 32 rows (decode steps: one new token times the
-    // group's q heads).  The rows then all sit in wave 0's block and three waves of four would only
-    // copy; instead waves 0 and 1 of a group both take those 32 rows and one 32-key half of every
-    // tile each, with private softmax state merged at the end like the wave groups' -- half the
-    // MFMAs and half the softmax per wave and tile, which is what a step costs when nothing overlaps it.
-    constexpr int NSUB = DEC ? 1 : 2;   // 32-key halves of a tile per wave
+template <int D, int NG, int RING, class Work>
+__global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
+    constexpr int NSUB = 2;             // 32-key halves of a tile
     constexpr int CPR = D / 8;          // 16-byte chunks per K/V row
     constexpr int ROWB = D * 2;         // bytes per row
     constexpr int PLANEB = TN * ROWB;   // one tile of K (or V)
@@ -69,20 +57,16 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     static_assert(NSTAGE * STAGEB <= 160 * 1024, "LDS");
     __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGEB];
 
-    // ---- work item: consecutive workgroup ids round-robin over the 8 XCDs, so the kv head
-    // is taken from the low bits: all row tiles of one (request, kv head) stream share an L2
-    const int Hkv = a.b.kv_heads;
-    int g, item;
-    if ((Hkv & 7) == 0) {
-        const int x = blockIdx.x & 7, j = blockIdx.x >> 3, hpx = Hkv >> 3;
-        g = x + 8 * (j % hpx);
-        item = j / hpx;
-    } else {
-        g = blockIdx.x % Hkv;
-        item = blockIdx.x / Hkv;
-    }
-    const AttnItem it = wl.item[item];
-    const int r = it.req_tile >> 16, tile = it.req_tile & 0xffff;
+    touch_args(a, wk);
+    const int Hkv = a.kv_heads;
+    int g, entry;
+    split_block_id(a, blockIdx.x, &g, &entry);
+    entry += wk.entry0;
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = NG == 1 ? 0 : w >> 2, wq = w & 3;
+    const WorkItem it = find_item(wk, entry, a.group, TM);
+    const int tile = it.tile;
 
     const int G = a.group;
     // x / G for 0 <= x < 2^26 / G without an integer division (the host supplies ceil(2^32 / G), 0 for G = 1)
@@ -91,39 +75,29 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     const int N = it.new_len;
     const int rows_total = N * G;
     const int row0 = tile * TM;
-    if (row0 >= rows_total) return;
-    const int P = it.prefix_len;
+    const int P = it.prefix;
     const int s0 = it.new_start;
     const int Hq = a.q_heads;
-    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int grp = NG == 1 ? 0 : w >> 2, wq = w & 3;
 
     const __bf16* __restrict__ q = static_cast<const __bf16*>(a.q);
     const __bf16* __restrict__ k_new = static_cast<const __bf16*>(a.k_new);
     const __bf16* __restrict__ v_new = static_cast<const __bf16*>(a.v_new);
-    const __bf16* __restrict__ pool_k = static_cast<const __bf16*>(a.b.pool_k);
-    const __bf16* __restrict__ pool_v = static_cast<const __bf16*>(a.b.pool_v);
-    const int32_t* __restrict__ table = a.b.block_table + (long long)r * a.b.table_stride;
+    const __bf16* __restrict__ pool_k = static_cast<const __bf16*>(a.pool_k);
+    const __bf16* __restrict__ pool_v = static_cast<const __bf16*>(a.pool_v);
+    const int32_t* __restrict__ table = a.block_table + (long long)it.req * a.table_stride;
 
     const int last_row = min(row0 + TM, rows_total) - 1;
     const int kv_limit = P + div_g(last_row) + 1;  // keys [0, kv_limit) are visible to some row of the item
-    const int ntiles_all = (kv_limit + TN - 1) / TN;
-    // key split across workgroups: copy `sidx` of S takes tiles [t_lo, ntiles)
-    const int S = SPLIT ? wl.splits : 1, sidx = SPLIT ? item % S : 0;
-    const int t_lo = ntiles_all * sidx / S;
-    const int ntiles = ntiles_all * (sidx + 1) / S;  // exclusive end of this copy's tiles
-    if (t_lo >= ntiles) return;                      // more copies than tiles: nothing for this one
-    const int nsteps = (ntiles - t_lo + NG - 1) / NG;  // group `grp` takes tile t_lo + step*NG + grp
+    const int ntiles = (kv_limit + TN - 1) / TN;
+    const int nsteps = (ntiles + NG - 1) / NG;  // group `grp` takes tile step*NG + grp
 
     // ---- this lane's query row
-    const int wrow0 = row0 + (DEC ? 0 : wq * 32);
-    const int ksub = DEC ? wq * 32 : 0;  // DEC: this wave's half of every tile (waves 2 and 3 only copy)
+    const int wrow0 = row0 + wq * 32;
     const int my_row = min(wrow0 + l32, rows_total - 1);  // rows past the end repeat the last one
     const int my_tok = div_g(my_row);
     const int my_head = g * G + (my_row - my_tok * G);
     const int my_vis = P + my_tok + 1;  // keys [0, my_vis) are visible to this row
-    const bool wave_active = wrow0 < rows_total && (!DEC || wq < 2);
+    const bool wave_active = wrow0 < rows_total;
     const int wave_vis_min = P + div_g(wrow0) + 1;
     const int wave_vis_max = P + div_g(min(wrow0 + 31, rows_total - 1)) + 1;
 
@@ -135,7 +109,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     int blk_base = 0;
     int blk_vec;
     {
-        const int e = (min(t_lo + lane * NG + grp, ntiles - 1) * TN >> 4) + wq;
+        const int e = (min(lane * NG + grp, ntiles - 1) * TN >> 4) + wq;
         blk_vec = e < nblk_item ? table[e] : 0;
     }
     bf16x8 qreg[KSTEPS];
@@ -186,17 +160,17 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     auto prepare = [&](int step) {
         if (step - blk_base >= 64) {
             blk_base = step;
-            const int e = (min(t_lo + (step + lane) * NG + grp, ntiles - 1) * TN >> 4) + wq;
+            const int e = (min((step + lane) * NG + grp, ntiles - 1) * TN >> 4) + wq;
             blk_vec = e < nblk_item ? table[e] : 0;
             asm volatile("" ::"v"(blk_vec));  // the compiler's wait for this load stays inside the branch
         }
-        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
+        const int tg = min(step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
         const int kbase = tg * TN + wq * 16;
         const int blk = __builtin_amdgcn_readlane(blk_vec, step - blk_base);
         const uint32_t dst = smem_addr + (grp * RING + step % RING) * STAGEB + wq * 16 * ROWB;
         if (kbase + 16 <= P) {
             // the whole block is cached: one pool block, uniform base + per-lane constant
-            const long long boff = ((long long)blk * a.b.block_stride + (long long)g * kBlock * D) * 2;
+            const long long boff = ((long long)blk * a.block_stride + (long long)g * kBlock * D) * 2;
             pend_kb = uniform_u64(reinterpret_cast<const char*>(pool_k) + boff);
             pend_vb = uniform_u64(reinterpret_cast<const char*>(pool_v) + boff);
             pend_dst = dst;
@@ -220,7 +194,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
                 const int kj = kbase + row16;
                 long long off;
                 if (kj < P) {
-                    off = (long long)blk * a.b.block_stride + ((long long)g * kBlock + row16) * D + chunk * 8;
+                    off = (long long)blk * a.block_stride + ((long long)g * kBlock + row16) * D + chunk * 8;
                 } else {
                     const int kn = min(kj, kv_limit - 1) - P;
                     off = ((long long)(s0 + kn) * Hkv + g) * D + chunk * 8;
@@ -242,7 +216,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     int koff[KSTEPS];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
-        koff[ks] = grp_off + (ksub + l32) * ROWB + (((2 * ks + hf) ^ swz<D>(l32)) << 4);
+        koff[ks] = grp_off + l32 * ROWB + (((2 * ks + hf) ^ swz<D>(l32)) << 4);
         asm volatile("" : "+v"(koff[ks]));  // keep it one register: address = this + immediate
     }
     // V, A operand of O^T (transposing read): rows kk*16 + 8*h2 + 4*hf + (lane&15)/4 + {sub*32},
@@ -254,7 +228,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
         for (int dt = 0; dt < DT; ++dt) {
             const int row = 8 * h2 + 4 * hf + ((lane & 15) >> 2);
             const int elem = dt * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-            voff[h2][dt] = grp_off + (ksub + row) * ROWB + ((((elem >> 3)) ^ swz<D>(row)) << 4) + (elem & 7) * 2;
+            voff[h2][dt] = grp_off + row * ROWB + ((((elem >> 3)) ^ swz<D>(row)) << 4) + (elem & 7) * 2;
             asm volatile("" : "+v"(voff[h2][dt]));
         }
 
@@ -276,8 +250,8 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
         block_barrier();  // every wave's part is in LDS, and every wave is done with the previous step
         if (step + RING - 1 < nsteps) prepare(step + RING - 1);
 
-        const int tg = t_lo + step * NG + grp;
-        const int base = tg * TN + ksub;  // first key this wave looks at
+        const int tg = step * NG + grp;
+        const int base = tg * TN;  // first key this wave looks at
         if (!wave_active || tg >= ntiles || base >= wave_vis_max) {
             flush();
             return;
@@ -399,11 +373,11 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     // because the loop has just read them as keys; requested up front, next to Q, the rows cost 1-4 %
     // on the prefill configurations and gain 1-2 % on decode steps).  This work item owns the tokens
     // whose first row (head 0 of the group) it holds; 16-byte chunks, four per thread in flight.
-    if (a.fused_append && sidx == S - 1) {  // the last copy always has tiles
+    if (a.fused_append) {
         const int tok_lo = div_g(row0 + G - 1);
         const int tok_hi = min(N - 1, div_g(row0 + TM - 1));
-        __bf16* wk = static_cast<__bf16*>(a.pool_k_w);
-        __bf16* wv = static_cast<__bf16*>(a.pool_v_w);
+        __bf16* wk = static_cast<__bf16*>(a.pool_k);
+        __bf16* wv = static_cast<__bf16*>(a.pool_v);
         const int n = (tok_hi - tok_lo + 1) * CPR;
         constexpr int UNR = 4;
         for (int i0 = tid; i0 < n; i0 += (256 * NG) * UNR) {
@@ -421,7 +395,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
                 const int tok = tok_lo + idx / CPR, ch = idx % CPR;
                 const int pos = P + tok;
                 const long long src = ((long long)(s0 + tok) * Hkv + g) * D + ch * 8;
-                dst[u] = (long long)blk[u] * a.b.block_stride + ((long long)g * kBlock + (pos & 15)) * D + ch * 8;
+                dst[u] = (long long)blk[u] * a.block_stride + ((long long)g * kBlock + (pos & 15)) * D + ch * 8;
                 kk[u] = *reinterpret_cast<const u32x4*>(k_new + src);
                 vv[u] = *reinterpret_cast<const u32x4*>(v_new + src);
             }
@@ -437,49 +411,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
 
     // ---- merge the wave groups through LDS (the DMA ring is idle now)
     constexpr int WSTRIDE = (DT * 16 + 4) * 64;  // floats per wave in the merge area: [DT*4 + 1 chunks][64 lanes][4]
-    if (DEC) {
-        // up to 2 * NG waves hold a state for the same 32 rows: wave (grp, wq < 2) is participant
-        // p = 2 * grp + wq; everyone but participant 0 leaves its state in area p, participant 0 adds
-        // them up one after the other and goes on alone
-        static_assert(2 * NG * WSTRIDE * 4 <= NSTAGE * STAGEB, "merge areas fit the ring");
-        typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
-        const int part_id = 2 * grp + wq;
-        block_barrier();
-        if (wq < 2 && part_id != 0) {
-            lds_f32x4* const xw = reinterpret_cast<lds_f32x4*>(lds0 + part_id * (WSTRIDE * 4)) + lane;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 v = {oacc[dt][i4 * 4], oacc[dt][i4 * 4 + 1], oacc[dt][i4 * 4 + 2], oacc[dt][i4 * 4 + 3]};
-                    xw[(dt * 4 + i4) * 64] = v;
-                }
-            const f32x4 ml = {m_run, l_run, 0.f, 0.f};
-            xw[DT * 4 * 64] = ml;
-        }
-        block_barrier();
-        if (w != 0) return;
-#pragma unroll 1
-        for (int other = 1; other < 2 * NG; ++other) {
-            lds_f32x4* const xw = reinterpret_cast<lds_f32x4*>(lds0 + other * (WSTRIDE * 4)) + lane;
-            const f32x4 ml = xw[DT * 4 * 64];
-            const float m1 = ml[0], l1 = ml[1];
-            // a participant (or, with a key split, all of them) may have seen no visible key of a row: weight 0
-            const float m = fmaxf(m_run, m1);
-            const float s0f = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
-            const float s1f = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
-            m_run = m;
-            l_run = l_run * s0f + l1 * s1f;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 v = xw[(dt * 4 + i4) * 64];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) oacc[dt][i4 * 4 + e] = oacc[dt][i4 * 4 + e] * s0f + v[e] * s1f;
-                }
-        }
-    } else if (NG > 1) {
+    if (NG > 1) {
         typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
         lds_f32x4* const xw = reinterpret_cast<lds_f32x4*>(lds0 + wq * (WSTRIDE * 4)) + lane;
         block_barrier();
@@ -499,7 +431,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
         if (wave_active) {
             const f32x4 ml = xw[DT * 4 * 64];
             const float m1 = ml[0], l1 = ml[1];
-            // a group (or, with a key split, both) may have seen no visible key of a row: weight 0
+            // a group may have seen no visible key of a row: weight 0
             const float m = fmaxf(m_run, m1);
             const float s0f = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
             const float s1f = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
@@ -525,39 +457,8 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     if (!wave_active) return;
     constexpr int OROWB = ROWB + 16;
     static_assert(32 * OROWB <= WSTRIDE * 4, "output patch fits the merge area");
-    lds_char* const patch = lds0 + wq * (NG > 1 ? WSTRIDE * 4 : 32 * OROWB);  // DEC: wave 0 only, area 0 holds no state
+    lds_char* const patch = lds0 + wq * (NG > 1 ? WSTRIDE * 4 : 32 * OROWB);
     const float l_tot = l_run + other_half(l_run);
-    if (SPLIT) {
-        // ---- one of S copies of the item: leave O (unnormalised, fp32), max and sum of every row in the
-        // workspace; partial (item, copy, kv head) = [TM][D] floats of O, then [TM][2] floats (max, sum).
-        // Same turn through LDS as below, in two passes of D/2 floats per row.
-        float* const part = static_cast<float*>(a.partial) + ((long long)(wl.part_base + item) * Hkv + g) * (TM * (D + 2));
-        const int prow = wq * 32;
-        if (hf == 0) {
-            const float2 ml = {m_run, l_tot};
-            *reinterpret_cast<float2*>(part + TM * D + (prow + l32) * 2) = ml;
-        }
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-            for (int dtl = 0; dtl < DT / 2; ++dtl)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const int dt = pass * (DT / 2) + dtl;
-                    const f32x4 v = {oacc[dt][i4 * 4], oacc[dt][i4 * 4 + 1], oacc[dt][i4 * 4 + 2], oacc[dt][i4 * 4 + 3]};
-                    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + l32 * OROWB + (dtl * 32 + i4 * 8 + hf * 4) * 4) = v;
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int p = 0; p < 32 / RPI; ++p) {
-                const int rr = p * RPI + lane / CPR;
-                const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(patch + rr * OROWB + (lane % CPR) * 16);
-                *reinterpret_cast<f32x4*>(part + (prow + rr) * D + pass * (D / 2) + (lane % CPR) * 4) = v;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the patch is rewritten by the next pass
-        }
-        return;
-    }
     const float inv = 1.f / l_tot;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -584,112 +485,25 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     }
 }
 
-// Combines the S partial results of every row of a split work item (see the end of
-// attn_bf16_kernel for the layout): out = sum_s O_s 2^(m_s - m) / sum_s l_s 2^(m_s - m), m = max_s m_s.
-// The list holds one entry per split item (its copy 0); one workgroup per (entry, kv head, run of
-// 256 / (D/4) rows): 4 consecutive d of one row per thread.
-template <int D>
-__global__ __launch_bounds__(256) void attn_bf16_merge_kernel(AttnLaunch a, AttnWorkList wl) {
-    constexpr int TPR = D / 4;          // threads per row
-    constexpr int RPW = 256 / TPR;      // rows per workgroup
-    constexpr int CHUNKS = TM / RPW;    // workgroups per (entry, kv head)
-    const int Hkv = a.b.kv_heads;
-    const int chunk = blockIdx.x % CHUNKS;
-    const int g = (blockIdx.x / CHUNKS) % Hkv;
-    const int lead = blockIdx.x / (CHUNKS * Hkv);  // the list holds copy 0 of every split item, in launch order
-    const AttnItem it = wl.item[lead];
-    const int S = wl.splits;
-    const int G = a.group;
-    const uint32_t g_magic = a.group_magic;
-    auto div_g = [&](int x) { return g_magic ? (int)__umulhi((uint32_t)x, g_magic) : x; };
-    const int rows_total = it.new_len * G;
-    const int row0 = (it.req_tile & 0xffff) * TM;
-    const int rows_here = min(TM, rows_total - row0);
-    const int kv_limit = it.prefix_len + div_g(row0 + rows_here - 1) + 1;
-    const int ntiles_all = (kv_limit + TN - 1) / TN;
-    constexpr int PART = TM * (D + 2);
-    const float* const part0 = static_cast<const float*>(a.partial) + ((long long)(wl.part_base + lead * S) * Hkv + g) * PART;
-    const long long copy_stride = (long long)Hkv * PART;
-    const int d4 = threadIdx.x % TPR;
-    __bf16* const outp = static_cast<__bf16*>(a.out);
-    const int r = chunk * RPW + threadIdx.x / TPR;
-    if (r < rows_here) {
-        // one round trip: every copy's (max, sum) and O piece are requested before any is used
-        float mc[kAttnMaxSplits], lc[kAttnMaxSplits];
-        f32x4 oc[kAttnMaxSplits];
-#pragma unroll
-        for (int c = 0; c < kAttnMaxSplits; ++c) {
-            mc[c] = -INFINITY;  // a copy that does not exist, or had no tiles and wrote nothing, weighs 0
-            lc[c] = 0.f;
-            oc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (c < S && ntiles_all * c / S < ntiles_all * (c + 1) / S) {
-                const float* pc = part0 + c * copy_stride;
-                const float2 ml = *reinterpret_cast<const float2*>(pc + TM * D + r * 2);
-                mc[c] = ml.x;
-                lc[c] = ml.y;
-                oc[c] = *reinterpret_cast<const f32x4*>(pc + r * D + d4 * 4);
-            }
-        }
-        float m = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < kAttnMaxSplits; ++c) m = fmaxf(m, mc[c]);
-        float l = 0.f;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < kAttnMaxSplits; ++c) {
-            const float wgt = mc[c] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mc[c] - m);  // a copy may hold no visible key of the row
-            l += lc[c] * wgt;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += oc[c][e] * wgt;
-        }
-        const float inv = 1.f / l;
-        const int row = row0 + r;
-        const int tok = div_g(row);
-        const int head = g * G + (row - tok * G);
-        bf16x4 o4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(acc[e] * inv);
-        *reinterpret_cast<bf16x4*>(outp + ((long long)(it.new_start + tok) * a.q_heads + head) * D + d4 * 4) = o4;
-    }
+template <int D, int NG, int RING, class Work>
+void launch_one(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
+    const dim3 grid((unsigned)entries * a.kv_heads), block(256 * NG);
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NG, RING, Work>), grid, block, 0, s, a, wk);
 }
-
-template <int D, int NG, int RING, bool DEC>
-void launch_dec(const AttnLaunch& a, const AttnWorkList& wl, hipStream_t s) {
-    if (wl.splits > 1)
-        hipLaunchKernelGGL((attn_bf16_kernel<D, NG, RING, true, DEC>), dim3(wl.n * a.b.kv_heads), dim3(256 * NG), 0, s, a, wl);
+template <class Work>
+void launch_list(const AttnLaunch& a, const Work& wk, int entries, int variant, hipStream_t s) {
+    const bool d64 = a.head_dim == 64;
+    if (variant == kAttnVariantTwoGroups)
+        d64 ? launch_one<64, 2, 2>(a, wk, entries, s) : launch_one<128, 2, 2>(a, wk, entries, s);
     else
-        hipLaunchKernelGGL((attn_bf16_kernel<D, NG, RING, false, DEC>), dim3(wl.n * a.b.kv_heads), dim3(256 * NG), 0, s, a, wl);
-}
-template <int D, int NG, int RING>
-void launch_one(const AttnLaunch& a, const AttnWorkList& wl, hipStream_t s) {
-    if (a.max_new * a.group <= 32) launch_dec<D, NG, RING, true>(a, wl, s);  // every item has at most 32 rows
-    else launch_dec<D, NG, RING, false>(a, wl, s);
+        d64 ? launch_one<64, 1, 2>(a, wk, entries, s) : launch_one<128, 1, 2>(a, wk, entries, s);
 }
 
 }  // namespace
 
-int attn_bf16_item_cost(int prefix, int new_len, int group, int tile) {
-    const int rows = new_len * group;
-    const int last_row = (tile + 1) * TM < rows ? (tile + 1) * TM - 1 : rows - 1;
-    return (prefix + last_row / group + 1 + TN - 1) / TN;
-}
-
-hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWorkList& wl, int variant, hipStream_t s) {
-    if (wl.n <= 0) return hipSuccess;
-    const bool d64 = a.b.head_dim == 64;
-    if (variant == kAttnVariantTwoGroups)
-        d64 ? launch_one<64, 2, 2>(a, wl, s) : launch_one<128, 2, 2>(a, wl, s);
-    else
-        d64 ? launch_one<64, 1, 2>(a, wl, s) : launch_one<128, 1, 2>(a, wl, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWorkList& wl, hipStream_t s) {
-    if (wl.n <= 0) return hipSuccess;
-    if (a.b.head_dim == 64)
-        hipLaunchKernelGGL((attn_bf16_merge_kernel<64>), dim3(wl.n * a.b.kv_heads * (TM / 16)), dim3(256), 0, s, a, wl);
-    else
-        hipLaunchKernelGGL((attn_bf16_merge_kernel<128>), dim3(wl.n * a.b.kv_heads * (TM / 8)), dim3(256), 0, s, a, wl);
+hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, hipStream_t s) {
+    if (entries <= 0) return hipSuccess;
+    wk.n_reqs <= kAttnReqStep ? launch_list(a, short_list(wk), entries, variant, s) : launch_list(a, wk, entries, variant, s);
     return hipGetLastError();
 }
 

@@ -41,8 +41,8 @@ constexpr int TR = kAttnF32RowsPerItem;  // rows per workgroup
 constexpr int KT = kBlock;               // keys per tile
 constexpr float kRaise = 8.f;            // log2 units a row's reference exponent may lag behind its maximum
 
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, AttnWork wk) {
+template <int D, int NW, class Work>
+__global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work wk) {
     constexpr int KJ = D / 16;             // 16-byte reads of a K row per lane
     constexpr int VC = D / 64;             // 16-byte reads of a V row per lane
     constexpr int CPR = D / 4;             // 16-byte chunks per row
@@ -55,12 +55,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Attn
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * PLANEB];
     __shared__ float Ms[NW][TR], Ls[NW][TR];
 
-    const int Hkv = a.b.kv_heads;
+    touch_args(a, wk);
+    const int Hkv = a.kv_heads;
     int g, entry;
-    split_block_id(blockIdx.x, Hkv, &g, &entry);
+    split_block_id(a, blockIdx.x, &g, &entry);
     entry += wk.entry0;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const WorkItem it = find_item(wk, entry, a.group, TR, lane);
+    const WorkItem it = find_item(wk, entry, a.group, TR);
     const int P = it.prefix, N = it.new_len, s0 = it.new_start, G = a.group;
     const uint32_t g_magic = a.group_magic;
     auto div_g = [&](uint32_t x) { return g_magic ? (int)__umulhi(x, g_magic) : (int)x; };  // exact while x * G < 2^32
@@ -72,9 +73,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Attn
     const float* __restrict__ q = static_cast<const float*>(a.q);
     const float* __restrict__ k_new = static_cast<const float*>(a.k_new);
     const float* __restrict__ v_new = static_cast<const float*>(a.v_new);
-    const float* __restrict__ pool_k = static_cast<const float*>(a.b.pool_k);
-    const float* __restrict__ pool_v = static_cast<const float*>(a.b.pool_v);
-    const int32_t* __restrict__ table = a.b.block_table + (long long)it.req * a.b.table_stride;
+    const float* __restrict__ pool_k = static_cast<const float*>(a.pool_k);
+    const float* __restrict__ pool_v = static_cast<const float*>(a.pool_v);
+    const int32_t* __restrict__ table = a.block_table + (long long)it.req * a.table_stride;
 
     const int l16 = lane & 15, kg = lane >> 4;
     const int kv_limit = P + tok0 + div_g(h0 + rows_here - 1) + 1;  // keys [0, kv_limit) are visible to some row
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Attn
     const long long new_off = ((long long)(s0 - P) * Hkv + g) * D;  // of the fresh row at position 0
     auto copy_tile = [&](int step, bool is_k) {
         const int base = (w + step * NW) * KT;
-        const long long boff = (long long)__builtin_amdgcn_readlane(blk_vec, step - blk_base) * a.b.block_stride + (long long)g * kBlock * D;
+        const long long boff = (long long)__builtin_amdgcn_readlane(blk_vec, step - blk_base) * a.block_stride + (long long)g * kBlock * D;
         const float* pool = is_k ? pool_k : pool_v;
         const float* fresh = is_k ? k_new : v_new;
         const uint32_t dst = is_k ? k_addr : v_addr;
@@ -230,13 +231,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Attn
     // fused append: this workgroup owns the tokens whose first row (head 0 of the group) it holds
     if (a.fused_append) {
         const int tok_lo = tok0 + (h0 != 0), tok_hi = min(N - 1, tok0 + div_g(h0 + TR - 1));
-        float* wk_pool = static_cast<float*>(a.pool_k_w);
-        float* wv_pool = static_cast<float*>(a.pool_v_w);
+        float* wk_pool = static_cast<float*>(a.pool_k);
+        float* wv_pool = static_cast<float*>(a.pool_v);
         for (int idx = tid; idx < (tok_hi - tok_lo + 1) * (D / 4); idx += 64 * NW) {
             const int tok = tok_lo + idx / (D / 4), c4 = idx % (D / 4);
             const int pos = P + tok;
             const long long src = ((long long)(s0 + tok) * Hkv + g) * D + c4 * 4;
-            const long long dst = (long long)table[pos >> 4] * a.b.block_stride + ((long long)g * kBlock + (pos & 15)) * D + c4 * 4;
+            const long long dst = (long long)table[pos >> 4] * a.block_stride + ((long long)g * kBlock + (pos & 15)) * D + c4 * 4;
             *reinterpret_cast<f32x4*>(wk_pool + dst) = *reinterpret_cast<const f32x4*>(k_new + src);
             *reinterpret_cast<f32x4*>(wv_pool + dst) = *reinterpret_cast<const f32x4*>(v_new + src);
         }
@@ -283,19 +284,22 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Attn
     }
 }
 
+template <int D, class Work>
+void launch_one(const AttnLaunch& a, const Work& wk, int entries, int waves, hipStream_t s) {
+    const dim3 grid((unsigned)entries * a.kv_heads);
+    if (waves == 4) hipLaunchKernelGGL((attn_f32_kernel<D, 4, Work>), grid, dim3(256), 0, s, a, wk);
+    else hipLaunchKernelGGL((attn_f32_kernel<D, 8, Work>), grid, dim3(512), 0, s, a, wk);
+}
+template <class Work>
+void launch_list(const AttnLaunch& a, const Work& wk, int entries, int waves, hipStream_t s) {
+    a.head_dim == 64 ? launch_one<64>(a, wk, entries, waves, s) : launch_one<128>(a, wk, entries, waves, s);
+}
+
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s) {
     if (entries <= 0) return hipSuccess;
-    const dim3 grid((unsigned)entries * a.b.kv_heads);
-    const bool d64 = a.b.head_dim == 64;
-    if (waves == 4) {
-        if (d64) hipLaunchKernelGGL((attn_f32_kernel<64, 4>), grid, dim3(256), 0, s, a, wk);
-        else hipLaunchKernelGGL((attn_f32_kernel<128, 4>), grid, dim3(256), 0, s, a, wk);
-    } else {
-        if (d64) hipLaunchKernelGGL((attn_f32_kernel<64, 8>), grid, dim3(512), 0, s, a, wk);
-        else hipLaunchKernelGGL((attn_f32_kernel<128, 8>), grid, dim3(512), 0, s, a, wk);
-    }
+    wk.n_reqs <= kAttnReqStep ? launch_list(a, short_list(wk), entries, waves, s) : launch_list(a, wk, entries, waves, s);
     return hipGetLastError();
 }
 

@@ -58,7 +58,6 @@ int check_pool(const ragc_kv_pool* pool) {
 
 struct BatchInfo {
     int64_t total_new = 0;
-    int32_t max_new = 0;
 };
 
 // Host view of the batch metadata.  The h_* arrays of the batch are used when given; an array
@@ -131,7 +130,6 @@ int check_batch(const ragc_kv_pool* pool, const ragc_batch* b, bool need_device,
                     return fail(RAGC_ERR_RANGE, "request %d: block_table[%lld] = %d outside [0, %d)", r, (long long)i, row[i], pool->num_blocks);
         }
         info->total_new += n;
-        info->max_new = std::max<int32_t>(info->max_new, (int32_t)n);
     }
     if (info->total_new > (int64_t)1 << 30) return fail(RAGC_ERR_RANGE, "sum of new_len %lld too large", (long long)info->total_new);
     return RAGC_OK;
@@ -229,132 +227,148 @@ int cu_count() {
     return cus;
 }
 
-// How the bf16 path will run a batch: the (request, 128-row tile) work items, most key tiles
-// first so the long ones start early; how many copies of each item share its keys; which
-// kernel shape; and the workspace the copies need.  ragc_prefill_attn_workspace and
+// How the bf16 path will run a batch: which kernel, on row tiles of how many rows, with how many copies of
+// each item along its keys; and the workspace the copies may need.  ragc_prefill_attn_workspace and
 // ragc_prefill_attn both call this, so they always agree.
-struct Bf16Item {
-    int32_t cost;  // key tiles
-    ragc::AttnItem it;
-};
 struct Bf16Plan {
-    std::vector<Bf16Item> items;
+    std::vector<int32_t> order;  // requests with new tokens, most keys first
+    bool rows_kernel = false;    // attn_bf16_rows_kernel
+    int rows = ragc::kAttnRowsPerItem;
     int splits = 1;
-    int variant = ragc::kAttnVariantOneGroup;
+    int waves = 8;  // per workgroup of attn_bf16_rows_kernel
+    int variant = ragc::kAttnVariantOneGroup;  // of attn_bf16_kernel
     int64_t workspace = 0;
 };
 
+int64_t row_tiles(const HostMeta& h, int r, int group, int rows) { return ((int64_t)h.new_len[r] * group + rows - 1) / rows; }
+
+// Requests with the most keys first, and the row tiles of one request next to each other: long items start
+// early, and the workgroups that run at the same time on an XCD walk the key tiles of the same few requests at
+// about the same pace, so a tile fetched by one row tile is still in that XCD's L2 for the others.
+void order_requests(const HostMeta& h, int num_reqs, std::vector<int32_t>* order) {
+    order->reserve(num_reqs);
+    for (int r = 0; r < num_reqs; ++r)
+        if (h.new_len[r] > 0) order->push_back(r);
+    const auto keys = [&](int r) { return (int64_t)h.prefix_len[r] + h.new_len[r]; };
+    std::stable_sort(order->begin(), order->end(), [&](int x, int y) { return keys(x) > keys(y); });
+}
+
 int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta& h, int group, uint32_t flags, Bf16Plan* plan) {
+    int64_t items = 0, short_items = 0, max_rows = 0, max_keys = 0, sum_keys = 0;
     for (int r = 0; r < batch->num_reqs; ++r) {
-        const int n = h.new_len[r], p = h.prefix_len[r];
-        const int64_t rows = (int64_t)n * group;
-        const int64_t tiles = (rows + ragc::kAttnRowsPerItem - 1) / ragc::kAttnRowsPerItem;
+        const int64_t tiles = row_tiles(h, r, group, ragc::kAttnRowsPerItem);
         if (tiles > 65535) return fail(RAGC_ERR_RANGE, "request %d: new_len * group too large", r);
-        for (int t = 0; t < (int)tiles; ++t)
-            plan->items.push_back({ragc::attn_bf16_item_cost(p, n, group, t),
-                                   ragc::AttnItem{(uint32_t)r << 16 | (uint32_t)t, p, n, h.new_start[r]}});
+        if (tiles == 0) continue;
+        items += tiles;
+        const int64_t short_tiles = row_tiles(h, r, group, ragc::kAttnShortRows);
+        short_items += short_tiles;
+        sum_keys += short_tiles * ((int64_t)h.prefix_len[r] + h.new_len[r]);
+        max_rows = std::max(max_rows, (int64_t)h.new_len[r] * group);
+        max_keys = std::max(max_keys, (int64_t)h.prefix_len[r] + h.new_len[r]);
     }
-    // Order: requests by their most expensive row tile, longest first, and the row tiles of one
-    // request next to each other (longest first).  Long items start early, and the workgroups that
-    // run at the same time on an XCD walk the key tiles of the same few requests at about the same
-    // pace, so a tile fetched by one row tile is still in that XCD's L2 for the others.
-    std::vector<int32_t> req_cost(batch->num_reqs, 0);
-    for (const Bf16Item& it : plan->items) {
-        int32_t& c = req_cost[it.it.req_tile >> 16];
-        c = std::max(c, it.cost);
-    }
-    std::stable_sort(plan->items.begin(), plan->items.end(), [&](const Bf16Item& x, const Bf16Item& y) {
-        const uint32_t rx = x.it.req_tile >> 16, ry = y.it.req_tile >> 16;
-        if (rx != ry) return req_cost[rx] != req_cost[ry] ? req_cost[rx] > req_cost[ry] : rx < ry;
-        return x.cost > y.cost;
-    });
-    const int64_t wgs = (int64_t)plan->items.size() * pool->kv_heads;
+    order_requests(h, batch->num_reqs, &plan->order);
+    const int64_t wgs = items * pool->kv_heads;
     const int64_t cus = cu_count();
-    // Fewer work items than CUs: split each along its keys until every CU has one, keeping at
-    // least three key tiles per copy of the longest item (measured on eight small shapes: with the
-    // one-round-trip merge pass, copies of three to four tiles are still worth their fixed cost).
-    // ragc_debug_set_attn_plan overrides (tests).
+    const int force_splits = std::min(g_force_splits.load(std::memory_order_relaxed), ragc::kAttnMaxSplits);
+    const int force_variant = g_force_variant.load(std::memory_order_relaxed);
+    const bool may_split = !(flags & RAGC_ATTN_NO_SPLIT) && wgs > 0;
+    // The workspace: one 128-row partial result per item and copy, for as many copies as give every CU one with at
+    // least three 64-key tiles each.  The copies that are really made (below) never need more.
     int splits = 1;
-    if (!(flags & RAGC_ATTN_NO_SPLIT) && wgs > 0) {
+    if (may_split) {
         splits = (int)std::min<int64_t>(cus / wgs, ragc::kAttnMaxSplits);
-        splits = std::min(splits, plan->items.front().cost / 3);
-        if (const int force = g_force_splits.load(std::memory_order_relaxed); force > 0) splits = std::min(force, ragc::kAttnMaxSplits);
+        splits = (int)std::min<int64_t>(splits, (max_keys + 63) / 64 / 3);
+        if (force_splits > 0) splits = force_splits;
         if (splits < 1) splits = 1;
     }
-    plan->splits = splits;
+    plan->workspace = splits > 1 ? items * splits * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnRowsPerItem) : 0;
+    const int64_t short_wgs = short_items * pool->kv_heads;
+    // The 32-row kernel takes launches of at most 32 rows per request, and those that leave CUs without a 128-row item
+    // as long as its own workgroups, one per CU at a time, need at most two rounds: up to 256 of them it is 1.0-1.3
+    // times as fast as the 128-row kernel with split keys (one request of 1000 + 256 tokens: 14.7 us against 19.1), at
+    // 400-512 0.94-1.3 times, at 728 and more 0.5-0.9 times.
+    // Forced key splits go to it as well: the 128-row kernel does not split.
+    plan->rows_kernel = max_rows <= ragc::kAttnShortRows || (may_split && force_splits > 1) ||
+                        (force_variant < 0 && wgs < cus && short_wgs <= 2 * cus);
+    if (plan->rows_kernel) {
+        plan->rows = ragc::kAttnShortRows;
+        // Copies until every CU has a workgroup, of at least two 32-key tiles for each of its eight waves; up to 1280
+        // keys a copy of the whole range is faster than two copies and the merge pass (1000 keys, 8 workgroups: 10.4
+        // us against 13.0; 4096 keys, 8 copies: 17.9 us against 26.9).  The workspace is sized for the copies that
+        // 128-row items would have.
+        const int64_t tiles = (max_keys + 31) / 32;
+        const int64_t room = plan->workspace / (std::max<int64_t>(short_wgs, 1) * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnShortRows));
+        plan->splits = tiles <= 40 ? 1 : (int)std::min({room, cus / std::max<int64_t>(short_wgs, 1), tiles / 16});
+        if (may_split && force_splits > 0) plan->splits = force_splits;
+        if (plan->splits < 1) plan->splits = 1;
+        if (plan->splits > ragc::kAttnMaxSplits) plan->splits = ragc::kAttnMaxSplits;
+        // With more workgroups than CUs and few keys for each, four waves: a CU then holds two workgroups at a time
+        // and one streams while the other starts (128 decode requests of 300-1000 keys, 8 heads: 61 us against 67; 64
+        // of 512-2048: 64 against 61, since eight waves finish a long request sooner).
+        plan->waves = short_wgs > cus && sum_keys < 1024 * short_items ? 4 : 8;
+        if (force_variant >= 0) plan->waves = force_variant == 0 ? 4 : 8;
+        return 0;
+    }
     // With at least two workgroups per CU two 4-wave workgroups share a CU; otherwise one 8-wave
-    // workgroup divides its key tiles between two wave groups -- unless the items are already split
-    // along their keys (measured: 4-wave workgroups are then as fast or faster, 23.8 against 26.3 us
-    // on four decode requests of 4096 keys).  ragc_debug_set_attn_plan overrides (tests).
-    plan->variant = (splits > 1 || wgs >= 2 * cus) ? ragc::kAttnVariantOneGroup : ragc::kAttnVariantTwoGroups;
-    if (const int force = g_force_variant.load(std::memory_order_relaxed); force >= 0) plan->variant = force;
-    plan->workspace = splits > 1 ? (int64_t)plan->items.size() * splits * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim) : 0;
+    // workgroup divides its key tiles between two wave groups.  ragc_debug_set_attn_plan overrides (tests).
+    plan->variant = wgs >= 2 * cus ? ragc::kAttnVariantOneGroup : ragc::kAttnVariantTwoGroups;
+    if (force_variant >= 0) plan->variant = force_variant;
     return 0;
 }
 
 constexpr uint32_t kAttnFlags = RAGC_ATTN_APPEND_FUSED | RAGC_ATTN_NO_SPLIT | RAGC_ATTN_VALIDATE;
 
-// Enqueue the launches of a planned bf16 batch: every copy of an item is a list entry of its
-// own and a launch takes kAttnMaxItems entries, so a long list goes out in several launches
-// (each followed by its merge pass when the items are split).
-int run_bf16_plan(ragc::AttnLaunch& a, const Bf16Plan& plan, hipStream_t s) {
-    const int S = plan.splits;
-    const size_t per_launch = (size_t)ragc::kAttnMaxItems / S;
-    for (size_t i = 0; i < plan.items.size(); i += per_launch) {
-        ragc::AttnWorkList wl{}, leads{};
-        wl.splits = leads.splits = S;
-        wl.part_base = leads.part_base = (int32_t)(i * S);
-        const size_t cnt = std::min(per_launch, plan.items.size() - i);
-        for (size_t j = 0; j < cnt; ++j) {
-            for (int c = 0; c < S; ++c) wl.item[wl.n++] = plan.items[i + j].it;
-            leads.item[leads.n++] = plan.items[i + j].it;
+// Enqueues `launch(list, entries)` for the requests of `order`, as many per launch as the kernel arguments and a grid hold.
+template <class Launch>
+int run_list(const ragc::AttnLaunch& a, const HostMeta& h, const std::vector<int32_t>& order, int rows, int splits, const Launch& launch) {
+    // the kernels divide workgroup ids by head_div with a multiply that is exact below 2^32 / head_div
+    const int64_t max_workgroups = std::min<int64_t>(ragc::kAttnMaxWorkgroups, UINT32_MAX / a.head_div);
+    const int64_t per_launch = std::max<int64_t>(1, max_workgroups / ((int64_t)a.kv_heads * splits)) * splits;
+    int64_t slots = 0;
+    for (size_t i = 0; i < order.size(); i += ragc::kAttnMaxReqs) {
+        ragc::AttnWork wk;
+        wk.n_reqs = (int32_t)std::min<size_t>(ragc::kAttnMaxReqs, order.size() - i);
+        wk.splits = splits;
+        wk.part_base = (int32_t)slots;
+        int64_t items = 0;
+        for (int j = 0; j < wk.n_reqs; ++j) {
+            const int r = order[i + j];
+            wk.first[j] = (int32_t)items;
+            wk.req[j] = {h.prefix_len[r], h.new_len[r], h.new_start[r], r};
+            items += row_tiles(h, r, a.group, rows);
+            if (items * splits > INT32_MAX) return fail(RAGC_ERR_RANGE, "new_len * group of the batch too large");
         }
-        hipError_t e = ragc::launch_attn_bf16(a, wl, plan.variant, s);
-        if (e == hipSuccess && S > 1) e = ragc::launch_attn_bf16_merge(a, leads, s);
-        if (e != hipSuccess)
-            return fail(RAGC_ERR_HIP, "prefill attention launch %zu of %zu: %s (earlier launches of this call stay enqueued)",
-                        i / per_launch + 1, (plan.items.size() + per_launch - 1) / per_launch, hipGetErrorString(e));
+        for (int j = wk.n_reqs; j % ragc::kAttnReqStep; ++j) wk.first[j] = INT32_MAX;
+        const int64_t entries = items * splits;
+        for (int64_t e0 = 0; e0 < entries; e0 += per_launch) {
+            wk.entry0 = (int32_t)e0;
+            const hipError_t e = launch(wk, (int)std::min<int64_t>(per_launch, entries - e0));
+            if (e != hipSuccess) return fail(RAGC_ERR_HIP, "prefill attention launch: %s (earlier launches of this call stay enqueued)", hipGetErrorString(e));
+        }
+        slots += entries;
     }
     return RAGC_OK;
 }
 
-// fp32 path: requests with the most keys first, so that their workgroups start early.  With at most one
-// workgroup per CU a workgroup has eight waves, so that every SIMD still has two to overlap (256 workgroups
-// of ~1100 keys: 31 us against 37); with more, four, and two workgroups share a CU (416 of ~1000 keys:
-// 45 us against 49, 512 of ~1100: 53 against 58).
-int run_f32(ragc::AttnLaunch& a, const ragc_batch* batch, const HostMeta& h, hipStream_t s) {
-    constexpr int TR = ragc::kAttnF32RowsPerItem;
+int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& plan, hipStream_t s) {
+    return run_list(a, h, plan.order, plan.rows, plan.splits, [&](const ragc::AttnWork& wk, int entries) {
+        hipError_t e = plan.rows_kernel ? ragc::launch_attn_bf16_rows(a, wk, entries, plan.waves, s) : ragc::launch_attn_bf16(a, wk, entries, plan.variant, s);
+        if (e == hipSuccess && wk.splits > 1) e = ragc::launch_attn_bf16_merge(a, wk, entries, s);
+        return e;
+    });
+}
+
+// fp32 path.  With at most one workgroup per CU a workgroup has eight waves, so that every SIMD still has two to
+// overlap (256 workgroups of ~1100 keys: 31 us against 37); with more, four, and two workgroups share a CU (416 of
+// ~1000 keys: 45 us against 49, 512 of ~1100: 53 against 58).
+int run_f32(const ragc::AttnLaunch& a, const ragc_batch* batch, const HostMeta& h, hipStream_t s) {
     std::vector<int32_t> order;
-    order.reserve(batch->num_reqs);
+    order_requests(h, batch->num_reqs, &order);
     int64_t tiles = 0;
-    const auto tiles_of = [&](int r) { return ((int64_t)h.new_len[r] * a.group + TR - 1) / TR; };
-    for (int r = 0; r < batch->num_reqs; ++r)
-        if (h.new_len[r] > 0) {
-            order.push_back(r);
-            tiles += tiles_of(r);
-        }
-    const auto keys = [&](int r) { return (int64_t)h.prefix_len[r] + h.new_len[r]; };
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return keys(x) > keys(y); });
-    const int waves = tiles * a.b.kv_heads > (int64_t)cu_count() ? 4 : 8;
-    const int32_t per_launch = std::max(1, ragc::kAttnF32MaxWorkgroups / a.b.kv_heads);
-    for (size_t i = 0; i < order.size(); i += ragc::kAttnMaxReqs) {
-        ragc::AttnWork wk;
-        wk.n_reqs = (int32_t)std::min<size_t>(ragc::kAttnMaxReqs, order.size() - i);
-        int64_t entries = 0;
-        for (int j = 0; j < wk.n_reqs; ++j) {
-            const int r = order[i + j];
-            wk.req[j] = {(int32_t)entries, h.prefix_len[r], h.new_len[r], h.new_start[r]};
-            wk.id[j] = (uint16_t)r;
-            entries += tiles_of(r);
-            if (entries > INT32_MAX) return fail(RAGC_ERR_RANGE, "new_len * group of the batch too large");
-        }
-        for (int64_t e0 = 0; e0 < entries; e0 += per_launch) {
-            wk.entry0 = (int32_t)e0;
-            const hipError_t e = ragc::launch_attn_f32(a, wk, (int)std::min<int64_t>(per_launch, entries - e0), waves, s);
-            if (e != hipSuccess) return hip_fail(e, "prefill attention launch");
-        }
-    }
-    return RAGC_OK;
+    for (int r : order) tiles += row_tiles(h, r, a.group, ragc::kAttnF32RowsPerItem);
+    const int waves = tiles * a.kv_heads > (int64_t)cu_count() ? 4 : 8;
+    return run_list(a, h, order, ragc::kAttnF32RowsPerItem, 1,
+                    [&](const ragc::AttnWork& wk, int entries) { return ragc::launch_attn_f32(a, wk, entries, waves, s); });
 }
 
 // ---- partial results of key-split work items for callers that cannot allocate --------------
@@ -412,22 +426,28 @@ int prefill_attn_impl(const ragc_kv_pool* pool, const ragc_batch* batch, const v
     if (validate)
         if (int rc = validate_batch(pool, batch, h, (flags & RAGC_ATTN_APPEND_FUSED) != 0)) return rc;
 
+    const auto magic = [](uint32_t d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
     ragc::AttnLaunch a;
-    a.b = make_paged(pool, batch);
+    a.pool_k = pool->k;
+    a.pool_v = pool->v;
+    a.block_stride = pool->block_stride_elems;
+    a.block_table = batch->block_table;
     a.q = q;
     a.k_new = k_new;
     a.v_new = v_new;
     a.out = out;
-    a.pool_k_w = pool->k;
-    a.pool_v_w = pool->v;
     a.partial = nullptr;
+    a.table_stride = batch->table_stride;
+    a.kv_heads = pool->kv_heads;
+    a.head_dim = pool->head_dim;
     a.q_heads = q_heads;
     a.group = q_heads / pool->kv_heads;
-    a.group_magic = a.group == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + a.group - 1) / a.group);
+    a.group_magic = magic(a.group);
     a.scale_log2e = softmax_scale * 1.44269504088896340736f;
     a.fused_append = (flags & RAGC_ATTN_APPEND_FUSED) ? 1 : 0;
-    a.max_new = info.max_new;
-    a.total_new = (int32_t)info.total_new;
+    a.head_shift = pool->kv_heads % 8 == 0 ? 3 : 0;
+    a.head_div = (uint32_t)pool->kv_heads >> a.head_shift;
+    a.head_magic = magic(a.head_div);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (pool->dtype == RAGC_DTYPE_F32) {
         return run_f32(a, batch, h, s);
@@ -448,7 +468,7 @@ int prefill_attn_impl(const ragc_kv_pool* pool, const ragc_batch* batch, const v
             a.partial = workspace;
         }
     }
-    return run_bf16_plan(a, plan, s);
+    return run_bf16_plan(a, h, plan, s);
 }
 
 }  // namespace

@@ -26,81 +26,92 @@ struct PagedBatch {
     int32_t head_dim;
 };
 
+// What every workgroup of an attention launch needs besides its work item.
 struct AttnLaunch {
-    PagedBatch b;
+    void* pool_k;
+    void* pool_v;
+    int64_t block_stride;  // elements between blocks of one plane
+    const int32_t* block_table;
     const void* q;
     const void* k_new;
     const void* v_new;
     void* out;
-    void* pool_k_w;  // writable aliases of the pool planes (fused append)
-    void* pool_v_w;
-    void* partial;   // workspace for the partial results of work items split along the keys (bf16 path)
+    void* partial;  // workspace for the partial results of work items split along the keys (bf16 path)
+    int32_t table_stride;
+    int32_t kv_heads;
+    int32_t head_dim;
     int32_t q_heads;
-    int32_t group;      // q_heads / kv_heads
+    int32_t group;         // q_heads / kv_heads
     uint32_t group_magic;  // ceil(2^32 / group), 0 for group 1: row / group by one multiply in the kernels
-    float scale_log2e;  // softmax_scale * log2(e)
+    float scale_log2e;     // softmax_scale * log2(e)
     int32_t fused_append;
-    int32_t max_new;  // max over requests of new_len (host-side)
-    int32_t total_new;
+    int32_t head_shift;    // workgroup id -> (kv head, entry), see split_block_id: 3 if kv_heads is a multiple of 8, else 0,
+    uint32_t head_div;     // kv_heads >> head_shift,
+    uint32_t head_magic;   // and ceil(2^32 / head_div), 0 for 1
 };
 
 // The requests of one attention launch, in the kernel arguments: request i of the list owns the work
-// entries [first, first of the next one), one per row tile, and carries its lengths, so a workgroup
-// needs no device array before it can look up its first block ids.
+// items [first, first of the next one), one per row tile, and carries its lengths, so a workgroup
+// needs no device array before it can look up its first block ids.  With `splits` = S > 1 every item is
+// S work entries in a row (entry e is copy e % S of item e / S), and entry e leaves its partial result in
+// slot part_base + e of the workspace.
 constexpr int kAttnMaxReqs = 192;
+constexpr int kAttnReqStep = 16;             // unused entries of `first` up to the next multiple hold INT_MAX
+constexpr int kAttnMaxWorkgroups = 1 << 22;  // of one launch: grid times workgroup size stays below 2^32 threads
 struct AttnReq {
-    int32_t first;
     int32_t prefix_len;
     int32_t new_len;
     int32_t new_start;
+    int32_t id;  // which request of the batch
 };
-struct AttnWork {
+template <int REQS>
+struct AttnWorkN {
     int32_t n_reqs;
+    int32_t splits;
+    int32_t part_base;
     int32_t entry0;  // first entry of this launch (one launch holds so many workgroups)
-    AttnReq req[kAttnMaxReqs];
-    uint16_t id[kAttnMaxReqs];  // which request of the batch
+    int32_t first[REQS];
+    AttnReq req[REQS];
 };
+using AttnWork = AttnWorkN<kAttnMaxReqs>;
+// A launch of up to kAttnReqStep requests takes a list of just that size: 0.45 KB of kernel arguments instead of
+// 4 KB, which the host writes in 3.5 us per launch instead of 4.2.
+using AttnWorkShort = AttnWorkN<kAttnReqStep>;
+inline AttnWorkShort short_list(const AttnWork& w) {
+    AttnWorkShort s;
+    s.n_reqs = w.n_reqs;
+    s.splits = w.splits;
+    s.part_base = w.part_base;
+    s.entry0 = w.entry0;
+    for (int i = 0; i < kAttnReqStep; ++i) {
+        s.first[i] = w.first[i];
+        s.req[i] = i < w.n_reqs ? w.req[i] : AttnReq{};
+    }
+    return s;
+}
 
 constexpr int kAttnF32RowsPerItem = 16;
-constexpr int kAttnF32MaxWorkgroups = 1 << 22;  // of one launch: grid times workgroup size stays below 2^32 threads
 // waves: 4 or 8 per workgroup
 hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
 
-// bf16 path: the host orders the (request, row tile) work items by cost and passes
-// them in the kernel argument buffer (no device staging); long lists go out in
-// several launches.
+// bf16 path.  Large batches: row tiles of kAttnRowsPerItem rows (attn_bf16.hip).  Launches that cannot fill the chip
+// with those: kAttnShortRows rows (attn_bf16_rows.hip).
 constexpr int kAttnRowsPerItem = 128;
-constexpr int kAttnMaxItems = 224;
-// One work item carries the request's lengths, so a workgroup needs no memory round trip
-// before it can look up its first block ids.
-struct AttnItem {
-    uint32_t req_tile;   // request << 16 | row tile
-    int32_t prefix_len;
-    int32_t new_len;
-    int32_t new_start;
-};
-// bytes of one partial result: O [rows][D] fp32, then (max, sum) per row
-inline int64_t attn_partial_bytes(int head_dim) { return (int64_t)kAttnRowsPerItem * (head_dim + 2) * 4; }
+constexpr int kAttnShortRows = 32;
+// bytes of one partial result of a key-split item: O [rows][D] fp32, then (max, sum) per row
+inline int64_t attn_partial_bytes(int head_dim, int rows) { return (int64_t)rows * (head_dim + 2) * 4; }
 constexpr int kAttnMaxSplits = 16;
-// With `splits` = S > 1 every work item appears S times in a row (entry e is copy e % S) and
-// entry e leaves its partial result in slot part_base + e of the workspace.
-struct AttnWorkList {
-    int32_t n;
-    int32_t splits;
-    int32_t part_base;
-    int32_t pad;
-    AttnItem item[kAttnMaxItems];
-};
 enum AttnVariant {
     kAttnVariantOneGroup = 0,   // 4 waves per workgroup, two workgroups per CU
     kAttnVariantTwoGroups = 1,  // 8 waves per workgroup on alternating key tiles
     kAttnVariantCount = 2
 };
-// number of 64-key tiles the work item (row tile `tile` of kAttnRowsPerItem rows) walks
-int attn_bf16_item_cost(int prefix, int new_len, int group, int tile);
-hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWorkList& wl, int variant, hipStream_t s);
-// second pass after a launch of split items: `wl` lists copy 0 of every item; combines the partial results into `out`
-hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWorkList& wl, hipStream_t s);
+// entries: items times wk.splits, from wk.entry0 on
+hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, hipStream_t s);
+// waves: 4 or 8 per workgroup
+hipError_t launch_attn_bf16_rows(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
+// second pass after a launch of split items of the 32-row kernel: combines the partial results into `out`
+hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWork& wk, int entries, hipStream_t s);
 
 hipError_t launch_append(const PagedBatch& b, void* pool_k, void* pool_v, const void* k_new, const void* v_new,
                          int32_t total_new, int esize, hipStream_t s);

@@ -577,3 +577,23 @@ def test_fp32_matrix_core_kernel_at_its_edges(H, hq, hkv, d, lens):
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "f32")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "f32")))
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens,flags", [
+    (8, 2, 128, [(20000, 1), (9000, 3), (8191, 2)], B.RAGC_ATTN_NO_SPLIT),        # block ids of a wave: several windows
+    (8, 2, 128, [(20000, 1), (17, 3)], 0),                                        # split keys; more copies than the short request has tiles
+    (4, 4, 64, [(31, 1), (32, 1), (33, 32), (0, 1), (255, 31), (257, 2)], 0),     # tile edges, first and last row
+    (12, 4, 128, [(700, 11), (15, 10), (48, 32)], 0),                             # group of 3: tokens straddle 32-row tiles
+    (8, 8, 128, [((37 * i) % 200, 1 + i % 3) for i in range(200)], 0),            # more requests than one launch lists, 4 waves each
+    (16, 8, 64, [((91 * i) % 3000, i % 2) for i in range(17)], 0),                # one more request than the short list
+    (32, 8, 128, [(1500, 100)], 0),                                               # a prefill request: 13 row tiles, split keys
+], ids=["windows", "split", "edges", "group3", "R200", "R17", "prefill"])
+def test_short_row_kernel_at_its_edges(H, hq, hkv, d, lens, flags):
+    """Launches of 32-row workgroups (decode steps, small prefills) against the oracle within the bf16 bound,
+    and the fused append byte for byte."""
+    w = W.make_small("bf16", hq, hkv, d, lens, seed=7800 + len(lens) + d, q_gain=2.0)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED | flags)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
