@@ -26,66 +26,80 @@ __device__ __forceinline__ int find_request(const int32_t* __restrict__ new_star
 // 16-byte chunks per plane, four of K and four of V per thread, all loads issued before the
 // first store.  For one head the 16 rows land next to each other in the pool (a 16-token block
 // is contiguous per head), so a wave writes whole 1 KiB runs and the workgroup reads 16 row
-// pieces of 1 KiB or more; both sides stay within a few DRAM pages.  The rows are resolved to
-// their paged slots once per workgroup (16 threads) and shared through LDS.  Loads and stores
-// are nontemporal: nothing here is touched twice.
+// pieces of 1 KiB or more; both sides stay within a few DRAM pages.  Every wave
+// resolves the rows to their paged slots itself, lane i row i.  Loads and stores are nontemporal:
+// nothing here is touched twice.
+//
+// What bounds it: HBM on large calls, the trips to memory in a row on small ones.  Where a chunk
+// comes from does not depend on its slot, so the sources are under way while the slots are looked
+// up, and up to 64 requests are searched in registers after one trip; 48 registers let all of a
+// call of 16000 rows run at once.  16 requests, 8710 rows, 8 heads of 128 in bf16, 71 MB moved:
+// 17.2 -> 15.7 us (4.5 TB/s; a large copy runs at 4.7 on the same card).  More requests than 64
+// are searched in memory as before: the lanes hold no more.
 constexpr int kAppendRows = 16;
 constexpr int kAppendUnroll = 4;
 constexpr int kAppendChunksPerGroup = 256 * kAppendUnroll;
 
-__global__ __launch_bounds__(256) void append_kernel(PagedBatch b, char* __restrict__ pool_k, char* __restrict__ pool_v,
-                                                     const char* __restrict__ k_new, const char* __restrict__ v_new,
-                                                     int total_new, int esize, int head_groups) {
-    __shared__ long long slot_off[kAppendRows];  // byte offset of (block, head 0, slot) of each row; -1: no such row
+__global__ __launch_bounds__(256, 8) void append_kernel(PagedBatch b, char* __restrict__ pool_k, char* __restrict__ pool_v,
+                                                        const char* k_new, const char* v_new,
+                                                        int total_new, int esize, int head_groups) {
     const int first_row = b.new_start[0];  // a sub-batch may start anywhere in the packed arrays
     // the head group varies fastest, so workgroups that run together cover whole source rows
     const int hg = blockIdx.x % head_groups;
     const int t0 = (blockIdx.x / head_groups) * kAppendRows;
+    const int rows = min(kAppendRows, total_new - t0);
     const int head_bytes = b.head_dim * esize;
-    if (threadIdx.x < kAppendRows) {
-        const int t_rel = t0 + threadIdx.x;
-        long long off = -1;
-        if (t_rel < total_new) {
-            const int t = first_row + t_rel;
-            const int r = find_request(b.new_start, b.num_reqs, t);
-            const int pos = b.prefix_len[r] + (t - b.new_start[r]);
-            const int blk = b.block_table[(long long)r * b.table_stride + (pos >> 4)];
-            off = ((long long)blk * b.block_stride + (long long)(pos & 15) * b.head_dim) * esize;
+    const int lane = threadIdx.x & 63;
+    const int t = first_row + t0 + min(lane & (kAppendRows - 1), rows - 1);
+    int r, start, prefix;
+    if (b.num_reqs <= 64) {  // one request per lane, then find_request among the lanes
+        const int mine = min(lane, b.num_reqs - 1);
+        const int starts = b.new_start[mine], prefixes = b.prefix_len[mine];
+        r = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1) {
+            const int s = __shfl(starts, r + step, 64);  // r + step <= 63
+            if (r + step < b.num_reqs && s <= t) r += step;
         }
-        slot_off[threadIdx.x] = off;
+        start = __shfl(starts, r, 64);
+        prefix = __shfl(prefixes, r, 64);
+    } else {
+        r = find_request(b.new_start, b.num_reqs, t);
+        start = b.new_start[r];
+        prefix = b.prefix_len[r];
     }
-    __syncthreads();
+    const int pos = prefix + (t - start);
+    const int blk = b.block_table[(long long)r * b.table_stride + (pos >> 4)];
     // chunks per head is 8, 16 or 32 (head_dim 64 or 128, 2 or 4 bytes per element)
     const int cph_shift = __ffs(head_bytes >> 4) - 1;
     const int per_head_shift = cph_shift + 4;  // chunks of one head over the 16 rows
     const int total = b.kv_heads << per_head_shift;
-    const long long row_bytes = (long long)b.kv_heads * head_bytes;
+    const int row_bytes = b.kv_heads * head_bytes;  // at most 65535 * 512
     const long long src0 = (long long)(first_row + t0) * row_bytes;
-    const long long dst_head_stride = (long long)kBlock * head_bytes;
     u32x4 kk[kAppendUnroll], vv[kAppendUnroll];
-    long long dst[kAppendUnroll];
 #pragma unroll
     for (int u = 0; u < kAppendUnroll; ++u) {
-        const int idx = hg * kAppendChunksPerGroup + u * 256 + threadIdx.x;  // (head, row, chunk), chunk fastest
-        dst[u] = -1;
-        if (idx < total) {
-            const int g = idx >> per_head_shift;
-            const int row = (idx >> cph_shift) & (kAppendRows - 1);
-            const int ch = idx & ((1 << cph_shift) - 1);
-            const long long so = slot_off[row];
-            if (so >= 0) {
-                dst[u] = so + g * dst_head_stride + (ch << 4);
-                const long long src = src0 + row * row_bytes + (long long)g * head_bytes + (ch << 4);
-                kk[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
-                vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
-            }
-        }
+        // (head, row, chunk), chunk fastest; past the end the last chunk again, and for a row that is not there the last one
+        const int idx = min(hg * kAppendChunksPerGroup + u * 256 + (int)threadIdx.x, total - 1);
+        const int row = min((idx >> cph_shift) & (kAppendRows - 1), rows - 1);
+        const int in_row = (idx >> per_head_shift) * head_bytes + ((idx & ((1 << cph_shift) - 1)) << 4);
+        const long long src = src0 + row * row_bytes + in_row;
+        kk[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k_new + src));
+        vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v_new + src));
     }
+    // no load sinks below, next to the store that uses it (the sources are not __restrict__ for the same reason)
+    asm volatile("" ::: "memory");
+    // lane i holds the byte offset of (block, head 0, slot) of row i
+    const long long slot = ((long long)blk * b.block_stride + (long long)(pos & 15) * b.head_dim) * esize;
 #pragma unroll
     for (int u = 0; u < kAppendUnroll; ++u) {
-        if (dst[u] >= 0) {
-            __builtin_nontemporal_store(kk[u], reinterpret_cast<u32x4*>(pool_k + dst[u]));
-            __builtin_nontemporal_store(vv[u], reinterpret_cast<u32x4*>(pool_v + dst[u]));
+        const int idx = hg * kAppendChunksPerGroup + u * 256 + threadIdx.x;
+        const int row = (idx >> cph_shift) & (kAppendRows - 1);
+        const long long so = __shfl(slot, row, 64);
+        if (idx < total && row < rows) {
+            const long long dst = so + (idx >> per_head_shift) * (kBlock * head_bytes) + ((idx & ((1 << cph_shift) - 1)) << 4);
+            __builtin_nontemporal_store(kk[u], reinterpret_cast<u32x4*>(pool_k + dst));
+            __builtin_nontemporal_store(vv[u], reinterpret_cast<u32x4*>(pool_v + dst));
         }
     }
 }

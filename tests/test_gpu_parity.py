@@ -597,3 +597,19 @@ def test_short_row_kernel_at_its_edges(H, hq, hkv, d, lens, flags):
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
+
+
+@pytest.mark.parametrize("dtype,hkv,d", [("bf16", 1, 64), ("bf16", 3, 128), ("f32", 8, 128), ("f32", 2, 64), ("bf16", 40, 64)])
+@pytest.mark.parametrize("reqs", [1, 63, 64, 65, 130])
+def test_append_kernel_at_its_edges(H, dtype, hkv, d, reqs):
+    """Requests found among the lanes of a wave (up to 64) and by a search in memory (more), some of them empty,
+    rows that do not fill the last workgroup, heads that do not fill a workgroup's chunks: byte for byte."""
+    lens = [((13 * i) % 50, (7 * i + 3) % 6 if i % 9 else 0) for i in range(reqs)] if reqs > 1 else [(21, 35)]
+    w = W.make_small(dtype, hkv, hkv, d, lens, seed=7900 + reqs)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    dw = H.DeviceWorkload(w)
+    dw.append()
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, dtype)))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, dtype)))
