@@ -41,6 +41,14 @@ namespace {
 
 constexpr int TM = kAttnRowsPerItem;  // rows per work item
 
+template <int N, class F>
+__device__ __forceinline__ void static_for(const F& f) {
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
 template <int D, int NG, int RING, class Work>
 __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
     constexpr int NSUB = 2;             // 32-key halves of a tile
@@ -129,31 +137,34 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     // ---- DMA: wave (grp, wq) copies block wq (16 keys) of tile step*NG+grp, K and V planes.
     // Lane i of DMA instruction c brings row RPI*c + i/CPR of the block, 16-byte chunk
     // (i%CPR) ^ swz(row): the swizzle is applied on the global side, LDS is written linearly.
-    uint32_t pool_loff[IPB], new_loff[IPB];  // byte offsets of this lane's chunk inside a pool block / a run of fresh rows
+    // Byte offsets of this lane's chunks inside the source, less what the instruction's own offset adds: inside a pool
+    // block, or (from the first fresh block on) inside a run of fresh rows.
+    uint32_t loff[IPB];
+    auto set_loff = [&](int row_stride) {
 #pragma unroll
-    for (int c = 0; c < IPB; ++c) {
-        const int row16 = RPI * c + lane / CPR;
-        const int chunk = (lane % CPR) ^ swz<D>(row16);
-        pool_loff[c] = (row16 * D + chunk * 8) * 2;
-        new_loff[c] = (row16 * Hkv * D + chunk * 8) * 2;
-    }
+        for (int c = 0; c < IPB; ++c) {
+            const int row16 = RPI * c + lane / CPR;
+            const int chunk = (lane % CPR) ^ swz<D>(row16);
+            loff[c] = (row16 * row_stride + chunk * 8) * 2 - c * 1024;
+        }
+    };
+    set_loff(D);
+    bool loff_fresh = false;
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     // The copy of one step is prepared (addresses) right after the barrier and its DMA
     // instructions are then slipped between the MFMAs of S^T = K.Q^T, where their issue cost
     // hides under the matrix pipe; `flush` issues whatever is still pending at once.
     int pend = 0;              // 1: a fast-path copy (uniform base + per-lane constant) waits to be issued
-    bool pend_fresh = false;   // source is the run of fresh rows, else one pool block
     uint64_t pend_kb = 0, pend_vb = 0;
     uint32_t pend_dst = 0;
-    auto emit = [&](int c) {
-        const uint32_t lo = pend_fresh ? new_loff[c] : pool_loff[c];
-        dma_16B_per_lane(pend_kb, lo, pend_dst + RPI * c * ROWB);
-        dma_16B_per_lane(pend_vb, lo, pend_dst + RPI * c * ROWB + PLANEB);
+    // copy instructions 2 i and 2 i + 1 of the 2 IPB of a step, K first, then V
+    auto emit = [&](auto i_c) {
+        constexpr int I = 2 * decltype(i_c)::value, C = I % IPB;
+        dma_two_runs<C * 1024>(I < IPB ? pend_kb : pend_vb, loff[C], loff[C + 1], I < IPB ? pend_dst : pend_dst + PLANEB);
     };
     auto flush = [&]() {
         if (pend) {
-#pragma unroll
-            for (int c = 0; c < IPB; ++c) emit(c);
+            static_for<IPB>(emit);
             pend = 0;
         }
     };
@@ -174,7 +185,6 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
             pend_kb = uniform_u64(reinterpret_cast<const char*>(pool_k) + boff);
             pend_vb = uniform_u64(reinterpret_cast<const char*>(pool_v) + boff);
             pend_dst = dst;
-            pend_fresh = false;
             pend = 1;
         } else if (kbase >= P && kbase + 16 <= kv_limit) {
             // 16 fresh rows, all inside the horizon
@@ -182,7 +192,10 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
             pend_kb = uniform_u64(reinterpret_cast<const char*>(k_new) + boff);
             pend_vb = uniform_u64(reinterpret_cast<const char*>(v_new) + boff);
             pend_dst = dst;
-            pend_fresh = true;
+            if (!loff_fresh) {  // no pool block follows
+                loff_fresh = true;
+                set_loff(Hkv * D);
+            }
             pend = 1;
         } else {
             // the block straddles the prefix end or the horizon: choose the source per row, issue
@@ -273,9 +286,9 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
 #pragma unroll
             for (int sub = 0; sub < NSUB; ++sub)
                 kbuf[ks][sub] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(kst + sub * 32 * ROWB + koff[ks]);
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            if (ks + 2 < KSTEPS) {
+        static_for<KSTEPS>([&](auto ks_c) {
+            constexpr int ks = decltype(ks_c)::value;
+            if constexpr (ks + 2 < KSTEPS) {
 #pragma unroll
                 for (int sub = 0; sub < NSUB; ++sub)
                     kbuf[(ks + 2) % 3][sub] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(kst + sub * 32 * ROWB + koff[ks + 2]);
@@ -283,8 +296,13 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
 #pragma unroll
             for (int sub = 0; sub < NSUB; ++sub)
                 sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kbuf[ks % 3][sub], qreg[ks], sacc[sub], 0, 0, 0);
-            if (ks < IPB && pend) emit(ks);  // two DMA instructions in the shadow of the MFMAs just issued
-        }
+            // Two copy instructions behind every other k-step: 8 waves of a CU that issue theirs in one burst after the
+            // barrier queue for the address unit (all behind the first four k-steps: 16 x (256-4096 + 64-768) tokens, 32/8
+            // heads 300 us against 296, 12 x (1000-2000 + 60-200) 77.6 against 75.8).
+            if constexpr (ks % 2 == 0) {
+                if (pend) emit(std::integral_constant<int, ks / 2>{});
+            }
+        });
         pend = 0;
         // causal frontier / end of sequence: only tiles that reach past the first row's horizon
         if (base + NSUB * 32 > wave_vis_min) {

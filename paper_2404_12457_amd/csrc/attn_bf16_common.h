@@ -41,6 +41,17 @@ __device__ __forceinline__ void dma_16B_per_lane(uint64_t sbase, uint32_t lane_o
     // one), and without it the compiler may move the LDS reads of the current tile across the copy.
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(sbase) : "m0");
 }
+// Two runs of 64 x 16 bytes: run i comes from sbase + off_i + OFF0 + 1024 i and lands at lds_addr + OFF0 + 1024 i (the
+// instruction's offset counts on both sides, so one write of M0 serves both).  sbase is in scalar registers that a vector
+// instruction may have written: five wait states before the first load reads them.
+template <int OFF0>
+__device__ __forceinline__ void dma_two_runs(uint64_t sbase, uint32_t off0, uint32_t off1, uint32_t lds_addr) {
+    static_assert(OFF0 + 1024 < 4096, "offset field");
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
+        ::"s"(lds_addr), "v"(off0), "v"(off1), "s"(sbase), "n"(OFF0), "n"(OFF0 + 1024)
+        : "m0");
+}
 __device__ __forceinline__ uint64_t uniform_u64(const void* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
