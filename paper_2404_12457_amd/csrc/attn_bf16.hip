@@ -31,8 +31,8 @@
 //                                B = P^T, which is exactly the accumulator layout of
 //                                S^T after conversion to bf16 -- no data movement.
 // With v_mfma_f32_32x32x16_bf16 a lane holds 16 of the 32 keys of a sub-tile for its
-// row; the other 16 sit in lane+32, so a row max costs one half-swap.  The running
-// max is only raised (and O, l rescaled) when a tile exceeds it by more than 2^8.
+// row; the other 16 sit in lane+32.  The row's reference exponent is only raised (and O, l
+// rescaled) when a tile's probabilities against it sum to more than 2^8.
 #include "attn_bf16_common.h"
 #include "attn_work.h"
 
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-    float m_run = -INFINITY;  // reference exponent of O and l (log2 domain); at most 2^8 below the true row max
+    float m_run = -INFINITY;  // reference exponent of O and l (log2 domain): a lane's probabilities of a tile sum to at most 2^8
     float l_run = 0.f;        // this lane's partial of the running sum (other half in lane^32)
     const float c = a.scale_log2e;
 
@@ -314,43 +314,54 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
                     if (kidx >= my_vis) sacc[sub][i] = -INFINITY;
                 }
         }
-        // online softmax, one row per lane pair (lane, lane^32)
-        float mx = sacc[0][0];
+        // Online softmax, one row per lane pair (lane, lane ^ 32), without a maximum: the probabilities are taken against
+        // the row's reference exponent as it stands, and only where a lane's sum of them says that a score may be 2^8 above
+        // it (or that the row has no reference yet: 2^inf, or NaN where every key is masked) is the maximum looked up, the
+        // reference raised and O, l rescaled.  Against a maximum per tile this takes 22 vector instructions and the trip
+        // maximum -> ballot -> branch -> exponentials out of a step: 24 requests at head_dim 64 73.5 -> 70.4 us, 12 x
+        // (1000-2000 + 60-200) tokens at 128 79.3 -> 77.2, others equal or better.  The first step looks the maximum up at
+        // once: weighing twice there cost 4 % on calls of one or two tiles.  One check per 32 keys instead of 64: 5 % more
+        // on the first of these, 9 % less on batches with one item per CU.
+        // The row sum is taken over the bf16-rounded probabilities, the same weights the PV product uses, so that the
+        // rounding of P cancels between numerator and denominator.
+        bf16x8 pb[NSUB][2];
+        float psum;
+        auto weigh = [&](float m_sub) {
+            psum = 0.f;
 #pragma unroll
-        for (int sub = 0; sub < NSUB; ++sub)
+            for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[sub][i]);
-        mx = fmaxf(mx, other_half(mx));
-        const float m_tile = mx * c;
-        const bool raise = m_tile > m_run + kRescaleThreshold;  // true on a row's first visible tile (m_run = -inf)
-        if (__builtin_amdgcn_ballot_w64(raise) != 0) {
-            // 1 where nothing changes, 0 on a row's first visible tile (exp2(-inf))
-            const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - m_tile) : 1.f;
-            m_run = raise ? m_tile : m_run;
+                for (int i = 0; i < 16; i += 2) {
+                    const float p0 = __builtin_amdgcn_exp2f(sacc[sub][i] * c - m_sub);
+                    const float p1 = __builtin_amdgcn_exp2f(sacc[sub][i + 1] * c - m_sub);
+                    const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
+                    psum = __builtin_amdgcn_fdot2_f32_bf16(pp, kOnes2, psum, false);
+                    pb[sub][i >> 3][i & 7] = pp[0];
+                    pb[sub][i >> 3][(i & 7) + 1] = pp[1];
+                }
+        };
+        bool raise_any = step == 0;  // there the rows have no reference yet, as a rule
+        if (!raise_any) {
+            weigh(m_run);
+            raise_any = __builtin_amdgcn_ballot_w64(!(psum <= kRaiseSum)) != 0;
+        }
+        if (raise_any) {
+            float mx = sacc[0][0];
+#pragma unroll
+            for (int sub = 0; sub < NSUB; ++sub)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[sub][i]);
+            mx = fmaxf(mx, other_half(mx)) * c;
+            const bool raise = mx > m_run;
+            const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - mx) : 1.f;  // 0 where the row has no reference yet
+            m_run = raise ? mx : m_run;
             l_run *= alpha;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
+            weigh(m_run == -INFINITY ? 0.f : m_run);  // still no visible key: exp2(-inf - 0) = 0
         }
-        // a row that has not seen a key yet (possible in the second wave group) has m_run = -inf
-        // and only masked scores: subtract 0 instead, so that exp2(-inf - 0) = 0 and not NaN
-        const float m_sub = m_run == -INFINITY ? 0.f : m_run;
-        // The row sum is taken over the bf16-rounded probabilities, the same weights the PV
-        // product uses, so that the rounding of P cancels between numerator and denominator.
-        float psum = 0.f;
-        bf16x8 pb[NSUB][2];
-#pragma unroll
-        for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                const float p0 = __builtin_amdgcn_exp2f(sacc[sub][i] * c - m_sub);
-                const float p1 = __builtin_amdgcn_exp2f(sacc[sub][i + 1] * c - m_sub);
-                const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                psum = __builtin_amdgcn_fdot2_f32_bf16(pp, kOnes2, psum, false);
-                pb[sub][i >> 3][i & 7] = pp[0];
-                pb[sub][i >> 3][(i & 7) + 1] = pp[1];
-            }
         l_run += psum;
 
         // O^T += V^T P^T ; V rows fetched with the transposing LDS read

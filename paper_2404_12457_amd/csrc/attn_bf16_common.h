@@ -17,6 +17,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int TN = 64;                    // keys per LDS tile
 constexpr float kRescaleThreshold = 8.f;  // log2 units
+constexpr float kRaiseSum = 256.f;        // of a lane's probabilities of a tile
 constexpr bf16x2 kOnes2 = {(__bf16)1.0f, (__bf16)1.0f};
 
 // Wave-wide copy of 64 x 16 bytes from global memory straight into LDS: lane i's 16 bytes

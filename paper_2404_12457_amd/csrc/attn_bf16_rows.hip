@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;  // as in attn_bf16_kernel: m lags the maximum by at most 2^8, l is this lane's part
+    float m_run = -INFINITY, l_run = 0.f;  // reference exponent, at most 2^8 below the maximum so far; l is this lane's part
     const float c = a.scale_log2e;
 
     auto do_tile = [&](int step, auto more_c) {

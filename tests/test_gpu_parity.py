@@ -613,3 +613,14 @@ def test_append_kernel_at_its_edges(H, dtype, hkv, d, reqs):
     torch.cuda.synchronize()
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, dtype)))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, dtype)))
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (4, 4, 64)])
+@pytest.mark.parametrize("gain", [0.0, 8.0, 40.0])
+def test_reference_exponent_follows_the_scores(H, variant, hq, hkv, d, gain, force_plan):
+    """Scores that are all equal, that pass the reference now and then, and that jump by more than 2^100 between
+    tiles, over rows whose first tile (or whose wave group) holds no visible key."""
+    force_plan(variant)
+    lens = [(0, 140), (63, 70), (64, 33), (500, 40), (1, 1), (1000, 65)]
+    _check_all(H, W.make_small("bf16", hq, hkv, d, lens, seed=8100 + int(gain), q_gain=gain))
