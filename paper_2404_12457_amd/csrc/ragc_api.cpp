@@ -287,9 +287,22 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
     // as long as its own workgroups, one per CU at a time, need at most two rounds: up to 256 of them it is 1.0-1.3
     // times as fast as the 128-row kernel with split keys (one request of 1000 + 256 tokens: 14.7 us against 19.1), at
     // 400-512 0.94-1.3 times, at 728 and more 0.5-0.9 times.
+    // Between one and two 128-row items per CU it takes batches of half-empty items, whose idle rows the 128-row kernel
+    // pays for like others while a second round of items starts: at most two 32-row workgroups per CU (MHA requests of
+    // 33-64 new tokens: 416 of 272 keys 10.7 us against 16.6, 448 of 2800 keys 91 against 112), or three with short key
+    // ranges (592 of 189 keys 15.1 us against 19.6, 672 of 844: 46 against 51; but 640 of 2261: 88 against 85).  With
+    // exactly one item per CU there is no second round (424 workgroups of 1811 keys: 53.7 us against 49.7).
+    const bool half_empty = wgs > cus && wgs < 2 * cus &&
+                            (short_wgs <= 2 * cus || (pool->head_dim == 128 && short_wgs <= 3 * cus && max_keys <= 1024));
+    // At head_dim 64 several of its four-wave workgroups fit a CU next to each other, and it takes ragged batches as well:
+    // with at most two 128-row items per CU the 128-row kernel takes as long as its longest item, the 32-row kernel as
+    // long as its workgroups take in all, and the latter is less while their keys, per CU, are at most twice those of the
+    // longest request (in these units 1.6: 19.5 us against 24.4, 2.0: 20.3 against 23.5, 2.5: 24.7 against 24.4, 3: 28.6
+    // against 26.1).  At head_dim 128 it loses at 1.6 already (45.8 against 42.5).
+    const bool ragged_d64 = pool->head_dim == 64 && wgs < 2 * cus && sum_keys * pool->kv_heads <= 2 * cus * max_keys;
     // Forced key splits go to it as well: the 128-row kernel does not split.
     plan->rows_kernel = max_rows <= ragc::kAttnShortRows || (may_split && force_splits > 1) ||
-                        (force_variant < 0 && wgs < cus && short_wgs <= 2 * cus);
+                        (force_variant < 0 && ((wgs < cus && short_wgs <= 2 * cus) || half_empty || ragged_d64));
     if (plan->rows_kernel) {
         plan->rows = ragc::kAttnShortRows;
         // Copies until every CU has a workgroup, of at least two 32-key tiles for each of its eight waves; up to 1280
@@ -304,8 +317,9 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
         if (plan->splits > ragc::kAttnMaxSplits) plan->splits = ragc::kAttnMaxSplits;
         // With more workgroups than CUs and few keys for each, four waves: a CU then holds two workgroups at a time
         // and one streams while the other starts (128 decode requests of 300-1000 keys, 8 heads: 61 us against 67; 64
-        // of 512-2048: 64 against 61, since eight waves finish a long request sooner).
-        plan->waves = short_wgs > cus && sum_keys < 1024 * short_items ? 4 : 8;
+        // of 512-2048: 64 against 61, since eight waves finish a long request sooner).  At head_dim 64 four such workgroups
+        // fit, and with more than two per CU four waves win whatever the keys (704 of 2036 keys: 19.5 us against 22.7).
+        plan->waves = short_wgs > cus && (sum_keys < 1024 * short_items || (pool->head_dim == 64 && short_wgs > 2 * cus)) ? 4 : 8;
         if (force_variant >= 0) plan->waves = force_variant == 0 ? 4 : 8;
         return 0;
     }

@@ -624,3 +624,21 @@ def test_reference_exponent_follows_the_scores(H, variant, hq, hkv, d, gain, for
     force_plan(variant)
     lens = [(0, 140), (63, 70), (64, 33), (500, 40), (1, 1), (1000, 65)]
     _check_all(H, W.make_small("bf16", hq, hkv, d, lens, seed=8100 + int(gain), q_gain=gain))
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (32, 32, 128, [((53 * i) % 300, 33 + i % 20) for i in range(10)]),                     # 320-640 half-empty items of 128 rows
+    (32, 32, 128, [((17 * i) % 90, 33 + i % 32) for i in range(12)]),                      # more than two 32-row workgroups per CU
+    (32, 8, 64, [(1900, 130), (300, 60), (16, 100), (700, 90), (15, 64), (0, 130)]),       # ragged, four waves per workgroup
+    (64, 8, 64, [(2500, 33), (40, 70), (0, 31), (900, 50), (100, 64)]),
+    (12, 4, 64, [((211 * i) % 2400, 20 + 11 * (i % 5)) for i in range(20)]),               # more requests than the short list, group of 3
+], ids=["half_empty", "three_per_cu", "ragged", "ragged_gqa8", "ragged_R20"])
+def test_batches_between_the_two_bf16_kernels_match_oracle(H, hq, hkv, d, lens):
+    """Batches of one or two 128-row items per CU that go to the 32-row kernel: all rows against the oracle, and the
+    fused append byte for byte."""
+    w = W.make_small("bf16", hq, hkv, d, lens, seed=8200 + len(lens) + d)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
