@@ -1,5 +1,6 @@
 // bf16 prefix-cached paged attention for launches that cannot fill the chip with 128-row work
-// items: decode steps, a few new tokens per request, one or two short requests.
+// items: decode steps, a few new tokens per request, one or two short requests, batches of
+// half-empty items (plan_bf16 holds the rule).
 //
 // out[t,h,:] = softmax_j(scale * q[t,h,:].K_j) V_j over j = 0..prefix+i: cached keys from
 // 16-token pool blocks through the block table (paper Sec. 5.1), the rest from the request's
