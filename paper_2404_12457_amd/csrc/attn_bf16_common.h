@@ -23,7 +23,8 @@ constexpr bf16x2 kOnes2 = {(__bf16)1.0f, (__bf16)1.0f};
 // Wave-wide copy of 64 x 16 bytes from global memory straight into LDS: lane i's 16 bytes
 // land at lds_addr + 16*i.  Issued as inline assembly on purpose: the compiler's own
 // bookkeeping for this instruction drains every outstanding load before the next LDS read,
-// which would serialise the ring; the waits are placed by hand (wait_vmcnt + block_barrier).
+// which would serialise the copies; the waits are placed by hand (wait_vmcnt, and block_barrier
+// where a tile is shared between waves).
 // The s_nop is required: the LDS address travels in M0, and a scalar write of M0 needs one wait
 // state before an LDS-DMA instruction reads it (inside inline assembly nobody inserts it for us;
 // without it the copy can land at the previous instruction's LDS address).
@@ -31,16 +32,18 @@ __device__ __forceinline__ void dma_16B_per_lane(const void* gptr, uint32_t lds_
     lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);  // wave-uniform by construction; make the register class explicit
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory", "m0");
 }
-// same with a wave-uniform base address and a 32-bit per-lane byte offset
+// Same with a wave-uniform base address and a 32-bit per-lane byte offset.  The base is in scalar registers that a vector
+// instruction (a readfirstlane) may have written just before: five wait states before the load reads them.
 __device__ __forceinline__ void dma_16B_per_lane(uint64_t sbase, uint32_t lane_off, uint32_t lds_addr) {
     lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
     // a scalar register pair whatever the compiler knows or does not know about the value
     uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sbase), hi = __builtin_amdgcn_readfirstlane((uint32_t)(sbase >> 32));
     asm volatile("" : "+s"(lo), "+s"(hi));
     sbase = ((uint64_t)hi << 32) | lo;
-    // No "memory" clobber: the slot this copy writes is not read before the next barrier (which has
-    // one), and without it the compiler may move the LDS reads of the current tile across the copy.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(sbase) : "m0");
+    // No "memory" clobber, so that the compiler may move LDS reads of another buffer across the copy.  Reads of the buffer it
+    // writes cannot come near it: the callers put a wait with such a clobber between the last read and the copy
+    // (lgkmcnt(0), or block_barrier) and another one between the copy and the next read (wait_vmcnt).
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(sbase) : "m0");
 }
 // Two runs of 64 x 16 bytes: run i comes from sbase + off_i + OFF0 + 1024 i and lands at lds_addr + OFF0 + 1024 i (the
 // instruction's offset counts on both sides, so one write of M0 serves both).  sbase is in scalar registers that a vector
