@@ -250,9 +250,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
 
     // ---- combine the waves' states: O = sum_w O_w 2^(m_w - m), l = sum_w l_w 2^(m_w - m), m = max_w m_w.  Every wave
     // leaves its O in its own part of LDS, [row][chunk of 4 columns], chunks XORed with the row against bank conflicts.
+    // l is exactly 0 in a wave that has seen no key of the row, and its O is not looked at; m = -inf does not say so: a
+    // wave whose scores were all NaN still has it, next to l = NaN and O = NaN, which must reach the output.
     l_run += other_half(l_run);
     if (hf == 0) MLs[w][l32] = float2{m_run, l_run};
-    if (l32 < rows_here && m_run != -INFINITY) {
+    if (l32 < rows_here && l_run != 0.f) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
         f32x4 o[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
-            if (ml[x].x == -INFINITY) continue;  // a wave, or every one of a copy, may have seen no key of the row
+            if (ml[x].y == 0.f) continue;  // a wave, or every one of a copy, may have seen no key of the row
             const float wgt = __builtin_amdgcn_exp2f(ml[x].x - m);
             l += ml[x].y * wgt;
 #pragma unroll

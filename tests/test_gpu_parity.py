@@ -642,3 +642,35 @@ def test_batches_between_the_two_bf16_kernels_match_oracle(H, hq, hkv, d, lens):
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
+
+
+@pytest.mark.parametrize("dtype,d,variant,splits", [
+    ("bf16", 128, None, None), ("bf16", 64, None, None), ("bf16", 128, 0, 16), ("bf16", 64, 1, 7), ("bf16", 128, 0, 1), ("bf16", 64, 1, 1),
+    ("f32", 128, None, None), ("f32", 64, None, None)])
+@pytest.mark.parametrize("new", [1, 3, 40])
+def test_nan_keys_reach_every_row_that_sees_them_and_no_other(H, dtype, d, variant, splits, new, force_plan):
+    """K of kv head 1 is NaN in 32 adjacent cached tokens -- all that one wave, or one copy of a split item, sees of a
+    short range -- and in one fresh token: the rows of that head's group that see such a key are NaN in full, all
+    others match the oracle.  The next request has nothing but NaN keys in head 0."""
+    force_plan(variant, splits)
+    hq, hkv = 8, 2
+    lens = [(200, new), (1100, new), (40, new), (0, new), (64, 1)]
+    w = W.make_small(dtype, hq, hkv, d, lens, seed=8300 + d + new)
+    dw = H.DeviceWorkload(w)
+    nan = float("nan")
+    affected = np.zeros((w.total_new, hq), bool)
+    for r, first in ((0, 64), (1, 992)):
+        dw.pool_k[torch.from_numpy(w.block_table[r, first // 16:first // 16 + 2].astype(np.int64)).cuda(), 1] = nan
+        affected[w.new_slice(r), hq // 2:] = True
+    s3 = int(w.new_start[3])  # request 3: its last fresh token, seen by that token alone
+    dw.k_new[s3 + new - 1, 1] = nan
+    affected[s3 + new - 1, hq // 2:] = True
+    s4 = w.new_slice(4)
+    dw.pool_k[torch.from_numpy(w.block_table[4, :4].astype(np.int64)).cuda(), 0] = nan
+    dw.k_new[s4, 0] = nan
+    affected[s4, :hq // 2] = True
+    got = U.out_to_f64(H.to_host(dw.attn()), dtype)
+    want = U.oracle_all(w)
+    assert np.all(np.isnan(got[affected]))
+    assert np.all(np.isfinite(got[~affected]))
+    assert np.max(np.abs(got[~affected] - want[~affected])) <= U.TOL[dtype]
