@@ -209,6 +209,12 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_sub);
         l_run += (p[0] + p[1]) + (p[2] + p[3]);
+        if (!MORE && base + KT > kv_limit) {
+            // rows past the horizon hold the last visible V again, which 0 times its probability only takes out while
+            // it is finite (the K rows are masked whatever they hold)
+            for (int x = lane; x < (base + KT - kv_limit) * CPR; x += 64)
+                *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(vbuf + (kv_limit - base) * ROWB + x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll

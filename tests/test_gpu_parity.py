@@ -674,3 +674,14 @@ def test_nan_keys_reach_every_row_that_sees_them_and_no_other(H, dtype, d, varia
     assert np.all(np.isnan(got[affected]))
     assert np.all(np.isfinite(got[~affected]))
     assert np.max(np.abs(got[~affected] - want[~affected])) <= U.TOL[dtype]
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (8, 2, 128)])
+def test_fp32_infinite_v_of_the_newest_token_gives_infinity(H, hq, hkv, d):
+    """The last visible row of V is infinite where the visible range ends inside a block: the row that sees it is
+    infinite, not NaN, as no key past the range weighs anything."""
+    w = W.make_small("f32", hq, hkv, d, [(0, 1), (5, 1), (30, 1), (300, 1), (2000, 1), (47, 1)], seed=8400)
+    dw = H.DeviceWorkload(w)
+    dw.v_new.fill_(float("inf"))
+    out = dw.attn()
+    assert bool((out == float("inf")).all())
