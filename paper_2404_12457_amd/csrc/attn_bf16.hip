@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     // copy instructions 2 i and 2 i + 1 of the 2 IPB of a step, K first, then V
     auto emit = [&](auto i_c) {
         constexpr int I = 2 * decltype(i_c)::value, C = I % IPB;
-        dma_two_runs<C * 1024>(I < IPB ? pend_kb : pend_vb, loff[C], loff[C + 1], I < IPB ? pend_dst : pend_dst + PLANEB);
+        dma_runs<2, C * 1024>(I < IPB ? pend_kb : pend_vb, loff + C, I < IPB ? pend_dst : pend_dst + PLANEB);
     };
     auto flush = [&]() {
         if (pend) {

@@ -32,29 +32,28 @@ __device__ __forceinline__ void dma_16B_per_lane(const void* gptr, uint32_t lds_
     lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);  // wave-uniform by construction; make the register class explicit
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(gptr) : "memory", "m0");
 }
-// Same with a wave-uniform base address and a 32-bit per-lane byte offset.  The base is in scalar registers that a vector
-// instruction (a readfirstlane) may have written just before: five wait states before the load reads them.
-__device__ __forceinline__ void dma_16B_per_lane(uint64_t sbase, uint32_t lane_off, uint32_t lds_addr) {
-    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
-    // a scalar register pair whatever the compiler knows or does not know about the value
-    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sbase), hi = __builtin_amdgcn_readfirstlane((uint32_t)(sbase >> 32));
-    asm volatile("" : "+s"(lo), "+s"(hi));
-    sbase = ((uint64_t)hi << 32) | lo;
-    // No "memory" clobber, so that the compiler may move LDS reads of another buffer across the copy.  Reads of the buffer it
-    // writes cannot come near it: the callers put a wait with such a clobber between the last read and the copy
-    // (lgkmcnt(0), or block_barrier) and another one between the copy and the next read (wait_vmcnt).
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(sbase) : "m0");
-}
-// Two runs of 64 x 16 bytes: run i comes from sbase + off_i + OFF0 + 1024 i and lands at lds_addr + OFF0 + 1024 i (the
-// instruction's offset counts on both sides, so one write of M0 serves both).  sbase is in scalar registers that a vector
-// instruction may have written: five wait states before the first load reads them.
-template <int OFF0>
-__device__ __forceinline__ void dma_two_runs(uint64_t sbase, uint32_t off0, uint32_t off1, uint32_t lds_addr) {
-    static_assert(OFF0 + 1024 < 4096, "offset field");
-    asm volatile(
-        "s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
-        ::"s"(lds_addr), "v"(off0), "v"(off1), "s"(sbase), "n"(OFF0), "n"(OFF0 + 1024)
-        : "m0");
+// N runs of 64 x 16 bytes from a wave-uniform base address: run i comes from sbase + off[i] + OFF0 + 1024 i and lands at
+// lds_addr + OFF0 + 1024 i (the instruction's offset counts on both sides, so one write of M0 serves all).  sbase is in scalar
+// registers that a vector instruction (a readfirstlane) may have written just before: five wait states before the first load
+// reads them.
+// No "memory" clobber, so that the compiler may move LDS reads of another buffer across the copies.  Reads of the buffer they
+// write cannot come near: the callers put a wait with such a clobber between the last read and the copies (lgkmcnt(0), or
+// block_barrier) and another one between the copies and the next read (wait_vmcnt).
+template <int N, int OFF0 = 0>
+__device__ __forceinline__ void dma_runs(uint64_t sbase, const uint32_t* off, uint32_t lds_addr) {
+    static_assert((N == 2 || N == 4) && OFF0 + (N - 1) * 1024 < 4096, "offset field");
+    if constexpr (N == 2)
+        asm volatile(
+            "s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
+            ::"s"(lds_addr), "v"(off[0]), "v"(off[1]), "s"(sbase), "n"(OFF0), "n"(OFF0 + 1024)
+            : "m0");
+    else
+        asm volatile(
+            "s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %5 offset:%6\n\tglobal_load_lds_dwordx4 %2, %5 offset:%7\n\t"
+            "global_load_lds_dwordx4 %3, %5 offset:%8\n\tglobal_load_lds_dwordx4 %4, %5 offset:%9"
+            ::"s"(lds_addr), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sbase), "n"(OFF0), "n"(OFF0 + 1024),
+              "n"(OFF0 + 2048), "n"(OFF0 + 3072)
+            : "m0");
 }
 __device__ __forceinline__ uint64_t uniform_u64(const void* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);

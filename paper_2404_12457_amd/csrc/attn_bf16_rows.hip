@@ -99,13 +99,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     lds_char* const kbuf = (lds_char*)smem + w * (2 * PLANEB);
     lds_char* const vbuf = kbuf + PLANEB;
     const uint32_t k_addr = (uint32_t)(uintptr_t)kbuf;
-    uint32_t pool_loff[IPB], new_loff[IPB];
+    uint32_t pool_loff[IPB], new_loff[IPB];  // less what the instructions' own offsets add
 #pragma unroll
     for (int c = 0; c < IPB; ++c) {
         const int row16 = RPI * c + lane / CPR;
         const int chunk = (lane % CPR) ^ swz<D>(row16);
-        pool_loff[c] = (row16 * D + chunk * 8) * 2;
-        new_loff[c] = (row16 * Hkv * D + chunk * 8) * 2;
+        pool_loff[c] = (row16 * D + chunk * 8) * 2 - c * 1024;
+        new_loff[c] = (row16 * Hkv * D + chunk * 8) * 2 - c * 1024;
     }
     auto copy_tile = [&](int step, bool is_k) {
         const __bf16* pool = is_k ? pool_k : pool_v;
@@ -116,13 +116,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
             const int blk = __builtin_amdgcn_readlane(blk_vec, 2 * (step - blk_base) + b);
             const uint32_t dst = k_addr + (is_k ? 0 : PLANEB) + b * kBlock * ROWB;
             if (kbase + kBlock <= P) {  // cached: one pool block
-                const uint64_t src = uniform_u64(pool + (long long)blk * a.block_stride + (long long)g * kBlock * D);
-#pragma unroll
-                for (int c = 0; c < IPB; ++c) dma_16B_per_lane(src, pool_loff[c], dst + RPI * c * ROWB);
+                dma_runs<IPB>(uniform_u64(pool + (long long)blk * a.block_stride + (long long)g * kBlock * D), pool_loff, dst);
             } else if (kbase >= P && kbase + kBlock <= kv_limit) {  // 16 fresh rows, all inside the horizon
-                const uint64_t src = uniform_u64(fresh + ((long long)(s0 + kbase - P) * Hkv + g) * D);
-#pragma unroll
-                for (int c = 0; c < IPB; ++c) dma_16B_per_lane(src, new_loff[c], dst + RPI * c * ROWB);
+                dma_runs<IPB>(uniform_u64(fresh + ((long long)(s0 + kbase - P) * Hkv + g) * D), new_loff, dst);
             } else {  // the prefix or the horizon ends inside, or before: keys past the horizon repeat the last visible one
 #pragma unroll 1
                 for (int c = 0; c < IPB; ++c) {

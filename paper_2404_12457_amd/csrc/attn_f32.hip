@@ -118,20 +118,22 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
         const float* pool = is_k ? pool_k : pool_v;
         const float* fresh = is_k ? k_new : v_new;
         const uint32_t dst = is_k ? k_addr : v_addr;
+        auto copy_runs = [&](uint64_t src, int row_bytes) {  // four instructions, 4 KiB of LDS, at a time
+#pragma unroll
+            for (int n0 = 0; n0 < NI; n0 += 4) {
+                uint32_t off[4];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const int row = RPI * (n0 + n) + lane / CPR, chunk = lane % CPR;
+                    off[n] = (uint32_t)(row * row_bytes + (is_k ? chunk ^ row : chunk) * 16 - n * 1024);
+                }
+                dma_runs<4>(src, off, dst + n0 * 1024);
+            }
+        };
         if (base + KT <= P) {  // one pool block: uniform base, per-lane constant offset
-            const uint64_t src = uniform_u64(pool + boff);
-#pragma unroll
-            for (int n = 0; n < NI; ++n) {
-                const int row = RPI * n + lane / CPR, chunk = lane % CPR;
-                dma_16B_per_lane(src, (uint32_t)(row * ROWB + (is_k ? chunk ^ row : chunk) * 16), dst + n * 1024);
-            }
+            copy_runs(uniform_u64(pool + boff), ROWB);
         } else if (base >= P && base + KT <= kv_limit) {  // fresh rows, all inside the horizon
-            const uint64_t src = uniform_u64(fresh + new_off + (long long)base * new_row);
-#pragma unroll
-            for (int n = 0; n < NI; ++n) {
-                const int row = RPI * n + lane / CPR, chunk = lane % CPR;
-                dma_16B_per_lane(src, (uint32_t)(row * new_row * 4 + (is_k ? chunk ^ row : chunk) * 16), dst + n * 1024);
-            }
+            copy_runs(uniform_u64(fresh + new_off + (long long)base * new_row), new_row * 4);
         } else {  // the prefix or the horizon ends inside: source per row; keys past the horizon repeat the last visible one
 #pragma unroll 1
             for (int n = 0; n < NI; ++n) {
