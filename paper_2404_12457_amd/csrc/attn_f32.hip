@@ -160,16 +160,26 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
     auto do_tile = [&](int step, auto more_c) {
         constexpr bool MORE = decltype(more_c)::value;  // another tile follows
         wait_vmcnt<NI>();  // K is here, V may be under way
-        f32x4 s_even = {0.f, 0.f, 0.f, 0.f}, s_odd = s_even;  // two chains: a product waits for the one before it
+        // Eight chains of products: a product waits for the one before it, and every one of a chain rounds at the size of
+        // the sum so far.  Against 64 bits, 4 requests of 512-1024 + 32-100 tokens, five draws: relative error 4.0e-7 to
+        // 4.2e-7 and largest 3.6e-6 to 4.9e-6; with two chains 5.8e-7 to 6.1e-7 and 6.0e-6 to 1.6e-5 in the same time.
+        constexpr int CH = 8;
+        f32x4 sp[CH];
+#pragma unroll
+        for (int x = 0; x < CH; ++x) sp[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < KJ; ++j) {
             const f32x4 kr = *reinterpret_cast<lds_f32x4*>(kbuf + koff[j]);
 #pragma unroll
-            for (int e = 0; e < 4; e += 2) {
-                s_even = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e], qreg[j][e], s_even, 0, 0, 0);
-                s_odd = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e + 1], qreg[j][e + 1], s_odd, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) {
+                f32x4& x = sp[(4 * j + e) % CH];
+                x = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e], qreg[j][e], x, 0, 0, 0);
             }
         }
+#pragma unroll
+        for (int n = CH / 2; n > 0; n /= 2)
+#pragma unroll
+            for (int x = 0; x < n; ++x) sp[x] += sp[x + n];
         if (MORE) {
             if (step + 1 - blk_base >= 64) {
                 blk_base = step + 1;
@@ -181,7 +191,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
         }
         f32x4 s;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] = (s_even[i] + s_odd[i]) * sc;
+        for (int i = 0; i < 4; ++i) s[i] = sp[0][i] * sc;
         const int base = (w + step * NW) * KT;
         if (base + KT > vis_min) {
 #pragma unroll
