@@ -22,8 +22,10 @@
 // overlaps the other's MFMAs.  With many work items NG = 1 and two workgroups share
 // a CU instead.
 //
-// Launches too small to fill the chip with such items go to attn_bf16_rows_kernel, which can also
-// split them along the keys across workgroups.
+// Launches too small to fill the chip with such items go to attn_bf16_rows_kernel, or are split along
+// the keys ACROSS workgroups (SPLIT, NG = 1): every item then appears S times, each copy walks 1/S of
+// the key tiles and leaves its unnormalised O and its (max, sum) per row in the caller's workspace,
+// and attn_bf16_merge_kernel combines the S partial results of every row.
 //
 // The products are computed transposed so that a lane owns ONE query row:
 //   S^T[key][row] = K . Q^T      A = K tile (LDS, 16-byte reads), B = Q (registers)
@@ -49,8 +51,10 @@ __device__ __forceinline__ void static_for(const F& f) {
     }
 }
 
-template <int D, int NG, int RING, class Work>
-__global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
+template <int D, int NG, bool SPLIT, class Work>
+__global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
+    static_assert(!SPLIT || NG == 1, "copies of an item are one wave group each");
+    constexpr int RING = 2;             // stages per wave group
     constexpr int NSUB = 2;             // 32-key halves of a tile
     constexpr int CPR = D / 8;          // 16-byte chunks per K/V row
     constexpr int ROWB = D * 2;         // bytes per row
@@ -58,7 +62,6 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     constexpr int STAGEB = 2 * PLANEB;
     constexpr int RPI = 64 / CPR;       // rows covered by one wave-wide 1 KiB DMA instruction
     constexpr int IPB = 16 / RPI;       // DMA instructions per 16-row block and plane
-    constexpr int LPS = 2 * IPB;        // DMA instructions per wave and step
     constexpr int KSTEPS = D / 16;
     constexpr int DT = D / 32;
     constexpr int NSTAGE = NG * RING;
@@ -73,7 +76,8 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = NG == 1 ? 0 : w >> 2, wq = w & 3;
-    const WorkItem it = find_item(wk, entry, a.group, TM);
+    const int S = SPLIT ? wk.splits : 1, sidx = SPLIT ? entry % S : 0;
+    const WorkItem it = find_item(wk, SPLIT ? entry / S : entry, a.group, TM);
     const int tile = it.tile;
 
     const int G = a.group;
@@ -96,8 +100,10 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
 
     const int last_row = min(row0 + TM, rows_total) - 1;
     const int kv_limit = P + div_g(last_row) + 1;  // keys [0, kv_limit) are visible to some row of the item
-    const int ntiles = (kv_limit + TN - 1) / TN;
-    const int nsteps = (ntiles + NG - 1) / NG;  // group `grp` takes tile step*NG + grp
+    const int ntiles_all = (kv_limit + TN - 1) / TN;
+    // copy sidx of S takes tiles [t_lo, ntiles); more copies than tiles: nothing for some, but each of them leaves a state
+    const int t_lo = ntiles_all * sidx / S, ntiles = ntiles_all * (sidx + 1) / S;
+    const int nsteps = (ntiles - t_lo + NG - 1) / NG;  // group `grp` takes tile t_lo + step*NG + grp
 
     // ---- this lane's query row
     const int wrow0 = row0 + wq * 32;
@@ -117,7 +123,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     int blk_base = 0;
     int blk_vec;
     {
-        const int e = (min(lane * NG + grp, ntiles - 1) * TN >> 4) + wq;
+        const int e = (min(t_lo + lane * NG + grp, max(ntiles - 1, 0)) * TN >> 4) + wq;
         blk_vec = e < nblk_item ? table[e] : 0;
     }
     bf16x8 qreg[KSTEPS];
@@ -171,11 +177,11 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     auto prepare = [&](int step) {
         if (step - blk_base >= 64) {
             blk_base = step;
-            const int e = (min((step + lane) * NG + grp, ntiles - 1) * TN >> 4) + wq;
+            const int e = (min(t_lo + (step + lane) * NG + grp, ntiles - 1) * TN >> 4) + wq;
             blk_vec = e < nblk_item ? table[e] : 0;
             asm volatile("" ::"v"(blk_vec));  // the compiler's wait for this load stays inside the branch
         }
-        const int tg = min(step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
+        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
         const int kbase = tg * TN + wq * 16;
         const int blk = __builtin_amdgcn_readlane(blk_vec, step - blk_base);
         const uint32_t dst = smem_addr + (grp * RING + step % RING) * STAGEB + wq * 16 * ROWB;
@@ -257,13 +263,11 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     // one step with the ring slot as a compile-time constant
     auto do_step = [&](int step, auto slot_c) {
         constexpr int SLOT = decltype(slot_c)::value;
-        // loads of this step have landed (later steps may stay in flight)
-        if (RING > 2 && step + RING - 2 < nsteps) wait_vmcnt<(RING - 2) * LPS>();
-        else wait_vmcnt<0>();
+        wait_vmcnt<0>();  // the copies of this step have landed
         block_barrier();  // every wave's part is in LDS, and every wave is done with the previous step
-        if (step + RING - 1 < nsteps) prepare(step + RING - 1);
+        if (step + 1 < nsteps) prepare(step + 1);
 
-        const int tg = step * NG + grp;
+        const int tg = t_lo + step * NG + grp;
         const int base = tg * TN;  // first key this wave looks at
         if (!wave_active || tg >= ntiles || base >= wave_vis_max) {
             flush();
@@ -382,27 +386,20 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
             }
     };
 
-#pragma unroll
-    for (int s = 0; s < RING - 1; ++s)
-        if (s < nsteps) {
-            prepare(s);
-            flush();
-        }
-
+    if (!SPLIT || nsteps > 0) {
+        prepare(0);
+        flush();
+    }
     for (int step0 = 0; step0 < nsteps; step0 += RING) {
         do_step(step0, std::integral_constant<int, 0>{});
         if (step0 + 1 < nsteps) do_step(step0 + 1, std::integral_constant<int, 1>{});
-        if (RING > 2) {
-            if (step0 + 2 < nsteps) do_step(step0 + 2, std::integral_constant<int, 2 % RING>{});
-            if (step0 + 3 < nsteps) do_step(step0 + 3, std::integral_constant<int, 3 % RING>{});
-        }
     }
 
     // ---- fused append (after the key loop: nothing waits for it, and the fresh rows are L2-hot
     // because the loop has just read them as keys; requested up front, next to Q, the rows cost 1-4 %
-    // on the prefill configurations and gain 1-2 % on decode steps).  This work item owns the tokens
+    // on the prefill configurations and gain 1-2 % on decode steps).  This work item (its last copy) owns the tokens
     // whose first row (head 0 of the group) it holds; 16-byte chunks, four per thread in flight.
-    if (a.fused_append) {
+    if (a.fused_append && sidx == S - 1) {
         const int tok_lo = div_g(row0 + G - 1);
         const int tok_hi = min(N - 1, div_g(row0 + TM - 1));
         __bf16* wk = static_cast<__bf16*>(a.pool_k);
@@ -460,7 +457,7 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
         if (wave_active) {
             const f32x4 ml = xw[DT * 4 * 64];
             const float m1 = ml[0], l1 = ml[1];
-            // a group may have seen no visible key of a row: weight 0
+            // a group may have seen no visible key of a row: weight 0 (which lets NaN through)
             const float m = fmaxf(m_run, m1);
             const float s0f = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
             const float s1f = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
@@ -488,6 +485,32 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     static_assert(32 * OROWB <= WSTRIDE * 4, "output patch fits the merge area");
     lds_char* const patch = lds0 + wq * (NG > 1 ? WSTRIDE * 4 : 32 * OROWB);
     const float l_tot = l_run + other_half(l_run);
+    if (SPLIT) {
+        // one of S copies: O (unnormalised, fp32), max and sum of every row go to the workspace, [TM][D] floats of O, then
+        // [TM][2] floats (max, sum).  Same turn through LDS as below, in two passes of D/2 floats per row.
+        float* const part = static_cast<float*>(a.partial) + ((long long)(wk.part_base + entry) * Hkv + g) * (TM * (D + 2));
+        if (hf == 0) *reinterpret_cast<float2*>(part + TM * D + (wq * 32 + l32) * 2) = float2{m_run, l_tot};
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+            for (int dtl = 0; dtl < DT / 2; ++dtl)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const int dt = pass * (DT / 2) + dtl;
+                    const f32x4 v = {oacc[dt][i4 * 4], oacc[dt][i4 * 4 + 1], oacc[dt][i4 * 4 + 2], oacc[dt][i4 * 4 + 3]};
+                    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + l32 * OROWB + (dtl * 32 + i4 * 8 + hf * 4) * 4) = v;
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int p = 0; p < 32 / RPI; ++p) {
+                const int rr = p * RPI + lane / CPR;
+                const f32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(patch + rr * OROWB + (lane % CPR) * 16);
+                *reinterpret_cast<f32x4*>(part + (wq * 32 + rr) * D + pass * (D / 2) + (lane % CPR) * 4) = v;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the patch is rewritten by the next pass
+        }
+        return;
+    }
     const float inv = 1.f / l_tot;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -514,18 +537,17 @@ __global__ __launch_bounds__(256 * NG, (NG == 1 && RING == 2) ? 2 : 1) void attn
     }
 }
 
-template <int D, int NG, int RING, class Work>
+template <int D, int NG, bool SPLIT, class Work>
 void launch_one(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
     const dim3 grid((unsigned)entries * a.kv_heads), block(256 * NG);
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NG, RING, Work>), grid, block, 0, s, a, wk);
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NG, SPLIT, Work>), grid, block, 0, s, a, wk);
 }
 template <class Work>
 void launch_list(const AttnLaunch& a, const Work& wk, int entries, int variant, hipStream_t s) {
     const bool d64 = a.head_dim == 64;
-    if (variant == kAttnVariantTwoGroups)
-        d64 ? launch_one<64, 2, 2>(a, wk, entries, s) : launch_one<128, 2, 2>(a, wk, entries, s);
-    else
-        d64 ? launch_one<64, 1, 2>(a, wk, entries, s) : launch_one<128, 1, 2>(a, wk, entries, s);
+    if (wk.splits > 1) d64 ? launch_one<64, 1, true>(a, wk, entries, s) : launch_one<128, 1, true>(a, wk, entries, s);
+    else if (variant == kAttnVariantTwoGroups) d64 ? launch_one<64, 2, false>(a, wk, entries, s) : launch_one<128, 2, false>(a, wk, entries, s);
+    else d64 ? launch_one<64, 1, false>(a, wk, entries, s) : launch_one<128, 1, false>(a, wk, entries, s);
 }
 
 }  // namespace

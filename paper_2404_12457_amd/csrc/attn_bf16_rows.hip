@@ -300,27 +300,27 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     }
 }
 
-// Combines the S partial results of every row of a split work item (see the end of
+// Combines the S partial results of every row of a split work item of ROWS rows, of either kernel (see the end of
 // attn_bf16_rows_kernel for the layout): out = sum_s O_s 2^(m_s - m) / sum_s l_s 2^(m_s - m), m = max_s m_s.
 // One workgroup per (item, kv head, run of 256 / (D/4) rows): 4 consecutive d of one row per thread.
-template <int D, class Work>
+template <int D, int ROWS, class Work>
 __global__ __launch_bounds__(256) void attn_bf16_merge_kernel(AttnLaunch a, Work wk) {
     constexpr int TPR = D / 4;          // threads per row
     constexpr int RPW = 256 / TPR;      // rows per workgroup
-    constexpr int CHUNKS = TR / RPW;    // workgroups per (entry, kv head)
+    constexpr int CHUNKS = ROWS / RPW;    // workgroups per (entry, kv head)
     const int Hkv = a.kv_heads;
     const int chunk = blockIdx.x % CHUNKS;
     const int g = (blockIdx.x / CHUNKS) % Hkv;
     const int lead = blockIdx.x / (CHUNKS * Hkv) + wk.entry0 / wk.splits;
-    const WorkItem it = find_item(wk, lead, a.group, TR);
+    const WorkItem it = find_item(wk, lead, a.group, ROWS);
     const int S = wk.splits;
     const int G = a.group;
     const uint32_t g_magic = a.group_magic;
     auto div_g = [&](int x) { return g_magic ? (int)__umulhi((uint32_t)x, g_magic) : x; };
     const int rows_total = it.new_len * G;
-    const int row0 = it.tile * TR;
-    const int rows_here = min(TR, rows_total - row0);
-    constexpr int PART = TR * (D + 2);
+    const int row0 = it.tile * ROWS;
+    const int rows_here = min(ROWS, rows_total - row0);
+    constexpr int PART = ROWS * (D + 2);
     const float* const part0 = static_cast<const float*>(a.partial) + ((long long)(wk.part_base + lead * S) * Hkv + g) * PART;
     const long long copy_stride = (long long)Hkv * PART;
     const int d4 = threadIdx.x % TPR;
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(256) void attn_bf16_merge_kernel(AttnLaunch a, Work
             oc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (c < S) {
                 const float* pc = part0 + c * copy_stride;
-                const float2 ml = *reinterpret_cast<const float2*>(pc + TR * D + r * 2);
+                const float2 ml = *reinterpret_cast<const float2*>(pc + ROWS * D + r * 2);
                 mc[c] = ml.x;
                 lc[c] = ml.y;
                 oc[c] = *reinterpret_cast<const f32x4*>(pc + r * D + d4 * 4);
@@ -366,24 +366,29 @@ __global__ __launch_bounds__(256) void attn_bf16_merge_kernel(AttnLaunch a, Work
     }
 }
 
-template <int D, int NW, class Work>
+template <int D, int NW, bool SPLIT, class Work>
 void launch_one(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
     const dim3 grid((unsigned)entries * a.kv_heads), block(64 * NW);
-    if (wk.splits > 1) hipLaunchKernelGGL((attn_bf16_rows_kernel<D, NW, true, Work>), grid, block, 0, s, a, wk);
-    else hipLaunchKernelGGL((attn_bf16_rows_kernel<D, NW, false, Work>), grid, block, 0, s, a, wk);
+    hipLaunchKernelGGL((attn_bf16_rows_kernel<D, NW, SPLIT, Work>), grid, block, 0, s, a, wk);
 }
 template <class Work>
 void launch_list(const AttnLaunch& a, const Work& wk, int entries, int waves, hipStream_t s) {
     const bool d64 = a.head_dim == 64;
-    if (waves == 4) d64 ? launch_one<64, 4>(a, wk, entries, s) : launch_one<128, 4>(a, wk, entries, s);
-    else d64 ? launch_one<64, 8>(a, wk, entries, s) : launch_one<128, 8>(a, wk, entries, s);
+    if (wk.splits > 1) d64 ? launch_one<64, 8, true>(a, wk, entries, s) : launch_one<128, 8, true>(a, wk, entries, s);
+    else if (waves == 4) d64 ? launch_one<64, 4, false>(a, wk, entries, s) : launch_one<128, 4, false>(a, wk, entries, s);
+    else d64 ? launch_one<64, 8, false>(a, wk, entries, s) : launch_one<128, 8, false>(a, wk, entries, s);
 }
 
+template <int D, int ROWS, class Work>
+void launch_merge_one(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
+    const dim3 grid((unsigned)(entries / wk.splits) * a.kv_heads * (ROWS * D / 1024));
+    hipLaunchKernelGGL((attn_bf16_merge_kernel<D, ROWS, Work>), grid, dim3(256), 0, s, a, wk);
+}
 template <class Work>
-void launch_merge(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
-    const dim3 grid((unsigned)(entries / wk.splits) * a.kv_heads * (TR * a.head_dim / 1024));
-    if (a.head_dim == 64) hipLaunchKernelGGL((attn_bf16_merge_kernel<64, Work>), grid, dim3(256), 0, s, a, wk);
-    else hipLaunchKernelGGL((attn_bf16_merge_kernel<128, Work>), grid, dim3(256), 0, s, a, wk);
+void launch_merge(const AttnLaunch& a, const Work& wk, int entries, int rows, hipStream_t s) {
+    const bool d64 = a.head_dim == 64;
+    if (rows == TR) d64 ? launch_merge_one<64, TR>(a, wk, entries, s) : launch_merge_one<128, TR>(a, wk, entries, s);
+    else d64 ? launch_merge_one<64, kAttnRowsPerItem>(a, wk, entries, s) : launch_merge_one<128, kAttnRowsPerItem>(a, wk, entries, s);
 }
 
 }  // namespace
@@ -394,9 +399,9 @@ hipError_t launch_attn_bf16_rows(const AttnLaunch& a, const AttnWork& wk, int en
     return hipGetLastError();
 }
 
-hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWork& wk, int entries, hipStream_t s) {
+hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWork& wk, int entries, int rows, hipStream_t s) {
     if (entries <= 0) return hipSuccess;
-    wk.n_reqs <= kAttnReqStep ? launch_merge(a, short_list(wk), entries, s) : launch_merge(a, wk, entries, s);
+    wk.n_reqs <= kAttnReqStep ? launch_merge(a, short_list(wk), entries, rows, s) : launch_merge(a, wk, entries, rows, s);
     return hipGetLastError();
 }
 

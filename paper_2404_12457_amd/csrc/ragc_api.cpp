@@ -235,7 +235,7 @@ struct Bf16Plan {
     bool rows_kernel = false;    // attn_bf16_rows_kernel
     int rows = ragc::kAttnRowsPerItem;
     int splits = 1;
-    int waves = 8;  // per workgroup of attn_bf16_rows_kernel
+    int waves = 8;                             // per workgroup of attn_bf16_rows_kernel
     int variant = ragc::kAttnVariantOneGroup;  // of attn_bf16_kernel
     int64_t workspace = 0;
 };
@@ -254,7 +254,7 @@ void order_requests(const HostMeta& h, int num_reqs, std::vector<int32_t>* order
 }
 
 int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta& h, int group, uint32_t flags, Bf16Plan* plan) {
-    int64_t items = 0, short_items = 0, max_rows = 0, max_keys = 0, sum_keys = 0;
+    int64_t items = 0, short_items = 0, max_rows = 0, max_keys = 0, req_keys = 0, sum_keys = 0;  // sum_keys: over the 32-row items
     for (int r = 0; r < batch->num_reqs; ++r) {
         const int64_t tiles = row_tiles(h, r, group, ragc::kAttnRowsPerItem);
         if (tiles > 65535) return fail(RAGC_ERR_RANGE, "request %d: new_len * group too large", r);
@@ -262,72 +262,117 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
         items += tiles;
         const int64_t short_tiles = row_tiles(h, r, group, ragc::kAttnShortRows);
         short_items += short_tiles;
-        sum_keys += short_tiles * ((int64_t)h.prefix_len[r] + h.new_len[r]);
+        const int64_t keys = (int64_t)h.prefix_len[r] + h.new_len[r];
+        req_keys += keys;
+        sum_keys += short_tiles * keys;
         max_rows = std::max(max_rows, (int64_t)h.new_len[r] * group);
-        max_keys = std::max(max_keys, (int64_t)h.prefix_len[r] + h.new_len[r]);
+        max_keys = std::max(max_keys, keys);
     }
     order_requests(h, batch->num_reqs, &plan->order);
-    const int64_t wgs = items * pool->kv_heads;
+    if (items == 0) return 0;
     const int64_t cus = cu_count();
+    const int64_t wgs = items * pool->kv_heads, short_wgs = short_items * pool->kv_heads;
+    const bool d128 = pool->head_dim == 128;
     const int force_splits = std::min(g_force_splits.load(std::memory_order_relaxed), ragc::kAttnMaxSplits);
     const int force_variant = g_force_variant.load(std::memory_order_relaxed);
-    const bool may_split = !(flags & RAGC_ATTN_NO_SPLIT) && wgs > 0;
-    // The workspace: one 128-row partial result per item and copy, for as many copies as give every CU one with at
-    // least three 64-key tiles each.  The copies that are really made (below) never need more.
-    int splits = 1;
-    if (may_split) {
-        splits = (int)std::min<int64_t>(cus / wgs, ragc::kAttnMaxSplits);
-        splits = (int)std::min<int64_t>(splits, (max_keys + 63) / 64 / 3);
-        if (force_splits > 0) splits = force_splits;
-        if (splits < 1) splits = 1;
+    const bool may_split = !(flags & RAGC_ATTN_NO_SPLIT);
+    const auto rows32 = [&](int64_t splits, int waves) {
+        plan->rows_kernel = true;
+        plan->rows = ragc::kAttnShortRows;
+        plan->splits = (int)splits;
+        plan->waves = waves;
+        return 0;
+    };
+    const auto rows128 = [&](int64_t splits, int variant) {
+        plan->splits = (int)splits;
+        plan->variant = splits > 1 ? ragc::kAttnVariantOneGroup : variant;
+        return 0;
+    };
+    // Copies that give every CU a 128-row item with at least three 64-key tiles.  The workspace holds one partial result
+    // per item and copy; the copies of 32-row items (below) never need more.
+    int64_t splits128 = may_split ? std::max<int64_t>(1, std::min({cus / wgs, (int64_t)ragc::kAttnMaxSplits, (max_keys + 63) / 64 / 3})) : 1;
+    if (may_split && force_splits > 0) splits128 = force_splits;
+    plan->workspace = splits128 > 1 ? items * splits128 * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnRowsPerItem) : 0;
+
+    if (force_variant >= 0 || (may_split && force_splits > 0)) {  // tests
+        const int64_t splits = may_split && force_splits > 0 ? force_splits : 1;
+        if (max_rows <= ragc::kAttnShortRows || (splits > 1 && force_variant != ragc::kAttnVariantOneGroup))
+            return rows32(splits, force_variant == ragc::kAttnVariantOneGroup && splits == 1 ? 4 : 8);
+        return rows128(splits, force_variant >= 0 ? force_variant : wgs >= 2 * cus ? ragc::kAttnVariantOneGroup : ragc::kAttnVariantTwoGroups);
     }
-    plan->workspace = splits > 1 ? items * splits * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnRowsPerItem) : 0;
-    const int64_t short_wgs = short_items * pool->kv_heads;
-    // The 32-row kernel takes launches of at most 32 rows per request, and those that leave CUs without a 128-row item
-    // as long as its own workgroups, one per CU at a time, need at most two rounds: up to 256 of them it is 1.0-1.3
-    // times as fast as the 128-row kernel with split keys (one request of 1000 + 256 tokens: 14.7 us against 19.1), at
-    // 400-512 0.94-1.3 times, at 728 and more 0.5-0.9 times.
-    // Between one and two 128-row items per CU it takes batches of half-empty items, whose idle rows the 128-row kernel
-    // pays for like others while a second round of items starts: at most two 32-row workgroups per CU (MHA requests of
-    // 33-64 new tokens: 416 of 272 keys 10.7 us against 16.6, 448 of 2800 keys 91 against 112), or three with short key
-    // ranges (592 of 189 keys 15.1 us against 19.6, 672 of 844: 46 against 51; but 640 of 2261: 88 against 85).  With
-    // exactly one item per CU there is no second round (424 workgroups of 1811 keys: 53.7 us against 49.7).
-    const bool half_empty = wgs > cus && wgs < 2 * cus &&
-                            (short_wgs <= 2 * cus || (pool->head_dim == 128 && short_wgs <= 3 * cus && max_keys <= 1024));
+
+    // The lines below: 3600 batches, each timed with every choice; both sides of a line as the library would run them.
+    const bool uniform = sum_keys * 100 >= max_keys * short_items * 97;   // every request about as long as the longest
+    const bool even = sum_keys * 100 >= max_keys * short_items * 78;
+    const bool many_keys = sum_keys >= 1024 * short_items;
+    // The 32-row kernel takes launches of at most 32 rows per request, and those that leave CUs without a 128-row item, or a
+    // second round of 128-row items half empty, as long as its own workgroups need at most two rounds (one per CU at a time at
+    // head_dim 128): with fewer 128-row items than CUs 0.4-1.0 times the time of the other kernel (one request of 1000 + 256
+    // tokens 14.7 us against 19.1), with one to two per CU 0.7 (416 workgroups of 272 keys 10.7 us against 16.6).  With exactly
+    // one 128-row item per CU there is no second round (424 workgroups of 1811 keys: 53.7 us against 49.7).
     // At head_dim 64 several of its four-wave workgroups fit a CU next to each other, and it takes ragged batches as well:
     // with at most two 128-row items per CU the 128-row kernel takes as long as its longest item, the 32-row kernel as
     // long as its workgroups take in all, and the latter is less while their keys, per CU, are at most twice those of the
     // longest request (in these units 1.6: 19.5 us against 24.4, 2.0: 20.3 against 23.5, 2.5: 24.7 against 24.4, 3: 28.6
     // against 26.1).  At head_dim 128 it loses at 1.6 already (45.8 against 42.5).
-    const bool ragged_d64 = pool->head_dim == 64 && wgs < 2 * cus && sum_keys * pool->kv_heads <= 2 * cus * max_keys;
-    // Forced key splits go to it as well: the 128-row kernel does not split.
-    plan->rows_kernel = max_rows <= ragc::kAttnShortRows || (may_split && force_splits > 1) ||
-                        (force_variant < 0 && ((wgs < cus && short_wgs <= 2 * cus) || half_empty || ragged_d64));
-    if (plan->rows_kernel) {
-        plan->rows = ragc::kAttnShortRows;
-        // Copies until every CU has a workgroup, of at least two 32-key tiles for each of its eight waves; up to 1280
-        // keys a copy of the whole range is faster than two copies and the merge pass (1000 keys, 8 workgroups: 10.4
-        // us against 13.0; 4096 keys, 8 copies: 17.9 us against 26.9).  The workspace is sized for the copies that
-        // 128-row items would have.
-        const int64_t tiles = (max_keys + 31) / 32;
-        const int64_t room = plan->workspace / (std::max<int64_t>(short_wgs, 1) * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnShortRows));
-        plan->splits = tiles <= 40 ? 1 : (int)std::min({room, cus / std::max<int64_t>(short_wgs, 1), tiles / 16});
-        if (may_split && force_splits > 0) plan->splits = force_splits;
-        if (plan->splits < 1) plan->splits = 1;
-        if (plan->splits > ragc::kAttnMaxSplits) plan->splits = ragc::kAttnMaxSplits;
-        // With more workgroups than CUs and few keys for each, four waves: a CU then holds two workgroups at a time
-        // and one streams while the other starts (128 decode requests of 300-1000 keys, 8 heads: 61 us against 67; 64
-        // of 512-2048: 64 against 61, since eight waves finish a long request sooner).  At head_dim 64 four such workgroups
-        // fit, and with more than two per CU four waves win whatever the keys (704 of 2036 keys: 19.5 us against 22.7).
-        plan->waves = short_wgs > cus && (sum_keys < 1024 * short_items || (pool->head_dim == 64 && short_wgs > 2 * cus)) ? 4 : 8;
-        if (force_variant >= 0) plan->waves = force_variant == 0 ? 4 : 8;
-        return 0;
+    const bool rows_kernel = max_rows <= ragc::kAttnShortRows || (wgs != cus && wgs < 2 * cus && short_wgs <= 2 * cus) ||
+                             (!d128 && wgs < 2 * cus && sum_keys * pool->kv_heads <= 2 * cus * max_keys);
+    if (!rows_kernel) {
+        // With at least two 128-row items per CU two 4-wave workgroups share a CU; otherwise one 8-wave workgroup divides its
+        // key tiles between two wave groups.  Between one and two items per CU the second round of 8-wave workgroups costs as
+        // much as the first; where the items are half empty (at most three 32-row workgroups per CU) and short, sharing is
+        // faster at head_dim 128: 0.67 times up to 300 keys, 0.77 up to 600, 0.82 up to 1024 (medians of 266 batches; the
+        // 32-row kernel 0.74 / 0.85 / 1.0 of its time the other way round).
+        const bool shared = wgs >= 2 * cus || (d128 && wgs > cus && short_wgs <= 3 * cus && max_keys <= 1024);
+        return rows128(1, shared ? ragc::kAttnVariantOneGroup : ragc::kAttnVariantTwoGroups);
     }
-    // With at least two workgroups per CU two 4-wave workgroups share a CU; otherwise one 8-wave
-    // workgroup divides its key tiles between two wave groups.  ragc_debug_set_attn_plan overrides (tests).
-    plan->variant = wgs >= 2 * cus ? ragc::kAttnVariantOneGroup : ragc::kAttnVariantTwoGroups;
-    if (force_variant >= 0) plan->variant = force_variant;
-    return 0;
+    // Decode steps of head_dim 64, all of one length, a little over two workgroups per CU: the four waves of a 128-row item
+    // share its copies (528 of 4030 keys: 105 us against 113; medians 0.95 up to 2.5 per CU, 1.0 above).
+    if (!d128 && max_rows <= ragc::kAttnShortRows && uniform && max_keys >= 300 && short_wgs > 2 * cus && 2 * short_wgs <= 5 * cus)
+        return rows128(1, ragc::kAttnVariantOneGroup);
+    // Workgroup ids go round-robin over the XCDs, kv head first, copies next, row tiles last: the row tiles of a request read
+    // its keys through one L2 where heads times copies is a multiple of 8, and otherwise through up to `step` of them, `again`
+    // bytes more from memory.
+    const int64_t step = pool->kv_heads % 8 == 0 ? 1 : pool->kv_heads % 4 == 0 ? 2 : pool->kv_heads % 2 == 0 ? 4 : 8;
+    const int64_t reqs = (int64_t)plan->order.size();
+    const int64_t again = req_keys * pool->kv_heads * pool->head_dim * 4 / reqs * (std::min(short_items, step * reqs) - reqs);
+    if (short_wgs <= cus) {
+        // Copies until every CU has a workgroup, of at least two 32-key tiles for each of its eight waves; up to 1408
+        // keys one copy of the whole range and no merge pass is faster (1280-1400 keys: 0.88 times at head_dim 128, 0.80 at
+        // 64; 4096 keys, 8 copies: 17.9 us against 26.9).
+        const int64_t tiles = (max_keys + 31) / 32;
+        int64_t splits = 1;
+        if (splits128 > 1 && tiles > 44)
+            splits = std::max<int64_t>(1, std::min({items * splits128 * 4 / short_items, cus / short_wgs, tiles / 16, (int64_t)ragc::kAttnMaxSplits}));
+        // Where `again` bytes cost time (head_dim 128, above 30 MB) the copies are made a multiple of `step`, or, where that
+        // does not fit, long requests are split as 128-row items, which read their keys a quarter as often: 48 workgroups of
+        // 6850 keys, 2 heads: 4 copies 19.9 us, 5 copies 31.0; without such a number the 128-row items take 0.7-1.0 times
+        // the time from 60 MB on, or from 30 with up to 96 workgroups, and 1.0-1.2 times below; next to it only where it
+        // leaves CUs idle: 68 of 8088 keys 40.6 against 48.8, 48 of 3509 17.0 against 15.5.
+        if (d128 && splits128 > 1 && tiles > 44 && again > 30000000) {
+            if (splits >= step) splits -= splits % step;
+            if (splits >= step ? again > 60000000 && short_wgs * splits <= 160 : again > 60000000 || short_wgs <= 96)
+                return rows128(splits128, ragc::kAttnVariantTwoGroups);
+        }
+        return rows32(splits, 8);
+    }
+    // Between one and two 32-row workgroups per CU at head_dim 128, all requests of one length: two rounds, the second more or
+    // less empty.  Long ones are split as 128-row items, or take them whole where there is nothing to split and the second
+    // round is short: 280 workgroups of 6025 keys 48.3 us against 68.8, 288 of 4491 40.7 against 54.0; but 492 of 6277, not
+    // split, 92.2 against 78.0.  From 2200 keys on where the items are ragged or few (272 of 2946 60 against 70); with fewer
+    // keys the four waves below are faster (288 of 1891: 26.5 against 29.1, medians 0.8-0.9), unless they read much again
+    // (272 of 1710, 4 heads: 24.1 against 29.7).
+    if (d128 && wgs < cus && max_rows > ragc::kAttnShortRows && uniform && (splits128 > 1 || short_wgs * 5 <= cus * 9) &&
+        (max_keys > 3000 || again > 55000000 || (max_keys > 2200 && (splits128 >= 3 || short_wgs * 4 < wgs * 11))))
+        return rows128(splits128, ragc::kAttnVariantTwoGroups);
+    // Four waves per workgroup: a CU then holds two workgroups at a time at head_dim 128 (four at 64), one streams while the
+    // other starts, and requests of like length do not wait for a second round.  Eight finish a long request sooner where
+    // the lengths differ.  head_dim 128, 257-512 workgroups: four take 0.7-0.9 times the time up to 2200 keys, 0.9 above
+    // with a mean of at least 0.78 of the longest, 1.05-1.14 below that (64 decode requests of 512-2048 keys, 8 heads: 64 us
+    // against 61).  head_dim 64: 0.96 for decode steps of one length, 1.0 otherwise; above two per CU 0.9 whatever the keys.
+    const bool four = d128 ? !many_keys || even || (max_rows > ragc::kAttnShortRows && max_keys <= 2200)
+                           : !many_keys || short_wgs > 2 * cus || (uniform && max_rows <= ragc::kAttnShortRows);
+    return rows32(1, four ? 4 : 8);
 }
 
 constexpr uint32_t kAttnFlags = RAGC_ATTN_APPEND_FUSED | RAGC_ATTN_NO_SPLIT | RAGC_ATTN_VALIDATE;
@@ -367,7 +412,7 @@ int run_list(const ragc::AttnLaunch& a, const HostMeta& h, const std::vector<int
 int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& plan, hipStream_t s) {
     return run_list(a, h, plan.order, plan.rows, plan.splits, [&](const ragc::AttnWork& wk, int entries) {
         hipError_t e = plan.rows_kernel ? ragc::launch_attn_bf16_rows(a, wk, entries, plan.waves, s) : ragc::launch_attn_bf16(a, wk, entries, plan.variant, s);
-        if (e == hipSuccess && wk.splits > 1) e = ragc::launch_attn_bf16_merge(a, wk, entries, s);
+        if (e == hipSuccess && wk.splits > 1) e = ragc::launch_attn_bf16_merge(a, wk, entries, plan.rows, s);
         return e;
     });
 }

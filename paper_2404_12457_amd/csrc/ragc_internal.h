@@ -95,7 +95,7 @@ constexpr int kAttnF32RowsPerItem = 16;
 hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
 
 // bf16 path.  Large batches: row tiles of kAttnRowsPerItem rows (attn_bf16.hip).  Launches that cannot fill the chip
-// with those: kAttnShortRows rows (attn_bf16_rows.hip).
+// with those: kAttnShortRows rows (attn_bf16_rows.hip), or either split along the keys.
 constexpr int kAttnRowsPerItem = 128;
 constexpr int kAttnShortRows = 32;
 // bytes of one partial result of a key-split item: O [rows][D] fp32, then (max, sum) per row
@@ -106,12 +106,12 @@ enum AttnVariant {
     kAttnVariantTwoGroups = 1,  // 8 waves per workgroup on alternating key tiles
     kAttnVariantCount = 2
 };
-// entries: items times wk.splits, from wk.entry0 on
+// entries: items times wk.splits, from wk.entry0 on; split items are kAttnVariantOneGroup
 hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, hipStream_t s);
-// waves: 4 or 8 per workgroup
+// waves: 4 or 8 per workgroup; split items have 8
 hipError_t launch_attn_bf16_rows(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
-// second pass after a launch of split items of the 32-row kernel: combines the partial results into `out`
-hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWork& wk, int entries, hipStream_t s);
+// second pass after a launch of split items of `rows` rows: combines the partial results into `out`
+hipError_t launch_attn_bf16_merge(const AttnLaunch& a, const AttnWork& wk, int entries, int rows, hipStream_t s);
 
 hipError_t launch_append(const PagedBatch& b, void* pool_k, void* pool_v, const void* k_new, const void* v_new,
                          int32_t total_new, int esize, hipStream_t s);

@@ -698,3 +698,21 @@ def test_fp32_scores_are_summed_in_short_chains(H, hq, hkv, d):
         got = U.out_to_f64(H.to_host(H.DeviceWorkload(w).attn()), "f32")
         errors.append(U.rel_l2(got, U.oracle_all(w)))
     assert max(errors) <= 4e-7, errors
+
+
+@pytest.mark.parametrize("hq,hkv,lens", [
+    (64, 8, [(3200, 46)] * 3 + [(0, 0)]),            # 288 workgroups of 32 rows, 72 of 128: split in three as 128-row items
+    (40, 8, [(3100, 23)] * 20 + [(17, 0)]),          # 160 items of 128 rows: not split
+    (28, 4, [(3300, 18)] * 9),                       # row tiles on different XCDs, no number of copies that brings them together
+    (8, 2, [(2900, 17)] * 14),                       # row tiles of a request, three each, brought together by the copies
+    (16, 1, [(4000, 4)] * 20),                       # one kv head
+], ids=["split_items", "whole_items", "split_heads4", "copies_heads2", "heads1"])
+def test_long_batches_of_one_length_match_oracle(H, hq, hkv, lens):
+    """Batches with a few hundred 32-row workgroups and thousands of keys each, where the plan turns to split or whole
+    128-row items: all rows against the oracle, and the fused append byte for byte."""
+    w = W.make_small("bf16", hq, hkv, 128, lens, seed=8600 + len(lens) + hkv, q_gain=2.0)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
