@@ -240,17 +240,36 @@ struct Bf16Plan {
     int64_t workspace = 0;
 };
 
-int64_t row_tiles(const HostMeta& h, int r, int group, int rows) { return ((int64_t)h.new_len[r] * group + rows - 1) / rows; }
+// rows: a power of two (a shift instead of a division: every request of a batch comes by here three times)
+inline int64_t row_tiles(const HostMeta& h, int r, int group, int rows) {
+    return ((int64_t)h.new_len[r] * group + rows - 1) >> __builtin_ctz((unsigned)rows);
+}
 
 // Requests with the most keys first, and the row tiles of one request next to each other: long items start
 // early, and the workgroups that run at the same time on an XCD walk the key tiles of the same few requests at
 // about the same pace, so a tile fetched by one row tile is still in that XCD's L2 for the others.
 void order_requests(const HostMeta& h, int num_reqs, std::vector<int32_t>* order) {
-    order->reserve(num_reqs);
-    for (int r = 0; r < num_reqs; ++r)
-        if (h.new_len[r] > 0) order->push_back(r);
-    const auto keys = [&](int r) { return (int64_t)h.prefix_len[r] + h.new_len[r]; };
-    std::stable_sort(order->begin(), order->end(), [&](int x, int y) { return keys(x) > keys(y); });
+    // one number per request, the one with the most keys smallest, then by request (at most 65535 of them); batches of
+    // one length, or already in order, are left as they are
+    constexpr int kSmall = 128;
+    uint64_t small[kSmall];
+    std::vector<uint64_t> large;
+    uint64_t* rank = small;
+    if (num_reqs > kSmall) {
+        large.resize(num_reqs);
+        rank = large.data();
+    }
+    int n = 0;
+    bool sorted = true;
+    for (int r = 0; r < num_reqs; ++r) {
+        if (h.new_len[r] <= 0) continue;
+        rank[n] = ((uint64_t)UINT32_MAX - ((uint32_t)h.prefix_len[r] + (uint32_t)h.new_len[r])) << 16 | (uint64_t)r;
+        sorted = sorted && (n == 0 || rank[n - 1] < rank[n]);
+        ++n;
+    }
+    if (!sorted) std::sort(rank, rank + n);
+    order->resize(n);
+    for (int i = 0; i < n; ++i) (*order)[i] = (int32_t)(rank[i] & 0xffff);
 }
 
 int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta& h, int group, uint32_t flags, Bf16Plan* plan) {
