@@ -78,7 +78,8 @@
  *     range-checked) and flags (copy mechanism).
  *   - the fused-append flag is spelled RAGC_ATTN_APPEND_FUSED; RAGC_ATTN_NO_SPLIT is new.
  *   - more exports: ragc_last_error, ragc_kv_bytes_per_token, ragc_prefill_attn_workspace,
- *     ragc_batch_validate, ragc_debug_set_attn_plan, ragc_prefill_attn_static.
+ *     ragc_batch_validate, ragc_debug_set_attn_plan, ragc_debug_get_attn_plan,
+ *     ragc_prefill_attn_static.
  *   - host copies of the lengths are optional but their absence costs a synchronous
  *     read-back per call (the launch is sized on the host).
  */
@@ -185,16 +186,29 @@ int ragc_batch_validate(const ragc_kv_pool* pool, const ragc_batch* batch, int32
 /* Test hook: override how ragc_prefill_attn lays a bf16 batch out on the GPU.
  *   variant  -1 = library's choice, 0 = 4-wave workgroups, 1 = 8-wave workgroups
  *   splits    0 = library's choice, 1..16 = copies of every work item along the keys
+ * Anything but (-1, 0) also settles which kernel runs: 32-row work items for batches of at
+ * most 32 rows (new tokens times q heads per kv head) per request and, with splits > 1 and
+ * variant -1 or 1, for all; 128-row work items otherwise.  32-row items with splits > 1 always
+ * have 8 waves, 128-row ones 4.
  * Process-wide and not synchronised with calls in flight on other threads: set it
  * before the calls it should affect and reset it (-1, 0) afterwards.  It changes the
  * workspace size, so query ragc_prefill_attn_workspace under the same setting. */
 int ragc_debug_set_attn_plan(int32_t variant, int32_t splits);
 
-/* Workspace ragc_prefill_attn needs for this batch with these flags (bytes, possibly 0).
- * A bf16 batch with fewer (request, 128-row tile, kv head) work items than the GPU has
- * compute units is split along the keys over several workgroups, whose partial results
- * (unnormalised output, row max and row sum, fp32) pass through the workspace and are
- * combined by a second kernel of the same call; RAGC_ATTN_NO_SPLIT turns that off (0 bytes).
+/* Test hook: the layout ragc_prefill_attn would choose for this batch with these flags (under
+ * the override above, if any).  plan[0]: rows per work item (fp32: 16; bf16: 32 or 128),
+ * plan[1]: waves per workgroup, plan[2]: copies of every work item along the keys (1: not
+ * split); all 0 for a batch without new tokens.  Only the host arrays of `batch` are read. */
+int ragc_debug_get_attn_plan(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads, uint32_t flags,
+                             int32_t* plan);
+
+/* Workspace ragc_prefill_attn needs for this batch with these flags (bytes, often 0).
+ * A bf16 batch with long key ranges (above 1400 keys) and fewer (request, 128-row tile, kv head)
+ * work items than the GPU has compute units may be split along the keys over several workgroups,
+ * whose partial results (unnormalised output, row max and row sum, fp32) pass through the
+ * workspace and are combined by a second kernel of the same call: kv heads times work items times
+ * copies times rows per item times (head_dim + 2) floats.  A batch that is not split needs none, and
+ * RAGC_ATTN_NO_SPLIT turns the split off.
  * Only the host arrays of `batch` are read.  Returns a negative ragc_status on error. */
 int64_t ragc_prefill_attn_workspace(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads,
                                     uint32_t flags);

@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional
+from typing import Optional, Tuple
 
 import numpy as np
 
@@ -25,7 +25,7 @@ RAGC_SWAP_TO_DEVICE, RAGC_SWAP_TO_HOST = 0, 1
 
 EXPORTS = ["ragc_version", "ragc_last_error", "ragc_kv_bytes_per_token", "ragc_prefill_attn_workspace",
            "ragc_prefill_attn", "ragc_prefill_attn_static", "ragc_kv_append", "ragc_kv_swap", "ragc_kv_gather",
-           "ragc_batch_validate", "ragc_debug_set_attn_plan"]
+           "ragc_batch_validate", "ragc_debug_set_attn_plan", "ragc_debug_get_attn_plan"]
 
 
 class ragc_kv_pool(ctypes.Structure):
@@ -72,6 +72,8 @@ def load() -> ctypes.CDLL:
         lib.ragc_batch_validate.argtypes = [P, P, I32]
         lib.ragc_debug_set_attn_plan.restype = ctypes.c_int
         lib.ragc_debug_set_attn_plan.argtypes = [I32, I32]
+        lib.ragc_debug_get_attn_plan.restype = ctypes.c_int
+        lib.ragc_debug_get_attn_plan.argtypes = [P, P, I32, U32, P]
         lib.ragc_kv_append.restype = ctypes.c_int
         lib.ragc_kv_append.argtypes = [P, P, P, P, P]
         lib.ragc_kv_swap.restype = ctypes.c_int
@@ -149,6 +151,13 @@ def ragc_batch_validate(pool, batch, writes_new_tokens: bool = True) -> int:
 
 def ragc_debug_set_attn_plan(variant: int = -1, splits: int = 0) -> int:
     return _check(load().ragc_debug_set_attn_plan(variant, splits))
+
+
+def ragc_debug_get_attn_plan(pool, batch, q_heads: int, flags: int = 0) -> Tuple[int, int, int]:
+    """(rows per work item, waves per workgroup, copies of every item along the keys)"""
+    plan = (ctypes.c_int32 * 3)()
+    _check(load().ragc_debug_get_attn_plan(_ref(pool), _ref(batch), q_heads, flags, ctypes.addressof(plan)))
+    return tuple(plan)
 
 
 def ragc_kv_append(pool, batch, k_new, v_new, stream: int = 0) -> int:

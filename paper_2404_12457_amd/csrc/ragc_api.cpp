@@ -228,8 +228,8 @@ int cu_count() {
 }
 
 // How the bf16 path will run a batch: which kernel, on row tiles of how many rows, with how many copies of
-// each item along its keys; and the workspace the copies may need.  ragc_prefill_attn_workspace and
-// ragc_prefill_attn both call this, so they always agree.
+// each item along its keys; and the workspace of the copies' partial results (0 without copies).
+// ragc_prefill_attn_workspace and ragc_prefill_attn both call this, so they always agree.
 struct Bf16Plan {
     std::vector<int32_t> order;  // requests with new tokens, most keys first
     bool rows_kernel = false;    // attn_bf16_rows_kernel
@@ -295,23 +295,24 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
     const int force_splits = std::min(g_force_splits.load(std::memory_order_relaxed), ragc::kAttnMaxSplits);
     const int force_variant = g_force_variant.load(std::memory_order_relaxed);
     const bool may_split = !(flags & RAGC_ATTN_NO_SPLIT);
-    const auto rows32 = [&](int64_t splits, int waves) {
-        plan->rows_kernel = true;
-        plan->rows = ragc::kAttnShortRows;
+    const auto make = [&](bool rows_kernel, int64_t splits, int64_t all_items) {
+        plan->rows_kernel = rows_kernel;
+        plan->rows = rows_kernel ? ragc::kAttnShortRows : ragc::kAttnRowsPerItem;
         plan->splits = (int)splits;
-        plan->waves = waves;
+        if (splits > 1) plan->workspace = all_items * splits * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim, plan->rows);
         return 0;
+    };
+    const auto rows32 = [&](int64_t splits, int waves) {
+        plan->waves = waves;
+        return make(true, splits, short_items);
     };
     const auto rows128 = [&](int64_t splits, int variant) {
-        plan->splits = (int)splits;
         plan->variant = splits > 1 ? ragc::kAttnVariantOneGroup : variant;
-        return 0;
+        return make(false, splits, items);
     };
-    // Copies that give every CU a 128-row item with at least three 64-key tiles.  The workspace holds one partial result
-    // per item and copy; the copies of 32-row items (below) never need more.
-    int64_t splits128 = may_split ? std::max<int64_t>(1, std::min({cus / wgs, (int64_t)ragc::kAttnMaxSplits, (max_keys + 63) / 64 / 3})) : 1;
-    if (may_split && force_splits > 0) splits128 = force_splits;
-    plan->workspace = splits128 > 1 ? items * splits128 * pool->kv_heads * ragc::attn_partial_bytes(pool->head_dim, ragc::kAttnRowsPerItem) : 0;
+    // Copies that give every CU a 128-row item with at least three 64-key tiles.  Those of 32-row items (below) never take
+    // more workspace.
+    const int64_t splits128 = may_split ? std::max<int64_t>(1, std::min({cus / wgs, (int64_t)ragc::kAttnMaxSplits, (max_keys + 63) / 64 / 3})) : 1;
 
     if (force_variant >= 0 || (may_split && force_splits > 0)) {  // tests
         const int64_t splits = may_split && force_splits > 0 ? force_splits : 1;
@@ -439,12 +440,16 @@ int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& 
 // fp32 path.  With at most one workgroup per CU a workgroup has eight waves, so that every SIMD still has two to
 // overlap (256 workgroups of ~1100 keys: 31 us against 37); with more, four, and two workgroups share a CU (416 of
 // ~1000 keys: 45 us against 49, 512 of ~1100: 53 against 58).
+int f32_waves(const HostMeta& h, const std::vector<int32_t>& order, int group, int kv_heads) {
+    int64_t tiles = 0;
+    for (int r : order) tiles += row_tiles(h, r, group, ragc::kAttnF32RowsPerItem);
+    return tiles * kv_heads > (int64_t)cu_count() ? 4 : 8;
+}
+
 int run_f32(const ragc::AttnLaunch& a, const ragc_batch* batch, const HostMeta& h, hipStream_t s) {
     std::vector<int32_t> order;
     order_requests(h, batch->num_reqs, &order);
-    int64_t tiles = 0;
-    for (int r : order) tiles += row_tiles(h, r, a.group, ragc::kAttnF32RowsPerItem);
-    const int waves = tiles * a.kv_heads > (int64_t)cu_count() ? 4 : 8;
+    const int waves = f32_waves(h, order, a.group, a.kv_heads);
     return run_list(a, h, order, ragc::kAttnF32RowsPerItem, 1,
                     [&](const ragc::AttnWork& wk, int entries) { return ragc::launch_attn_f32(a, wk, entries, waves, s); });
 }
@@ -569,6 +574,35 @@ int ragc_debug_set_attn_plan(int32_t variant, int32_t splits) {
     if (splits < 0 || splits > ragc::kAttnMaxSplits) return fail(RAGC_ERR_SHAPE, "splits %d outside [0, %d]", splits, ragc::kAttnMaxSplits);
     g_force_variant.store(variant, std::memory_order_relaxed);
     g_force_splits.store(splits, std::memory_order_relaxed);
+    return RAGC_OK;
+}
+
+int ragc_debug_get_attn_plan(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads, uint32_t flags, int32_t* plan) {
+    g_err[0] = 0;
+    if (int rc = check_pool(pool)) return rc;
+    if (flags & ~kAttnFlags) return fail(RAGC_ERR_SHAPE, "unknown flags 0x%x", flags);
+    if (q_heads <= 0 || q_heads % pool->kv_heads != 0)
+        return fail(RAGC_ERR_SHAPE, "q_heads %d not a multiple of kv_heads %d", q_heads, pool->kv_heads);
+    if (!plan) return fail(RAGC_ERR_NULL, "plan is NULL");
+    BatchInfo info;
+    HostMeta h;
+    if (int rc = check_batch(pool, batch, false, false, &h, &info)) return rc;
+    plan[0] = plan[1] = plan[2] = 0;
+    if (batch->num_reqs == 0 || info.total_new == 0) return RAGC_OK;
+    const int group = q_heads / pool->kv_heads;
+    if (pool->dtype == RAGC_DTYPE_F32) {
+        std::vector<int32_t> order;
+        order_requests(h, batch->num_reqs, &order);
+        plan[0] = ragc::kAttnF32RowsPerItem;
+        plan[1] = f32_waves(h, order, group, pool->kv_heads);
+        plan[2] = 1;
+        return RAGC_OK;
+    }
+    Bf16Plan p;
+    if (int rc = plan_bf16(pool, batch, h, group, flags, &p)) return rc;
+    plan[0] = p.rows;
+    plan[1] = p.rows_kernel ? p.waves : p.variant == ragc::kAttnVariantTwoGroups ? 8 : 4;
+    plan[2] = p.splits;
     return RAGC_OK;
 }
 

@@ -121,9 +121,14 @@ def test_debug_plan_override_changes_the_workspace_and_rejects_bad_values(lib):
     pool = _pool(num_blocks=512)
     auto = B.ragc_prefill_attn_workspace(pool, one, 8)
     try:
-        B.ragc_debug_set_attn_plan(-1, 3)
+        B.ragc_debug_set_attn_plan(-1, 3)  # two 32-row items, two kv heads, three copies
+        assert B.ragc_debug_get_attn_plan(pool, one, 8) == (32, 8, 3)
+        assert B.ragc_prefill_attn_workspace(pool, one, 8) == 3 * 2 * 2 * 32 * (128 + 2) * 4
+        B.ragc_debug_set_attn_plan(0, 3)  # one 128-row item
+        assert B.ragc_debug_get_attn_plan(pool, one, 8) == (128, 4, 3)
         assert B.ragc_prefill_attn_workspace(pool, one, 8) == 3 * 2 * 128 * (128 + 2) * 4
         B.ragc_debug_set_attn_plan(0, 1)
+        assert B.ragc_debug_get_attn_plan(pool, one, 8) == (128, 4, 1)
         assert B.ragc_prefill_attn_workspace(pool, one, 8) == 0
         for bad in ((2, 0), (-2, 0), (0, 17), (0, -1)):
             with pytest.raises(B.RagcError) as e:
@@ -135,25 +140,84 @@ def test_debug_plan_override_changes_the_workspace_and_rejects_bad_values(lib):
     assert B.ragc_prefill_attn_workspace(pool, one, 8) == auto
 
 
-def test_key_split_rule_as_seen_through_the_workspace_size(lib):
-    """S = min(CUs / workgroups, key tiles of the longest item / 3, 16), 256 CUs when no GPU is visible
-    (an MI355X has as many); the workspace is one partial result per (item, copy, kv head)."""
-    part = 128 * (128 + 2) * 4
+def _plan(p, n, hq, hkv, d=128, flags=0, dtype=B.RAGC_DTYPE_BF16):
+    """(rows per work item, waves, copies) of the library's own choice, 256 CUs when no GPU is visible (an MI355X has as
+    many); the workspace is one partial result per work item, copy and kv head, and nothing where there is one copy."""
+    b, keep = _batch(p=p, n=n, stride=1200)
+    pool = _pool(num_blocks=4096, kv_heads=hkv, head_dim=d, dtype=dtype)
+    rows, waves, copies = B.ragc_debug_get_attn_plan(pool, b, hq, flags)
+    items = sum(-(-(x * (hq // hkv)) // rows) for x in n) if rows else 0
+    want = items * copies * hkv * rows * (d + 2) * 4 if copies > 1 else 0
+    assert B.ragc_prefill_attn_workspace(pool, b, hq, flags) == want
+    # never more than one 128-row partial result per CU
+    assert want <= 256 * 128 * (d + 2) * 4
+    return rows, waves, copies
 
-    def copies(p, n, hq, hkv, stride=1200):
-        b, keep = _batch(p=p, n=n, stride=stride)
-        items = sum(-(-(x * (hq // hkv)) // 128) for x in n)
-        ws = B.ragc_prefill_attn_workspace(_pool(num_blocks=4096, kv_heads=hkv), b, hq)
-        assert ws % (items * hkv * part) == 0
-        return ws // (items * hkv * part)  # 0: not split
 
-    assert copies((4096,) * 4, (1,) * 4, 64, 8) == 8       # 32 workgroups, 65 tiles: every CU gets one
-    assert copies((1024,), (100,), 32, 32) == 6            # 32 workgroups, 18 tiles: three tiles per copy
-    assert copies((2048,) * 2, (1,) * 2, 32, 8) == 11      # 16 workgroups, 33 tiles
-    assert copies((16384,), (1,), 32, 8) == 16             # capped
-    assert copies((1024,) * 8, (1,) * 8, 32, 32) == 0      # 256 workgroups already
-    assert copies((100,), (20,), 8, 8) == 0                # two tiles: nothing to split
-    assert copies((256,) * 8, (100,) * 8, 32, 32) == 0
+def test_key_split_rule(lib):
+    """Copies of a 32-row item: at least two key tiles for each of eight waves, one workgroup per CU, at most 16; one up to
+    1408 keys."""
+    assert _plan((4096,) * 4, (1,) * 4, 64, 8) == (32, 8, 8)       # 32 workgroups, 129 tiles: every CU gets one
+    assert _plan((1024,), (100,), 32, 32) == (32, 8, 1)            # 128 workgroups, 36 tiles
+    assert _plan((1308,), (100,), 32, 32) == (32, 8, 1)            # 44 tiles
+    assert _plan((1309,), (100,), 32, 32) == (32, 8, 2)            # 45 tiles
+    assert _plan((2048,) * 2, (1,) * 2, 32, 8) == (32, 8, 4)       # 16 workgroups, 65 tiles
+    assert _plan((16384,), (1,), 32, 8) == (32, 8, 16)             # capped
+    assert _plan((16384,), (1,), 32, 8, flags=B.RAGC_ATTN_NO_SPLIT) == (32, 8, 1)
+    assert _plan((1024,) * 8, (1,) * 8, 32, 32) == (32, 8, 1)      # 256 workgroups already
+    assert _plan((100,), (20,), 8, 8) == (32, 8, 1)                # four tiles: nothing to split
+    assert _plan((10, 0), (0, 0), 8, 8) == (0, 0, 0)
+
+
+@pytest.mark.parametrize("p,n,hq,hkv,d,want", [
+    # 32 rows per request: always the 32-row kernel; one more row and a full chip of 128-row items: the 128-row kernel
+    ((300,) * 256, (8,) * 256, 8, 2, 128, (32, 4, 1)),
+    ((300,) * 256, (9,) * 256, 8, 2, 128, (128, 4, 1)),
+    # fewer 128-row items than CUs: the 32-row kernel up to two of its workgroups per CU
+    ((300,), (1024,), 32, 8, 128, (128, 8, 1)),                      # 256 items of 128 rows
+    ((300,), (960,), 16, 8, 128, (32, 4, 1)),                        # 120 and 480
+    ((300,), (1056,), 16, 8, 128, (128, 8, 1)),                      # 136 and 528
+    # one to two 128-row items per CU, half empty: the 32-row kernel, up to three and short keys: shared CUs, above: one each
+    ((300,) * 9, (64,) * 9, 32, 32, 128, (128, 4, 1)),               # 288 and 576
+    ((300,) * 10, (40,) * 10, 32, 32, 64, (128, 8, 1)),              # 320 and 640 at head_dim 64, all of one length
+    ((50,) * 16, (17,) * 16, 32, 16, 128, (128, 8, 1)),              # 256 and 512: exactly one item per CU
+    ((50,) * 17, (9,) + (8,) * 16, 64, 16, 128, (32, 4, 1)),         # 272 and 288
+    ((50,) * 17, (9,) * 17, 64, 16, 128, (128, 4, 1)),               # 272 and 544
+    ((50,) * 17, (9,) * 17, 60, 15, 128, (32, 4, 1)),                # 255 and 510
+    ((960,) * 9, (64,) * 9, 32, 32, 128, (128, 4, 1)),               # 1024 keys
+    ((961,) * 9, (64,) * 9, 32, 32, 128, (128, 8, 1)),               # 1025 keys
+    # ragged batches of head_dim 64
+    ((1900, 300, 16, 700, 15, 0), (130, 60, 100, 90, 64, 130), 32, 8, 64, (32, 4, 1)),
+    # a little over one 32-row workgroup per CU, thousands of keys, one length: split or whole 128-row items
+    ((4445,) * 3, (46,) * 3, 64, 8, 128, (128, 4, 3)),               # 72 and 288
+    ((2000,) * 3, (46,) * 3, 64, 8, 128, (32, 4, 1)),                # 2046 keys: four waves instead
+    ((4445, 3000, 3000), (46,) * 3, 64, 8, 128, (32, 4, 1)),         # not of one length, mean 0.78 of the longest
+    ((4445, 2000, 2000), (46,) * 3, 64, 8, 128, (32, 8, 1)),         # less
+    ((3200,) * 20, (23,) * 20, 40, 8, 128, (128, 8, 1)),             # 160 and 320: nothing to split
+    # row tiles of a request on several XCDs
+    ((6833,) * 8, (17,) * 8, 8, 2, 128, (32, 8, 4)),                 # five copies would fit, four share an L2
+    ((5666,) * 9, (6,) * 9, 28, 4, 128, (128, 4, 7)),                # two copies leave CUs idle
+    ((2081,) * 9, (6,) * 9, 28, 4, 128, (32, 8, 2)),
+    ((7876,) * 3, (92,) * 3, 8, 2, 128, (128, 4, 14)),               # three copies fit, 73 MB would be read again
+    ((7876,), (92,), 8, 2, 128, (32, 8, 10)),                        # 24 MB
+    # decode steps of head_dim 64
+    ((4000,) * 66, (1,) * 66, 40, 8, 64, (128, 4, 1)),               # 528 of one length
+    ((4000,) * 65 + (2000,) * 9, (1,) * 74, 40, 8, 64, (32, 4, 1)),  # 592, not of one length
+    ((4000,) * 81, (1,) * 81, 40, 8, 64, (32, 4, 1)),                # 648
+    ((4000,) * 34, (1,) * 34, 40, 8, 64, (32, 4, 1)),                # 272 of one length
+    ((4000,) * 20 + (2000,) * 14, (1,) * 34, 40, 8, 64, (32, 8, 1)),
+    # decode steps of head_dim 128
+    ((2000,) * 64, (1,) * 64, 64, 8, 128, (32, 4, 1)),
+    ((2000,) * 30 + (700,) * 34, (1,) * 64, 64, 8, 128, (32, 8, 1)),
+    ((1500,) * 10 + (500,) * 54, (1,) * 64, 64, 8, 128, (32, 4, 1)),  # fewer than 1024 keys on average
+])
+def test_plan_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
+    assert _plan(p, n, hq, hkv, d) == want
+
+
+def test_fp32_plan(lib):
+    assert _plan((300,), (64,), 32, 8, dtype=B.RAGC_DTYPE_F32) == (16, 8, 1)    # 128 workgroups
+    assert _plan((300,), (129,), 32, 8, dtype=B.RAGC_DTYPE_F32) == (16, 4, 1)   # 264
 
 
 def test_size_limits_and_workspace_errors(lib):
@@ -162,10 +226,10 @@ def test_size_limits_and_workspace_errors(lib):
     huge, keep2 = _batch(p=(0,), n=(2_000_000,), stride=125_000)
     assert _attn_code(_pool(), huge, hq=16) == B.RAGC_ERR_RANGE  # 16 M rows: more than 65535 row tiles
     assert "too large" in B.ragc_last_error()
-    # one request with a long prefix is split along its keys: the workspace is then mandatory
+    # one request with a long prefix is split along its keys: the workspace is then mandatory, and without a split it is not
     one, keep3 = _batch(p=(4096,), n=(16,), stride=300)
     need = B.ragc_prefill_attn_workspace(_pool(num_blocks=512), one, 8)
-    assert need > 0 and need % (128 * (128 + 2) * 4) == 0
+    assert need == 8 * 2 * 2 * 32 * (128 + 2) * 4  # eight copies of two 32-row items, two kv heads
     assert B.ragc_prefill_attn_workspace(_pool(num_blocks=512), one, 8, B.RAGC_ATTN_NO_SPLIT) == 0
     assert B.ragc_prefill_attn_workspace(_pool(num_blocks=512, dtype=B.RAGC_DTYPE_F32), one, 8) == 0
     for ws, nbytes, code in ((None, 0, B.RAGC_ERR_WORKSPACE), (A, need - 1, B.RAGC_ERR_WORKSPACE), (A + 16, need, B.RAGC_ERR_ALIGN)):
