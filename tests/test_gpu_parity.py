@@ -723,3 +723,26 @@ def test_long_batches_of_one_length_match_oracle(H, hq, hkv, lens):
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("heads", [32767, 32768])
+def test_batches_of_more_workgroups_than_one_launch_takes(H, dtype, heads):
+    """One new token and nothing cached: the output is V, bit for bit.  40 requests of 32767 kv heads go out in launches of
+    four requests each (workgroup ids are divided by the heads with a multiply that is exact up to 2^32 / heads), of
+    32768 in launches of 31."""
+    reqs, d = 40, 64
+    gen = torch.Generator(device="cuda").manual_seed(8700)
+    td = H.torch_dtype(dtype)
+    q, k, v = (torch.randn((reqs, heads, d), generator=gen, device="cuda", dtype=torch.float32).to(td) for _ in range(3))
+    out = torch.full_like(q, float("nan"))
+    pool_k = torch.zeros((1, heads, 16, d), device="cuda", dtype=td)
+    pool_v = torch.zeros_like(pool_k)
+    pool = B.make_pool(pool_k, pool_v, 1, heads, d, B.RAGC_DTYPE_BF16 if dtype == "bf16" else B.RAGC_DTYPE_F32)
+    h = [np.zeros(reqs, np.int32), np.ones(reqs, np.int32), np.arange(reqs + 1, dtype=np.int32), np.zeros((reqs, 1), np.int32)]
+    dev = [torch.from_numpy(a).cuda() for a in h]
+    batch = B.make_batch(reqs, 1, *dev, *h)
+    assert B.ragc_prefill_attn_workspace(pool, batch, heads) == 0
+    B.ragc_prefill_attn(pool, batch, q, k, v, out, heads, 0.125, 0, None, 0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(out), _bits(v))
