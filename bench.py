@@ -223,9 +223,10 @@ def calibrate(torch):
 
 
 GRID_ALPHAS = [0, 256, 512, 768, 1024, 1280, 1536, 2048, 2560, 3072, 4096, 5120, 6144, 8192]
-# T steps with the number of 128-row tiles of a request (beta rows per head here), so the grid has a
-# point on either side of every step: linear interpolation between them then follows the staircase
-GRID_BETAS = [1] + [x for k in range(1, 9) for x in (128 * k, 128 * k + 1)][:-1]
+# T steps with the number of 128-row tiles of a request (beta rows per head here), and once more where its
+# rows no longer fit one 32-row tile, so the grid has a point on either side of every step: linear
+# interpolation between them then follows the staircase
+GRID_BETAS = [1, 32, 33] + [x for k in range(1, 9) for x in (128 * k, 128 * k + 1)][:-1]
 GRID_BATCH = 8
 
 
