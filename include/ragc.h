@@ -133,7 +133,9 @@ typedef struct ragc_kv_pool {
  * and the work items carry the lengths to the device in the kernel arguments, so a
  * serving loop passes h_prefix_len, h_new_len and h_new_start; any of them that is NULL
  * is read back from its device array with a synchronous hipMemcpy inside the call (slow,
- * not capturable in a HIP graph, and the device array must be complete by then).
+ * not capturable in a HIP graph, and the device array must be complete by then).  An attention
+ * call captured in a HIP graph replays with the lengths of the capture, in fp32 and in bf16;
+ * block_table, and for ragc_kv_append all device arrays, are read when the work runs.
  * h_block_table is optional; when given, every entry the call will touch is
  * range-checked. */
 typedef struct ragc_batch {

@@ -23,14 +23,14 @@
 // tile before, V during the Q.K products.
 //
 // What bounds it: the matrix cores, 64 flop per cycle and SIMD (157 TFLOP/s on the chip; a large
-// library product reaches 133).  A 16-key tile at head_dim 128 is 64 products, 2048 cycles, and
+// library product reaches 153).  A 16-key tile at head_dim 128 is 64 products, 2048 cycles, and
 // the loop runs at 0.8 of that with two waves per SIMD; the rest of a small call is the 5 us
 // before the first tile and after the last.  Measured: 4 requests of 512-1024 cached and 32-100
-// new tokens, 32/8 heads: 195 -> 39 us (plain FMAs from shared tiles before); one request of
-// 256 + 32 tokens, 4 heads of 64: 27 -> 9 us.  Read from global memory in operand order instead
-// of through LDS, K costs a cache access per lane (41 on average per load instruction, 2600
-// cycles per tile and CU) and the first of these takes 43 us; with K staged through registers
-// and three waves per SIMD, 42 us.
+// new tokens, 32/8 heads: 196 -> 36.6 us (plain FMAs from shared tiles before); one request of
+// 256 + 32 tokens, 4 heads of 64: 27 -> 7.4 us.  Tried, when the first of these took 39: K read
+// from global memory in operand order instead of through LDS costs a cache access per lane (41
+// on average per load instruction, 2600 cycles per tile and CU), 43 us; K staged through
+// registers and three waves per SIMD, 42 us.
 #include "attn_bf16_common.h"
 #include "attn_work.h"
 
