@@ -160,10 +160,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
     auto do_tile = [&](int step, auto more_c) {
         constexpr bool MORE = decltype(more_c)::value;  // another tile follows
         wait_vmcnt<NI>();  // K is here, V may be under way
-        // Eight chains of products: a product waits for the one before it, and every one of a chain rounds at the size of
-        // the sum so far.  Against 64 bits, 4 requests of 512-1024 + 32-100 tokens, five draws: relative error 4.0e-7 to
-        // 4.2e-7 and largest 3.6e-6 to 4.9e-6; with two chains 5.8e-7 to 6.1e-7 and 6.0e-6 to 1.6e-5 in the same time.
-        constexpr int CH = 8;
+        // Two chains of products side by side (a product waits for the one before it), and two after one another (each rounds
+        // at the size of its sum so far).  Against 64 bits, 4 requests of 512-1024 + 32-100 tokens, five draws: relative error
+        // 4.5e-7 to 4.7e-7, largest 4.2e-6 to 6.3e-6; with one pair 5.8e-7 to 6.1e-7 and 6.0e-6 to 1.6e-5, in the same time.
+        // More side by side cost time where two waves share a SIMD (eight: 2 % on 43 batches, up to 24 %).
+        constexpr int CH = 4;
         f32x4 sp[CH];
 #pragma unroll
         for (int x = 0; x < CH; ++x) sp[x] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
             const f32x4 kr = *reinterpret_cast<lds_f32x4*>(kbuf + koff[j]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                f32x4& x = sp[(4 * j + e) % CH];
+                f32x4& x = sp[2 * (j / (KJ / 2)) + e % 2];
                 x = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[e], qreg[j][e], x, 0, 0, 0);
             }
         }

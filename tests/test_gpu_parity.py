@@ -697,14 +697,14 @@ def test_fp32_infinite_v_of_the_newest_token_gives_infinity(H, hq, hkv, d):
 @pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 2, 64)])
 def test_fp32_scores_are_summed_in_short_chains(H, hq, hkv, d):
     """Relative error against 64 bits under a moderately sharp softmax, where the rounding of the scores decides it:
-    3.4e-7 to 3.6e-7 with eight chains of products per score, 5.6e-7 (head_dim 128) and 4.5e-7 (64) with two,
-    6.0e-7 and 5.8e-7 with plain multiply-adds; within 2 % over the seeds."""
+    4.2e-7 (head_dim 128) and 3.7e-7 (64) with chains of 8 and 4 products, 5.6e-7 and 4.5e-7 with chains twice as long,
+    6.0e-7 and 5.8e-7 with plain multiply-adds; within 2 % over the seeds.  The bounds lie between the first two."""
     errors = []
     for seed in (8500, 8501, 8502):
         w = W.make_small("f32", hq, hkv, d, [(900, 40), (600, 60)], seed=seed, q_gain=2.0)
         got = U.out_to_f64(H.to_host(H.DeviceWorkload(w).attn()), "f32")
         errors.append(U.rel_l2(got, U.oracle_all(w)))
-    assert max(errors) <= 4e-7, errors
+    assert max(errors) <= (4.8e-7 if d == 128 else 4.1e-7), errors
 
 
 @pytest.mark.parametrize("hq,hkv,lens", [
