@@ -26,7 +26,7 @@
 // library product reaches 153).  A 16-key tile at head_dim 128 is 64 products, 2048 cycles, and
 // the loop runs at 0.8 of that with two waves per SIMD; the rest of a small call is the 5 us
 // before the first tile and after the last.  Measured: 4 requests of 512-1024 cached and 32-100
-// new tokens, 32/8 heads: 196 -> 36.6 us (plain FMAs from shared tiles before); one request of
+// new tokens, 32/8 heads: 196 -> 36.2 us (plain FMAs from shared tiles before); one request of
 // 256 + 32 tokens, 4 heads of 64: 27 -> 7.4 us.  Tried, when the first of these took 39: K read
 // from global memory in operand order instead of through LDS costs a cache access per lane (41
 // on average per load instruction, 2600 cycles per tile and CU), 43 us; K staged through
