@@ -55,6 +55,31 @@ __device__ __forceinline__ void dma_runs(uint64_t sbase, const uint32_t* off, ui
               "n"(OFF0 + 2048), "n"(OFF0 + 3072)
             : "m0");
 }
+// One dword per lane from `p`, and behind it N copies of 64 x 16 bytes straight into LDS (lane i's from src[x], to lds_addr +
+// x * stride + 16 i); returns when the dword is here, with the copies still under way.  All in one statement: the load's
+// register is not the compiler's before it has been written, and the compiler's own wait for it would drain the copies.
+template <int N>
+__device__ __forceinline__ int load_ahead_of_copies(const int32_t* p, const void* const* src, uint32_t lds_addr, uint32_t stride) {
+    static_assert(N == 1 || N == 2 || N == 4, "copies");
+    int v;
+    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+    if constexpr (N == 1)
+        asm volatile("global_load_dword %0, %1, off\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, off\n\ts_waitcnt vmcnt(1)"
+                     : "=&v"(v) : "v"(p), "s"(lds_addr), "v"(src[0]) : "memory", "m0");
+    else if constexpr (N == 2)
+        asm volatile(
+            "global_load_dword %0, %1, off\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, off\n\t"
+            "s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, off\n\ts_waitcnt vmcnt(2)"
+            : "=&v"(v) : "v"(p), "s"(lds_addr), "s"(lds_addr + stride), "v"(src[0]), "v"(src[1]) : "memory", "m0");
+    else
+        asm volatile(
+            "global_load_dword %0, %1, off\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, off\n\t"
+            "s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, off\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\t"
+            "global_load_lds_dwordx4 %8, off\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %9, off\n\ts_waitcnt vmcnt(4)"
+            : "=&v"(v) : "v"(p), "s"(lds_addr), "s"(lds_addr + stride), "s"(lds_addr + 2 * stride), "s"(lds_addr + 3 * stride),
+              "v"(src[0]), "v"(src[1]), "v"(src[2]), "v"(src[3]) : "memory", "m0");
+    return v;
+}
 __device__ __forceinline__ uint64_t uniform_u64(const void* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);

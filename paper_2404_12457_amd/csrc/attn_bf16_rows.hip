@@ -38,6 +38,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     constexpr int OCH = D / 4;        // 16-byte chunks of a fp32 output row
     static_assert(TR * D * 4 == 2 * PLANEB, "a wave's output fills its tile buffers");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * PLANEB];
+    __shared__ __attribute__((aligned(1024))) char qs[TR * ROWB];
     __shared__ float2 MLs[NW][TR];  // (max, sum) of every wave and row
 
     touch_args(a, wk);
@@ -76,23 +77,28 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
 
     // block ids of this wave's tiles, 32 steps of two at a time, one per lane
     const int nblk = (kv_limit + kBlock - 1) / kBlock;
-    int blk_base = 0, blk_vec = 0;
-    auto load_ids = [&](int step) {
-        blk_base = step;
-        blk_vec = table[min(tile_of(step + (lane >> 1)) * 2 + (lane & 1), nblk - 1)];
-    };
-    if (nsteps > 0) load_ids(0);
-    bf16x8 qreg[KSTEPS];
-    {
-        const __bf16* qp = q + ((long long)(s0 + my_tok) * Hq + g * G + (my_row - my_tok * G)) * D + hf * 8;
+    auto id_at = [&](int step) { return table + min(tile_of(step + (lane >> 1)) * 2 + (lane & 1), nblk - 1); };
+    int blk_base = 0, blk_vec;
+
+    // Q: every wave needs all rows.  Of more than eight they are copied to LDS once and shared, 1 KiB per instruction: read by
+    // every wave from memory they were 64 KiB per workgroup, half as much as the first tiles behind them (one request of 1024
+    // + 100 tokens 11.05 -> 10.6 us, 3000 + 64 of 2 heads, split, 12.9 -> 11.6).  Up to eight, the rows of a decode step, are
+    // 16 KiB and stay with the waves, behind their first tiles: no wave waits for the others (4 of 4096 keys 16.7 us, with
+    // shared rows 17.6).
+    const bool share_q = rows_here > 8;
+    if (share_q) {
+        constexpr int QI = TR / RPI, NQ = QI > NW ? QI / NW : 1;  // with fewer pieces than waves some bring the same one
+        const void* src[NQ];
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+        for (int x = 0; x < NQ; ++x) {
+            const int r = RPI * ((w + x * NW) % QI) + lane / CPR, row = row0 + min(r, rows_here - 1), tok = div_g(row);
+            src[x] = q + ((long long)(s0 + tok) * Hq + g * G + (row - tok * G)) * D + ((lane % CPR) ^ swz<D>(r)) * 8;
+        }
+        blk_vec = load_ahead_of_copies<NQ>(id_at(0), src, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)qs + w % QI * 1024, NW * 1024);
+    } else {
+        blk_vec = *id_at(0);
+        asm volatile("" ::"v"(blk_vec));  // the wait for this load stays inside the branch
     }
-    // every ordinary load has completed before the copies start to be counted
-    asm volatile("" ::"v"(blk_vec));
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" ::"v"(qreg[ks]));
-    wait_vmcnt<0>();
 
     // ---- copies: lane i of an instruction brings row RPI c + i / CPR of a block, chunk (i % CPR) ^ swz(row)
     typedef __attribute__((address_space(3))) char lds_char;
@@ -133,6 +139,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
         }
     };
 
+    // ---- the first tile, as soon as its block ids are here
+    if (nsteps > 0) {
+        copy_tile(0, true);
+        copy_tile(0, false);
+        if (share_q) wait_vmcnt<2 * NI>();  // this wave's part of Q
+    } else if (share_q) {
+        wait_vmcnt<0>();
+    }
+
     // ---- operand addresses (see attn_bf16_kernel)
     int koff[KSTEPS], voff[2][DT];
 #pragma unroll
@@ -145,6 +160,21 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
             const int elem = dt * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
             voff[h2][dt] = row * ROWB + ((((elem >> 3)) ^ swz<D>(row)) << 4) + (elem & 7) * 2;
         }
+
+    bf16x8 qreg[KSTEPS];
+    if (share_q) {
+        block_barrier();  // every wave's part of Q has landed
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            qreg[ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((lds_char*)qs + koff[ks]);
+    } else {
+        const __bf16* qp = q + ((long long)(s0 + my_tok) * Hq + g * G + (my_row - my_tok * G)) * D + hf * 8;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+        // every ordinary load has completed before the loop's copies are counted
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" ::"v"(qreg[ks]));
+    }
 
     f32x16 oacc[DT];
 #pragma unroll
@@ -167,7 +197,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
         }
         if (MORE) {
             if (step + 1 - blk_base >= 32) {
-                load_ids(step + 1);
+                blk_base = step + 1;
+                blk_vec = *id_at(step + 1);
                 asm volatile("" ::"v"(blk_vec));  // the wait for this load stays inside the branch
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this tile's K has been read
@@ -223,8 +254,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
         }
     };
     if (nsteps > 0) {
-        copy_tile(0, true);
-        copy_tile(0, false);
         for (int step = 0; step + 1 < nsteps; ++step) do_tile(step, std::true_type{});
         do_tile(nsteps - 1, std::false_type{});
     }
@@ -246,11 +275,18 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
 
     // ---- combine the waves' states: O = sum_w O_w 2^(m_w - m), l = sum_w l_w 2^(m_w - m), m = max_w m_w.  Every wave
     // leaves its O in its own part of LDS, [row][chunk of 4 columns], chunks XORed with the row against bank conflicts.
-    // l is exactly 0 in a wave that has seen no key of the row, and its O is not looked at; m = -inf does not say so: a
+    // l is exactly 0 in a wave that has seen no key of the row, and its O counts as 0; m = -inf does not say so: a
     // wave whose scores were all NaN still has it, next to l = NaN and O = NaN, which must reach the output.
+    // All waves' pieces are read without a look at their weights: a branch per wave made a trip to LDS of each.
     l_run += other_half(l_run);
     if (hf == 0) MLs[w][l32] = float2{m_run, l_run};
-    if (l32 < rows_here && l_run != 0.f) {
+    if (l_run == 0.f) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+    }
+    if (l32 < rows_here) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -273,8 +309,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
         f32x4 o[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
-            if (ml[x].y == 0.f) continue;  // a wave, or every one of a copy, may have seen no key of the row
-            const float wgt = __builtin_amdgcn_exp2f(ml[x].x - m);
+            // a wave, or every one of a copy, may have seen no key of the row
+            const float wgt = ml[x].y == 0.f ? 0.f : __builtin_amdgcn_exp2f(ml[x].x - m);
             l += ml[x].y * wgt;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
