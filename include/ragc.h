@@ -198,7 +198,7 @@ int ragc_batch_validate(const ragc_kv_pool* pool, const ragc_batch* batch, int32
 int ragc_debug_set_attn_plan(int32_t variant, int32_t splits);
 
 /* Test hook: the layout ragc_prefill_attn would choose for this batch with these flags (under
- * the override above, if any).  plan[0]: rows per work item (fp32: 16; bf16: 32 or 128),
+ * the override above, if any).  plan[0]: rows per work item (fp32: 16 or 32; bf16: 32 or 128),
  * plan[1]: waves per workgroup, plan[2]: copies of every work item along the keys (1: not
  * split); all 0 for a batch without new tokens.  Only the host arrays of `batch` are read. */
 int ragc_debug_get_attn_plan(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads, uint32_t flags,

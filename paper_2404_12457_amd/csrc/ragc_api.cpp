@@ -437,21 +437,40 @@ int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& 
     });
 }
 
-// fp32 path.  With at most one workgroup per CU a workgroup has eight waves, so that every SIMD still has two to
-// overlap (256 workgroups of ~1100 keys: 31 us against 37); with more, four, and two workgroups share a CU (416 of
-// ~1000 keys: 45 us against 49, 512 of ~1100: 53 against 58).
-int f32_waves(const HostMeta& h, const std::vector<int32_t>& order, int group, int kv_heads) {
-    int64_t tiles = 0;
-    for (int r : order) tiles += row_tiles(h, r, group, ragc::kAttnF32RowsPerItem);
-    return tiles * kv_heads > (int64_t)cu_count() ? 4 : 8;
+// fp32 path: which kernel (rows per item), and how many waves per workgroup.
+// Waves: with at most one workgroup per CU eight, so that every SIMD still has two to overlap (16-row items: 256 workgroups of
+// ~1100 keys 31 us against 37); with more, four, and two workgroups share a CU (416 of ~1000 keys: 45 us against 49, 512 of
+// ~1100: 53 against 58; 32-row items: 848 66 against 74, 384 22 against 27).
+// The 32-row items, whose kernel multiplies on the bf16 cores, take 0.72-0.85 of the time of the 16-row items where those leave
+// no CU idle, and more where they do (125 of ~2000 keys: 52 us against 41) or where their rows would be half empty (320
+// against 480: 15.2 against 11.9).  Lines from 160 batches timed with every choice, in workgroups of 16 rows per CU:
+// head_dim 128, from 1.25 on (1.3: 0.76-0.93; 1.03-1.16: 1.0-1.2), while they are at most one per CU with at least 96 keys on
+// average (1.6: 1.06 and 1.09 below); head_dim 64, whose steps are shorter, from 1 to 2 with at least 200 keys (0.74-0.96) and
+// from 4.5 on (0.74-0.93); 2 to 4: 0.93-1.11.
+struct F32Plan {
+    int rows, waves;
+};
+F32Plan plan_f32(const HostMeta& h, const std::vector<int32_t>& order, int group, int kv_heads, int head_dim) {
+    int64_t tiles = 0, split_tiles = 0, keys = 0;  // keys: over the 16-row items
+    for (int r : order) {
+        const int64_t t = row_tiles(h, r, group, ragc::kAttnF32Rows);
+        tiles += t;
+        split_tiles += row_tiles(h, r, group, ragc::kAttnF32SplitRows);
+        keys += t * ((int64_t)h.prefix_len[r] + h.new_len[r]);
+    }
+    const int64_t cus = cu_count(), wgs = tiles * kv_heads, split_wgs = split_tiles * kv_heads;
+    const bool split = split_tiles * 5 <= tiles * 3 &&
+                       (head_dim == 128 ? wgs * 4 >= cus * 5 && (split_wgs > cus || keys >= 96 * tiles)
+                                        : wgs * 2 >= cus * 9 || (wgs > cus && split_wgs <= cus && keys >= 200 * tiles));
+    return {split ? ragc::kAttnF32SplitRows : ragc::kAttnF32Rows, (split ? split_wgs : wgs) > cus ? 4 : 8};
 }
 
 int run_f32(const ragc::AttnLaunch& a, const ragc_batch* batch, const HostMeta& h, hipStream_t s) {
     std::vector<int32_t> order;
     order_requests(h, batch->num_reqs, &order);
-    const int waves = f32_waves(h, order, a.group, a.kv_heads);
-    return run_list(a, h, order, ragc::kAttnF32RowsPerItem, 1,
-                    [&](const ragc::AttnWork& wk, int entries) { return ragc::launch_attn_f32(a, wk, entries, waves, s); });
+    const F32Plan plan = plan_f32(h, order, a.group, a.kv_heads, a.head_dim);
+    return run_list(a, h, order, plan.rows, 1,
+                    [&](const ragc::AttnWork& wk, int entries) { return ragc::launch_attn_f32(a, wk, entries, plan.rows, plan.waves, s); });
 }
 
 // ---- partial results of key-split work items for callers that cannot allocate --------------
@@ -593,8 +612,9 @@ int ragc_debug_get_attn_plan(const ragc_kv_pool* pool, const ragc_batch* batch, 
     if (pool->dtype == RAGC_DTYPE_F32) {
         std::vector<int32_t> order;
         order_requests(h, batch->num_reqs, &order);
-        plan[0] = ragc::kAttnF32RowsPerItem;
-        plan[1] = f32_waves(h, order, group, pool->kv_heads);
+        const F32Plan p = plan_f32(h, order, group, pool->kv_heads, pool->head_dim);
+        plan[0] = p.rows;
+        plan[1] = p.waves;
         plan[2] = 1;
         return RAGC_OK;
     }

@@ -90,9 +90,11 @@ inline AttnWorkShort short_list(const AttnWork& w) {
     return s;
 }
 
-constexpr int kAttnF32RowsPerItem = 16;
-// waves: 4 or 8 per workgroup
-hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
+// fp32 path (attn_f32.hip): row tiles of 16 rows, or of 32 for the kernel that splits its operands
+constexpr int kAttnF32Rows = 16;
+constexpr int kAttnF32SplitRows = 32;
+// rows: one of these; waves: 4 or 8 per workgroup
+hipError_t launch_attn_f32(const AttnLaunch& a, const AttnWork& wk, int entries, int rows, int waves, hipStream_t s);
 
 // bf16 path.  Large batches: row tiles of kAttnRowsPerItem rows (attn_bf16.hip).  Launches that cannot fill the chip
 // with those: kAttnShortRows rows (attn_bf16_rows.hip), or either split along the keys.

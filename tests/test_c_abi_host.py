@@ -282,3 +282,19 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(RuntimeError, match="no fallback"):
         B.ragc_version()
+
+
+@pytest.mark.parametrize("p,n,hq,hkv,d,want", [
+    ((300,), (160,), 32, 8, 128, (32, 8, 1)),             # head_dim 128: 320 workgroups of 16 rows
+    ((300,), (156,), 32, 8, 128, (16, 4, 1)),             # 312
+    ((10,), (160,), 32, 8, 128, (32, 8, 1)),              # 170 keys
+    ((100,) * 16, (11,) * 16, 32, 8, 128, (16, 4, 1)),    # 384, and 256 of 32 rows: half empty
+    ((0,) * 3, (64,) * 3, 32, 8, 128, (16, 4, 1)),        # 384 of 64 keys, 192 of 32 rows
+    ((0,) * 5, (64,) * 5, 32, 8, 128, (32, 4, 1)),        # 640, 320
+    ((300,), (132,), 32, 8, 64, (32, 8, 1)),              # head_dim 64: 264
+    ((30,), (132,), 32, 8, 64, (16, 4, 1)),               # of 162 keys
+    ((300,), (300,), 32, 8, 64, (16, 4, 1)),              # 600
+    ((300,), (576,), 32, 8, 64, (32, 4, 1)),              # 1152
+])
+def test_fp32_plan_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
+    assert _plan(p, n, hq, hkv, d, dtype=B.RAGC_DTYPE_F32) == want

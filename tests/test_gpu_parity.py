@@ -746,3 +746,62 @@ def test_batches_of_more_workgroups_than_one_launch_takes(H, dtype, heads):
     B.ragc_prefill_attn(pool, batch, q, k, v, out, heads, 0.125, 0, None, 0, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(_bits(out), _bits(v))
+
+
+SPLIT_F32 = [
+    (32, 32, 128, [(0, 97), (150, 64), (15, 31)]),     # one row per token; frontiers inside and at the ends of tiles and blocks
+    (28, 4, 128, [(130, 33), (64, 150), (17, 80)]),    # group of 7: tokens straddle row tiles
+    (32, 8, 128, [(1100, 150), (9, 150), (0, 150)]),   # more tiles than waves, four waves per workgroup
+    (16, 16, 64, [(300, 200), (170, 90), (250, 17)]),
+    (32, 8, 64, [(20, 300), (0, 330)]),                # four waves per workgroup
+]
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", SPLIT_F32, ids=lambda v: str(v) if isinstance(v, int) else f"R{len(v)}")
+def test_fp32_split_products_at_their_edges(H, hq, hkv, d, lens):
+    """fp32 on 32-row items, products on the bf16 cores, against the fp64 oracle and byte for byte in the append.  Its
+    error is not above that of fp32 products (test_fp32_scores_are_summed_in_short_chains has theirs)."""
+    w = W.make_small("f32", hq, hkv, d, lens, seed=8800 + len(lens), q_gain=2.0)
+    dw, got, want = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, hq)[0] == 32
+    assert U.rel_l2(got, want) <= 4.8e-7
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "f32")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "f32")))
+
+
+@pytest.mark.parametrize("h,d,n", [(32, 128, 165), (16, 64, 300)], ids=["d128", "d64"])
+@pytest.mark.parametrize("what", ["inf_v", "nan_v", "inf_k", "tiny_v", "tiny_column", "largest_v"])
+def test_fp32_split_products_keep_what_no_split_survives(H, h, d, n, what):
+    """Infinities, NaN, the largest floats and magnitudes whose third parts are denormal come out as fp32 products give
+    them.  One request without a prefix, one row per token; head 1 is touched, from token 100 on where it is one token."""
+    w = W.make_small("f32", h, h, d, [(0, n)], seed=8900, q_gain=2.0)
+    k, v = np.array(w.k_new, np.float32), np.array(w.v_new, np.float32)
+    if what == "inf_v": v[100, 1, 5] = np.inf
+    if what == "nan_v": v[100, 1, 5] = np.nan
+    if what == "inf_k": k[100, 1, 5] = np.inf
+    if what == "tiny_v": v *= np.float32(1e-36)
+    if what == "tiny_column": v[:, :, 8:12] *= np.float32(1e-36)
+    if what == "largest_v": v[0, 1] = np.float32(3.4e38)  # infinite when rounded to bf16; token 0 sees nothing else
+    dw = H.DeviceWorkload(w)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, h)[0] == 32
+    dw.k_new.copy_(torch.from_numpy(k).reshape(dw.k_new.shape))
+    dw.v_new.copy_(torch.from_numpy(v).reshape(dw.v_new.shape))
+    got = dw.attn().double().cpu().numpy()
+    q, k, v = (np.asarray(x, np.float64) for x in (w.q, k, v))
+    for t in range(n):
+        if what in ("inf_v", "nan_v") and 100 - 32 < t < 100:
+            continue  # a key that the row does not see, but another row of its work item does: 0 * inf
+        with np.errstate(all="ignore"):
+            sc = np.einsum("hd,shd->hs", q[t], k[:t + 1]) * float(w.softmax_scale)
+            p = np.exp(sc - sc.max(1, keepdims=True))
+            want = np.einsum("hs,shd->hd", p / p.sum(1, keepdims=True), v[:t + 1])
+        if what == "largest_v":
+            assert np.array_equal(got[0, 1], v[0, 1])
+            want[1] = got[t, 1]  # sums of such values may overflow
+        assert np.array_equal(np.isnan(got[t]), np.isnan(want)), t
+        assert np.array_equal(np.isinf(got[t]), np.isinf(want)), t
+        ok = np.isfinite(want)
+        scale = np.abs(np.where(ok, want, 0)).max(0) if what == "tiny_column" else np.abs(np.where(ok, want, 0)).max()
+        assert np.all(np.abs(np.where(ok, got[t], 0) - np.where(ok, want, 0)) <= 1e-4 * scale), t  # the bound of test_small_cases, where |V| is 1
