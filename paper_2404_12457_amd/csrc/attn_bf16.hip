@@ -32,9 +32,20 @@
 //   O^T[d][row]  += V^T . P^T    A = V tile read with the transposing LDS load,
 //                                B = P^T, which is exactly the accumulator layout of
 //                                S^T after conversion to bf16 -- no data movement.
-// With v_mfma_f32_32x32x16_bf16 a lane holds 16 of the 32 keys of a sub-tile for its
-// row; the other 16 sit in lane+32.  The row's reference exponent is only raised (and O, l
-// rescaled) when a tile's probabilities against it sum to more than 2^8.
+// The row's reference exponent is only raised (and O, l rescaled) when a tile's probabilities
+// against it sum to more than 2^8.
+//
+// What bounds it, and which product.  With every CU busy the power limit holds the clock at 1.5 to
+// 2.1 GHz, and then a product's energy counts more than its cycles: on random operands a loop of
+// v_mfma_f32_16x16x32_bf16 sustains 1852 TFLOP/s at 2.07 GHz where 32x32x16, which moves the
+// accumulators through the registers twice as often per flop, sustains 1640 at 1.77.  At head_dim 128
+// the kernel uses 16x16x32 (KG = 4: two blocks of 16 rows per wave, a row in four lanes): 4 x (4096 +
+// 128) tokens of 64/8 heads 69.9 -> 66.3 us, 16 x (256-4096 + 64-768) of 32/8 302 -> 286, four whole
+// prompts of 2200-3500 252 -> 244.  Per cycle it is the slower one (16.5-17 instead of 16 in a loop),
+// and at head_dim 64, where a step has half the products for the same softmax and its launches mostly
+// run at 2.1 GHz and above, 32x32x16 (KG = 2: one block of 32 rows, a row in two lanes) stays ahead:
+// 320 items of 450-1900 keys 21.5 us against 22.7; only with the chip full of long items it is not
+// (2048 of 4224 keys: 81 us against 78).
 #include "attn_bf16_common.h"
 #include "attn_work.h"
 
@@ -51,19 +62,30 @@ __device__ __forceinline__ void static_for(const F& f) {
     }
 }
 
+__device__ __forceinline__ f32x16 product(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f32x4 product(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
 template <int D, int NG, bool SPLIT, class Work>
 __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
     static_assert(!SPLIT || NG == 1, "copies of an item are one wave group each");
     constexpr int RING = 2;             // stages per wave group
-    constexpr int NSUB = 2;             // 32-key halves of a tile
+    // Which product: v_mfma_f32_16x16x32_bf16 (KG = 4) or 32x32x16 (KG = 2); a lane is row lane % BR and group lane / BR
+    constexpr int KG = D == 128 ? 4 : 2;  // lanes per row, each with every KG-th run of four keys or columns
+    constexpr int BR = 64 / KG;         // rows, keys and columns of a product
+    constexpr int CK = 8 * KG;          // its contraction
+    constexpr int NE = 16 / (KG * KG / 4);  // accumulators per lane
+    constexpr int NSUB = TN / BR;       // BR-key subtiles of a tile
+    constexpr int RB = 32 / BR;         // BR-row blocks of a wave
+    typedef __attribute__((ext_vector_type(NE))) float accv;
     constexpr int CPR = D / 8;          // 16-byte chunks per K/V row
     constexpr int ROWB = D * 2;         // bytes per row
     constexpr int PLANEB = TN * ROWB;   // one tile of K (or V)
     constexpr int STAGEB = 2 * PLANEB;
     constexpr int RPI = 64 / CPR;       // rows covered by one wave-wide 1 KiB DMA instruction
     constexpr int IPB = 16 / RPI;       // DMA instructions per 16-row block and plane
-    constexpr int KSTEPS = D / 16;
-    constexpr int DT = D / 32;
+    constexpr int KSTEPS = D / CK;
+    constexpr int PSTEPS = TN / CK;     // contraction steps of P.V
+    constexpr int DB = D / BR;          // BR-column blocks of the output
     constexpr int NSTAGE = NG * RING;
     static_assert(NSTAGE * STAGEB <= 160 * 1024, "LDS");
     __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGEB];
@@ -73,7 +95,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     int g, entry;
     split_block_id(a, blockIdx.x, &g, &entry);
     entry += wk.entry0;
-    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, kg = lane / BR, lrow = lane % BR;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = NG == 1 ? 0 : w >> 2, wq = w & 3;
     const int S = SPLIT ? wk.splits : 1, sidx = SPLIT ? entry % S : 0;
@@ -107,10 +129,15 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
 
     // ---- this lane's query row
     const int wrow0 = row0 + wq * 32;
-    const int my_row = min(wrow0 + l32, rows_total - 1);  // rows past the end repeat the last one
-    const int my_tok = div_g(my_row);
-    const int my_head = g * G + (my_row - my_tok * G);
-    const int my_vis = P + my_tok + 1;  // keys [0, my_vis) are visible to this row
+    int my_vis[RB];  // keys [0, my_vis) are visible to row lrow of each block
+    const __bf16* qp[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int my_row = min(wrow0 + rb * BR + lrow, rows_total - 1);  // rows past the end repeat the last one
+        const int my_tok = div_g(my_row);
+        my_vis[rb] = P + my_tok + 1;
+        qp[rb] = q + ((long long)(s0 + my_tok) * Hq + g * G + (my_row - my_tok * G)) * D + kg * 8;
+    }
     const bool wave_active = wrow0 < rows_total;
     const int wave_vis_min = P + div_g(wrow0) + 1;
     const int wave_vis_max = P + div_g(min(wrow0 + 31, rows_total - 1)) + 1;
@@ -126,18 +153,19 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
         const int e = (min(t_lo + lane * NG + grp, max(ntiles - 1, 0)) * TN >> 4) + wq;
         blk_vec = e < nblk_item ? table[e] : 0;
     }
-    bf16x8 qreg[KSTEPS];
-    {
-        const __bf16* qp = q + ((long long)(s0 + my_tok) * Hq + my_head) * D + hf * 8;
+    bf16x8 qreg[RB][KSTEPS];
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-    }
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) qreg[rb][ks] = *reinterpret_cast<const bf16x8*>(qp[rb] + ks * CK);
     // Every ordinary load above completes here, before the DMA ring starts counting.  The
     // empty asm statements make the compiler itself wait for these registers now; otherwise it
     // would place its vmcnt waits at their first use inside the loop and drain the ring there.
     asm volatile("" ::"v"(blk_vec));
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" ::"v"(qreg[ks]));
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" ::"v"(qreg[rb][ks]));
     wait_vmcnt<0>();
 
     // ---- DMA: wave (grp, wq) copies block wq (16 keys) of tile step*NG+grp, K and V planes.
@@ -150,7 +178,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
 #pragma unroll
         for (int c = 0; c < IPB; ++c) {
             const int row16 = RPI * c + lane / CPR;
-            const int chunk = (lane % CPR) ^ swz<D>(row16);
+            const int chunk = (lane % CPR) ^ swz<D, KG>(row16);
             loff[c] = (row16 * row_stride + chunk * 8) * 2 - c * 1024;
         }
     };
@@ -174,6 +202,14 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             pend = 0;
         }
     };
+    // Steps whose block of this wave is cached as a whole -- most of them -- take one branch, a lane read and a few scalar sums,
+    // as all of it stands between the barrier and the first product of a step (with the three cases told apart and the
+    // address made anew in 64 bits at each: 8 x (4096 + 128) tokens of 64/8 heads 141.7 us against 135.1).
+    const uint64_t block_bytes = (uint64_t)a.block_stride * 2;
+    const uint64_t head_k = uniform_u64(pool_k + (long long)g * kBlock * D), head_v = uniform_u64(pool_v + (long long)g * kBlock * D);
+    const uint32_t copy_dst = smem_addr + grp * RING * STAGEB + wq * 16 * ROWB;
+    const int pool_tiles = P >= wq * 16 + 16 ? (P - wq * 16 - 16) / TN + 1 - t_lo - grp : 0;
+    const int pool_steps = pool_tiles > 0 ? (pool_tiles + NG - 1) / NG : 0;
     auto prepare = [&](int step) {
         if (step - blk_base >= 64) {
             blk_base = step;
@@ -181,18 +217,20 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             blk_vec = e < nblk_item ? table[e] : 0;
             asm volatile("" ::"v"(blk_vec));  // the compiler's wait for this load stays inside the branch
         }
-        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
-        const int kbase = tg * TN + wq * 16;
         const int blk = __builtin_amdgcn_readlane(blk_vec, step - blk_base);
-        const uint32_t dst = smem_addr + (grp * RING + step % RING) * STAGEB + wq * 16 * ROWB;
-        if (kbase + 16 <= P) {
-            // the whole block is cached: one pool block, uniform base + per-lane constant
-            const long long boff = ((long long)blk * a.block_stride + (long long)g * kBlock * D) * 2;
-            pend_kb = uniform_u64(reinterpret_cast<const char*>(pool_k) + boff);
-            pend_vb = uniform_u64(reinterpret_cast<const char*>(pool_v) + boff);
+        const uint32_t dst = copy_dst + step % RING * STAGEB;
+        if (__builtin_expect(step < pool_steps, 1)) {
+            // one pool block, uniform base + per-lane constant
+            const uint64_t boff = (uint32_t)blk * block_bytes;
+            pend_kb = head_k + boff;
+            pend_vb = head_v + boff;
             pend_dst = dst;
             pend = 1;
-        } else if (kbase >= P && kbase + 16 <= kv_limit) {
+            return;
+        }
+        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
+        const int kbase = tg * TN + wq * 16;
+        if (kbase >= P && kbase + 16 <= kv_limit) {
             // 16 fresh rows, all inside the horizon
             const long long boff = (((long long)(s0 + kbase - P)) * Hkv + g) * D * 2;
             pend_kb = uniform_u64(reinterpret_cast<const char*>(k_new) + boff);
@@ -209,7 +247,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
 #pragma unroll
             for (int c = 0; c < IPB; ++c) {
                 const int row16 = RPI * c + lane / CPR;
-                const int chunk = (lane % CPR) ^ swz<D>(row16);
+                const int chunk = (lane % CPR) ^ swz<D, KG>(row16);
                 const int kj = kbase + row16;
                 long long off;
                 if (kj < P) {
@@ -231,33 +269,38 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     typedef __attribute__((address_space(3))) char lds_char;
     lds_char* const lds0 = (lds_char*)smem;
     const int grp_off = grp * RING * STAGEB;  // folded into the per-lane offsets below
-    // K, A operand of S^T: row sub*32+l32, chunk 2*ks+hf
+    // K, A operand of S^T: row sub*BR+lrow, chunk KG*ks+kg
     int koff[KSTEPS];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
-        koff[ks] = grp_off + l32 * ROWB + (((2 * ks + hf) ^ swz<D>(l32)) << 4);
+        koff[ks] = grp_off + lrow * ROWB + (((KG * ks + kg) ^ swz<D, KG>(lrow)) << 4);
         asm volatile("" : "+v"(koff[ks]));  // keep it one register: address = this + immediate
     }
-    // V, A operand of O^T (transposing read): rows kk*16 + 8*h2 + 4*hf + (lane&15)/4 + {sub*32},
-    // 8 bytes at element dt*32 + 16*((lane>>4)&1) + 4*(lane&3)
-    int voff[2][DT];
+    // V, A operand of O^T (transposing reads): rows step*CK + h2*4*KG + 4*kg + (lane%16)/4, 8 bytes at element
+    // db*BR + (second 16 lanes of 32: 16) + 4*(lane%4).  Rows 16 apart are swizzled alike: one offset for both reads.
+    constexpr int NH = KG == 2 ? 2 : 1;
+    int voff[NH][DB];
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2)
+    for (int h2 = 0; h2 < NH; ++h2)
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            const int row = 8 * h2 + 4 * hf + ((lane & 15) >> 2);
-            const int elem = dt * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-            voff[h2][dt] = grp_off + row * ROWB + ((((elem >> 3)) ^ swz<D>(row)) << 4) + (elem & 7) * 2;
-            asm volatile("" : "+v"(voff[h2][dt]));
+        for (int db = 0; db < DB; ++db) {
+            const int row = h2 * 4 * KG + 4 * kg + ((lane & 15) >> 2);
+            const int elem = db * BR + (lane % BR / 16) * 16 + 4 * (lane & 3);
+            voff[h2][db] = grp_off + row * ROWB + (((elem >> 3) ^ swz<D, KG>(row)) << 4) + (elem & 7) * 2;
+            asm volatile("" : "+v"(voff[h2][db]));
         }
 
-    f32x16 oacc[DT];
+    accv oacc[DB][RB];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-    float m_run = -INFINITY;  // reference exponent of O and l (log2 domain): a lane's probabilities of a tile sum to at most 2^8
-    float l_run = 0.f;        // this lane's partial of the running sum (other half in lane^32)
+        for (int rb = 0; rb < RB; ++rb) oacc[db][rb] = accv(0.f);
+    float m_run[RB], l_run[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        m_run[rb] = -INFINITY;  // reference exponent of O and l (log2 domain): a lane's probabilities of a tile sum to at most 2^8
+        l_run[rb] = 0.f;        // this lane's partial of the running sum
+    }
     const float c = a.scale_log2e;
 
     // one step with the ring slot as a compile-time constant
@@ -277,48 +320,69 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
         lds_char* const vst = kst + PLANEB;
 
         // S^T = K Q^T
-        f32x16 sacc[NSUB];
+        accv sacc[NSUB][RB];
 #pragma unroll
         for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sacc[sub][i] = 0.f;
-        // K operands are read two k-steps ahead of the MFMAs that consume them (LDS latency is
-        // about four MFMAs long)
-        bf16x8 kbuf[3][NSUB];
+            for (int rb = 0; rb < RB; ++rb) sacc[sub][rb] = accv(0.f);
+        // Two K operands at a time, read two such groups ahead (a group is 64 cycles of products, about half the LDS latency).
+        constexpr int GROUPS = KSTEPS * NSUB / 2;
+        bf16x8 kbuf[3][2];
+        auto read_k = [&](auto g_c) {
+            constexpr int GI = decltype(g_c)::value;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+            for (int x = 0; x < 2; ++x)
+                kbuf[GI % 3][x] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(kst + (2 * GI + x) % NSUB * BR * ROWB + koff[(2 * GI + x) / NSUB]);
+        };
+        read_k(std::integral_constant<int, 0>{});
+        read_k(std::integral_constant<int, 1>{});
+        static_for<GROUPS>([&](auto g_c) {
+            constexpr int GI = decltype(g_c)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (GI + 2 < GROUPS) read_k(std::integral_constant<int, GI + 2>{});
 #pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
-                kbuf[ks][sub] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(kst + sub * 32 * ROWB + koff[ks]);
-        static_for<KSTEPS>([&](auto ks_c) {
-            constexpr int ks = decltype(ks_c)::value;
-            if constexpr (ks + 2 < KSTEPS) {
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                for (int sub = 0; sub < NSUB; ++sub)
-                    kbuf[(ks + 2) % 3][sub] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(kst + sub * 32 * ROWB + koff[ks + 2]);
-            }
-#pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
-                sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kbuf[ks % 3][sub], qreg[ks], sacc[sub], 0, 0, 0);
-            // Two copy instructions behind every other k-step: 8 waves of a CU that issue theirs in one burst after the
-            // barrier queue for the address unit (all behind the first four k-steps: 16 x (256-4096 + 64-768) tokens, 32/8
+                for (int rb = 0; rb < RB; ++rb) {
+                    accv& s = sacc[(2 * GI + x) % NSUB][rb];
+                    s = product(kbuf[GI % 3][x], qreg[rb][(2 * GI + x) / NSUB], s);
+                }
+            // Two copy instructions behind every other group: 8 waves of a CU that issue theirs in one burst after the
+            // barrier queue for the address unit (all behind the first half: 16 x (256-4096 + 64-768) tokens, 32/8
             // heads 300 us against 296, 12 x (1000-2000 + 60-200) 77.6 against 75.8).
-            if constexpr (ks % 2 == 0) {
-                if (pend) emit(std::integral_constant<int, ks / 2>{});
+            if constexpr (GI % 2 == 0) {
+                if (pend) emit(std::integral_constant<int, GI / 2>{});
             }
         });
+        bf16x8 vbuf[3][2];
+        auto read_v = [&](auto g_c) {
+            constexpr int GI = decltype(g_c)::value;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                constexpr int STEP = 2 * GI / DB;
+                const int db = (2 * GI + x) % DB;
+                lds_char* const vb = vst + STEP * CK * ROWB;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vb + voff[0][db]));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vb + (NH - 1 ? 0 : 4 * KG * ROWB) + voff[NH - 1][db]));
+                vbuf[GI % 3][x] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo), __builtin_bit_cast(bf16x4, hi), 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+        };
+        read_v(std::integral_constant<int, 0>{});
+        read_v(std::integral_constant<int, 1>{});
         pend = 0;
         // causal frontier / end of sequence: only tiles that reach past the first row's horizon
-        if (base + NSUB * 32 > wave_vis_min) {
+        if (base + TN > wave_vis_min) {
 #pragma unroll
             for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int kidx = base + sub * 32 + (i >> 2) * 8 + hf * 4 + (i & 3);
-                    if (kidx >= my_vis) sacc[sub][i] = -INFINITY;
+                for (int i = 0; i < NE; ++i) {
+                    const int kidx = base + sub * BR + (i >> 2) * (4 * KG) + kg * 4 + (i & 3);
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+                        if (kidx >= my_vis[rb]) sacc[sub][rb][i] = -INFINITY;
                 }
         }
-        // Online softmax, one row per lane pair (lane, lane ^ 32), without a maximum: the probabilities are taken against
+        // Online softmax, one row per KG lanes, without a maximum: the probabilities are taken against
         // the row's reference exponent as it stands, and only where a lane's sum of them says that a score may be 2^8 above
         // it (or that the row has no reference yet: 2^inf, or NaN where every key is masked) is the maximum looked up, the
         // reference raised and O, l rescaled.  Against a maximum per tile this takes 22 vector instructions and the trip
@@ -328,62 +392,68 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
         // on the first of these, 9 % less on batches with one item per CU.
         // The row sum is taken over the bf16-rounded probabilities, the same weights the PV product uses, so that the
         // rounding of P cancels between numerator and denominator.
-        bf16x8 pb[NSUB][2];
-        float psum;
-        auto weigh = [&](float m_sub) {
-            psum = 0.f;
+        bf16x8 pb[RB][PSTEPS];  // the scores' order of keys, which the V reads follow
+        float psum[RB];
+        auto weigh = [&](int rb, float m_sub) {
+            psum[rb] = 0.f;
 #pragma unroll
             for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-                for (int i = 0; i < 16; i += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(sacc[sub][i] * c - m_sub);
-                    const float p1 = __builtin_amdgcn_exp2f(sacc[sub][i + 1] * c - m_sub);
+                for (int i = 0; i < NE; i += 2) {
+                    const int e = sub * NE + i;
+                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[sub][rb][i], c, -m_sub));
+                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[sub][rb][i + 1], c, -m_sub));
                     const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                    psum = __builtin_amdgcn_fdot2_f32_bf16(pp, kOnes2, psum, false);
-                    pb[sub][i >> 3][i & 7] = pp[0];
-                    pb[sub][i >> 3][(i & 7) + 1] = pp[1];
+                    psum[rb] = __builtin_amdgcn_fdot2_f32_bf16(pp, kOnes2, psum[rb], false);
+                    pb[rb][e >> 3][e & 7] = pp[0];
+                    pb[rb][e >> 3][(e & 7) + 1] = pp[1];
                 }
         };
         bool raise_any = step == 0;  // there the rows have no reference yet, as a rule
         if (!raise_any) {
-            weigh(m_run);
-            raise_any = __builtin_amdgcn_ballot_w64(!(psum <= kRaiseSum)) != 0;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) weigh(rb, m_run[rb]);
+            raise_any = __builtin_amdgcn_ballot_w64(!(psum[0] <= kRaiseSum) || !(psum[RB - 1] <= kRaiseSum)) != 0;
         }
         if (raise_any) {
-            float mx = sacc[0][0];
 #pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
+            for (int rb = 0; rb < RB; ++rb) {
+                float mx = sacc[0][rb][0];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[sub][i]);
-            mx = fmaxf(mx, other_half(mx)) * c;
-            const bool raise = mx > m_run;
-            const float alpha = raise ? __builtin_amdgcn_exp2f(m_run - mx) : 1.f;  // 0 where the row has no reference yet
-            m_run = raise ? mx : m_run;
-            l_run *= alpha;
+                for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+                    for (int i = 0; i < NE; ++i) mx = fmaxf(mx, sacc[sub][rb][i]);
+                mx = fmaxf(mx, other_half(mx));
+                if (KG == 4) mx = fmaxf(mx, other_quarter(mx));
+                mx *= c;
+                const bool raise = mx > m_run[rb];
+                const float alpha = raise ? __builtin_amdgcn_exp2f(m_run[rb] - mx) : 1.f;  // 0 where the row has no reference yet
+                m_run[rb] = raise ? mx : m_run[rb];
+                l_run[rb] *= alpha;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-            weigh(m_run == -INFINITY ? 0.f : m_run);  // still no visible key: exp2(-inf - 0) = 0
-        }
-        l_run += psum;
-
-        // O^T += V^T P^T ; V rows fetched with the transposing LDS read
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                lds_char* const vb = vst + (sub * 32 + kk * 16) * ROWB;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vb + voff[0][dt]));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vb + voff[1][dt]));
-                    const bf16x4 lo_b = __builtin_bit_cast(bf16x4, lo);
-                    const bf16x4 hi_b = __builtin_bit_cast(bf16x4, hi);
-                    const bf16x8 va = __builtin_shufflevector(lo_b, hi_b, 0, 1, 2, 3, 4, 5, 6, 7);
-                    oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[sub][kk], oacc[dt], 0, 0, 0);
-                }
+                    for (int i = 0; i < NE; ++i) oacc[db][rb][i] *= alpha;
+                weigh(rb, m_run[rb] == -INFINITY ? 0.f : m_run[rb]);  // still no visible key: exp2(-inf - 0) = 0
             }
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) l_run[rb] += psum[rb];
+
+        // O^T += V^T P^T, two column blocks at a time over CK keys, so that a product waits for none of those just before it
+        constexpr int VGROUPS = PSTEPS * DB / 2;
+        static_for<VGROUPS>([&](auto g_c) {
+            constexpr int GI = decltype(g_c)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (GI + 2 < VGROUPS) read_v(std::integral_constant<int, GI + 2>{});
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    accv& o = oacc[(2 * GI + x) % DB][rb];
+                    o = product(vbuf[GI % 3][x], pb[rb][2 * GI / DB], o);
+                }
+        });
     };
 
     if (!SPLIT || nsteps > 0) {
@@ -436,41 +506,45 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     }
 
     // ---- merge the wave groups through LDS (the DMA ring is idle now)
-    constexpr int WSTRIDE = (DT * 16 + 4) * 64;  // floats per wave in the merge area: [DT*4 + 1 chunks][64 lanes][4]
+    constexpr int OC = NE / 4;  // 16-byte chunks of an accumulator
+    constexpr int WSTRIDE = (DB * RB * OC * 4 + 4) * 64;  // floats per wave in the merge area: [DB*RB*OC + 1 chunks][64 lanes][4]
+    auto ochunk = [&](int db, int rb, int i4) { return f32x4{oacc[db][rb][i4 * 4], oacc[db][rb][i4 * 4 + 1], oacc[db][rb][i4 * 4 + 2], oacc[db][rb][i4 * 4 + 3]}; };
     if (NG > 1) {
         typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
         lds_f32x4* const xw = reinterpret_cast<lds_f32x4*>(lds0 + wq * (WSTRIDE * 4)) + lane;
         block_barrier();
         if (grp == 1) {
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 v = {oacc[dt][i4 * 4], oacc[dt][i4 * 4 + 1], oacc[dt][i4 * 4 + 2], oacc[dt][i4 * 4 + 3]};
-                    xw[(dt * 4 + i4) * 64] = v;
-                }
-            const f32x4 ml = {m_run, l_run, 0.f, 0.f};
-            xw[DT * 4 * 64] = ml;
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int i4 = 0; i4 < OC; ++i4) xw[((db * RB + rb) * OC + i4) * 64] = ochunk(db, rb, i4);
+            const f32x4 ml = {m_run[0], l_run[0], m_run[RB - 1], l_run[RB - 1]};
+            xw[DB * RB * OC * 64] = ml;
         }
         block_barrier();
         if (grp == 1) return;
         if (wave_active) {
-            const f32x4 ml = xw[DT * 4 * 64];
-            const float m1 = ml[0], l1 = ml[1];
-            // a group may have seen no visible key of a row: weight 0 (which lets NaN through)
-            const float m = fmaxf(m_run, m1);
-            const float s0f = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m);
-            const float s1f = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
-            m_run = m;
-            l_run = l_run * s0f + l1 * s1f;
+            const f32x4 ml = xw[DB * RB * OC * 64];
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+            for (int rb = 0; rb < RB; ++rb) {
+                const float m1 = ml[2 * rb], l1 = ml[2 * rb + 1];
+                // a group may have seen no visible key of a row: weight 0 (which lets NaN through)
+                const float m = fmaxf(m_run[rb], m1);
+                const float s0f = m_run[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[rb] - m);
+                const float s1f = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - m);
+                m_run[rb] = m;
+                l_run[rb] = l_run[rb] * s0f + l1 * s1f;
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 v = xw[(dt * 4 + i4) * 64];
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) oacc[dt][i4 * 4 + e] = oacc[dt][i4 * 4 + e] * s0f + v[e] * s1f;
-                }
+                    for (int i4 = 0; i4 < OC; ++i4) {
+                        const f32x4 v = xw[((db * RB + rb) * OC + i4) * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) oacc[db][rb][i4 * 4 + e] = oacc[db][rb][i4 * 4 + e] * s0f + v[e] * s1f;
+                    }
+            }
         }
     } else {
         block_barrier();  // every wave is done with the ring: its memory is reused below
@@ -484,22 +558,30 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     constexpr int OROWB = ROWB + 16;
     static_assert(32 * OROWB <= WSTRIDE * 4, "output patch fits the merge area");
     lds_char* const patch = lds0 + wq * (NG > 1 ? WSTRIDE * 4 : 32 * OROWB);
-    const float l_tot = l_run + other_half(l_run);
+    float l_tot[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        l_tot[rb] = l_run[rb] + other_half(l_run[rb]);
+        if (KG == 4) l_tot[rb] += other_quarter(l_tot[rb]);
+    }
     if (SPLIT) {
         // one of S copies: O (unnormalised, fp32), max and sum of every row go to the workspace, [TM][D] floats of O, then
         // [TM][2] floats (max, sum).  Same turn through LDS as below, in two passes of D/2 floats per row.
         float* const part = static_cast<float*>(a.partial) + ((long long)(wk.part_base + entry) * Hkv + g) * (TM * (D + 2));
-        if (hf == 0) *reinterpret_cast<float2*>(part + TM * D + (wq * 32 + l32) * 2) = float2{m_run, l_tot};
+        if (kg < RB) {
+            const float2 ml = {kg ? m_run[RB - 1] : m_run[0], kg ? l_tot[RB - 1] : l_tot[0]};
+            *reinterpret_cast<float2*>(part + TM * D + (wq * 32 + kg * BR + lrow) * 2) = ml;
+        }
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-            for (int dtl = 0; dtl < DT / 2; ++dtl)
+            for (int dbl = 0; dbl < DB / 2; ++dbl)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const int dt = pass * (DT / 2) + dtl;
-                    const f32x4 v = {oacc[dt][i4 * 4], oacc[dt][i4 * 4 + 1], oacc[dt][i4 * 4 + 2], oacc[dt][i4 * 4 + 3]};
-                    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + l32 * OROWB + (dtl * 32 + i4 * 8 + hf * 4) * 4) = v;
-                }
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int i4 = 0; i4 < OC; ++i4)
+                        *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + (rb * BR + lrow) * OROWB + (dbl * BR + i4 * 4 * KG + kg * 4) * 4) =
+                            ochunk(pass * (DB / 2) + dbl, rb, i4);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int p = 0; p < 32 / RPI; ++p) {
@@ -511,16 +593,19 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
         }
         return;
     }
-    const float inv = 1.f / l_tot;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int rb = 0; rb < RB; ++rb) {
+        const float inv = 1.f / l_tot[rb];
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-            bf16x4 o4;
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[dt][i4 * 4 + e] * inv);
-            *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(patch + l32 * OROWB + (dt * 32 + i4 * 8 + hf * 4) * 2) = o4;
-        }
+            for (int i4 = 0; i4 < OC; ++i4) {
+                bf16x4 o4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[db][rb][i4 * 4 + e] * inv);
+                *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(patch + (rb * BR + lrow) * OROWB + (db * BR + i4 * 4 * KG + kg * 4) * 2) = o4;
+            }
+    }
     // lanes now read what other lanes of the same wave wrote: LDS operations of a wave complete in order
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __bf16* const outp = static_cast<__bf16*>(a.out);

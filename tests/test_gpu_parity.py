@@ -805,3 +805,18 @@ def test_fp32_split_products_keep_what_no_split_survives(H, h, d, n, what):
         ok = np.isfinite(want)
         scale = np.abs(np.where(ok, want, 0)).max(0) if what == "tiny_column" else np.abs(np.where(ok, want, 0)).max()
         assert np.all(np.abs(np.where(ok, got[t], 0) - np.where(ok, want, 0)) <= 1e-4 * scale), t  # the bound of test_small_cases, where |V| is 1
+
+
+@pytest.mark.parametrize("d,variant,splits", [(128, 0, 0), (128, 1, 0), (128, 0, 3), (64, 0, 0), (64, 1, 0), (64, 0, 3)])
+def test_cached_steps_end_at_every_block_of_a_tile(H, force_plan, d, variant, splits):
+    """128-row items: the prefix ends before, at and behind each of the four 16-token blocks of a 64-key tile (one wave copies
+    each), in the first tile and behind more tiles than one window of block ids holds; rows in blocks of 16 and 32."""
+    lens = [(p, 33 + p % 7) for p in (0, 15, 16, 17, 31, 32, 47, 48, 49, 63, 64, 65, 127, 4223, 4224, 4240, 8300)]
+    w = W.make_small("bf16", 8, 2, d, lens, seed=9000 + d, q_gain=2.0)
+    force_plan(variant, splits)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, 8)[0] == 128
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
