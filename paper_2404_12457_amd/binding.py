@@ -49,6 +49,11 @@ class RagcError(RuntimeError):
 
 _lib = None
 
+try:
+    from . import _calls  # ragc_prefill_attn and ragc_kv_append without ctypes
+except ImportError:
+    _calls = None
+
 
 def load() -> ctypes.CDLL:
     global _lib
@@ -56,6 +61,8 @@ def load() -> ctypes.CDLL:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2404_12457_amd.build` "
                                "(the HIP library is the only implementation; there is no fallback)")
+        if _calls is None:
+            raise RuntimeError("_calls.so is missing: build it with `python -m paper_2404_12457_amd.build`")
         lib = ctypes.CDLL(LIB_PATH)
         P, I32, I64, U32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32
         lib.ragc_version.restype = ctypes.c_int
@@ -81,6 +88,7 @@ def load() -> ctypes.CDLL:
         lib.ragc_kv_gather.restype = ctypes.c_int
         lib.ragc_kv_gather.argtypes = [P, P, I32, I32, P, P, P]
         _lib = lib
+        _calls.bind(lib, ctypes.cast(lib.ragc_prefill_attn, P).value, ctypes.cast(lib.ragc_kv_append, P).value)
     return _lib
 
 
@@ -176,3 +184,9 @@ def ragc_kv_swap(pool, host_k, host_v, host_block_stride_elems: int, num_host_sl
 
 def ragc_kv_gather(pool, batch, req: int, length: int, k_out, v_out, stream: int = 0) -> int:
     return _check(load().ragc_kv_gather(_ref(pool), _ref(batch), req, length, _ptr(k_out), _ptr(v_out), stream or None))
+
+
+_ctypes_calls = ragc_prefill_attn, ragc_kv_append  # what _calls turns to for anything but plain arguments
+if _calls is not None:
+    _calls.setup(globals(), ragc_kv_pool, ragc_batch, _check, ragc_prefill_attn, ragc_kv_append)
+    ragc_prefill_attn, ragc_kv_append = _calls.ragc_prefill_attn, _calls.ragc_kv_append

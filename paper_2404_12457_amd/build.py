@@ -1,5 +1,5 @@
 """Build libragc.so (the C-ABI library) and libragc_calib.so (the benchmark's calibration
-kernels) for gfx950 with hipcc, in-tree.
+kernels) for gfx950 with hipcc, and _calls.so (argument marshalling for Python), in-tree.
 
     python -m paper_2404_12457_amd.build
 
@@ -11,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -18,6 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libragc.so")
 CALIB_LIB = os.path.join(HERE, "libragc_calib.so")
+CALLS = os.path.join(HERE, "_calls.so")  # CPython extension, host code only
 SOURCES = ["ragc_api.cpp", "ragc_ctl.cpp", "kv_ops.hip", "attn_f32.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
@@ -46,6 +48,8 @@ def build(extra_flags=(), verbose: bool = False) -> str:
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES + ["calib.hip"]))
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs[:-1]], check=True)
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", CALIB_LIB, objs[-1]], check=True)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS], check=True)
     if verbose:
         print("built", LIB, "and", CALIB_LIB)
     return LIB

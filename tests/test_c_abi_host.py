@@ -298,3 +298,48 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
 ])
 def test_fp32_plan_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
     assert _plan(p, n, hq, hkv, d, dtype=B.RAGC_DTYPE_F32) == want
+
+
+def _outcome(f, *args, **kwargs):
+    try:
+        return f(*args, **kwargs)
+    except Exception as e:
+        return type(e), str(e)
+
+
+@pytest.mark.parametrize("args,kwargs", [
+    (("pool", "empty", A, A, A, A, 8, 0.125), {}),
+    (("pool", "empty", A, A, A, A, 8), dict(softmax_scale=0.125, stream=0, flags=1, workspace=None, workspace_bytes=0)),
+    (("pool", "batch", A, A, A, A + 1, 8, 0.125), {}),                       # misaligned
+    (("pool", "batch", A, A, A, A, 9, 0.125), {}),                           # heads
+    (("pool", "batch", None, A, A, A, 8, 0.125), {}),
+    ((None, "batch", A, A, A, A, 8, 0.125), {}),
+    (("pool", None, A, A, A, A, 8, 0.125), {}),
+    (("pool", "batch", A, A, A, A, 8, float("nan")), {}),
+    (("pool", "batch", A, A, A, A, 8, 0.125, 1 << 31), {}),                  # unknown flag
+    (("pool", "batch", np.zeros(3), A, A, A, np.int64(9), 1), {}),           # an array, a numpy number, a whole scale
+    (("batch", "pool", A, A, A, A, 8, 0.125), dict(bad=1)),
+    (("pool", "batch", A, A, A, A, 8.0, 0.125), {}),                         # no whole number
+    (("pool", "batch", A, A, A, A, 8, "x"), {}),
+    (("pool", "batch", "q", A, A, A, 8, 0.125), {}),
+    ((b"pool", "batch", A, A, A, A, 8, 0.125), {}),
+    (("pool", "batch", A, A, A, A), {}),
+    (("pool", "batch", A, A, A, A, 8, 0.125, 0, None, 0, 0, 0), {}),
+    (("pool", "batch", A, A, A, A, 8, 0.125), dict(pool=1)),
+    (("pool", "batch", A, A, A, A, 1 << 40, 0.125), dict(workspace_bytes=-1)),
+])
+def test_calls_marshalled_in_c_behave_as_through_ctypes(lib, args, kwargs):
+    empty, k0 = _batch(p=(), n=(), stride=1)
+    batch, k1 = _batch()
+    named = {"pool": _pool(), "empty": empty, "batch": batch}
+    args = [named.get(a, a) if isinstance(a, str) else a for a in args]
+    assert _outcome(B.ragc_prefill_attn, *args, **kwargs) == _outcome(B._ctypes_calls[0], *args, **kwargs)
+
+
+def test_append_marshalled_in_c_behaves_as_through_ctypes(lib):
+    empty, k0 = _batch(p=(), n=(), stride=1)
+    batch, k1 = _batch()
+    for args, kwargs in [((_pool(), empty, A, A), {}), ((_pool(), empty, A), dict(v_new=A, stream=0)), ((_pool(), batch, A + 1, A), {}),
+                         ((_pool(), batch, None, A), {}), ((None, batch, A, A), {}), ((_pool(), A), {}), ((_pool(), batch, A, A, 1.5), {}),
+                         ((_pool(), batch, A, A), dict(flags=1))]:
+        assert _outcome(B.ragc_kv_append, *args, **kwargs) == _outcome(B._ctypes_calls[1], *args, **kwargs)
