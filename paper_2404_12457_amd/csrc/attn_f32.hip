@@ -16,8 +16,10 @@
 // attn_f32_kernel, 16 rows: fp32 matrix cores (plain_rows), 64 flop per cycle and SIMD (157 TFLOP/s
 // on the chip).  A 16-key tile at head_dim 128 is 64 products, 2048 cycles, and the loop runs at 0.8
 // of that with two waves per SIMD; the rest of a small call is the 5 us before the first tile and
-// after the last.  One request of 256 + 32 tokens, 4 heads of 64: 7.3 us (27 with plain FMAs from
-// shared tiles).  Tried: K read from global memory in operand order instead of through LDS costs a
+// after the last.  So Q, which each wave would wait for by itself, comes through LDS once per
+// workgroup, behind the block ids and ahead of the first tile's copies: one request of 256 + 32
+// tokens, 4 heads of 64: 7.8 -> 7.15 us (27 with plain FMAs from shared tiles); 7 of 2-4 new tokens,
+// 16 heads of 64: 7.9 -> 6.65.  Tried: K read from global memory in operand order instead of through LDS costs a
 // cache access per lane (41 on average per load instruction, 2600 cycles per tile and CU); K staged
 // through registers and three waves per SIMD: both 5-10 % slower.
 //
@@ -54,7 +56,7 @@ constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};  // the pa
 //                              accumulator of S^T as it stands (lane: row l16, keys 4 kg + i)
 template <int D, int NW>
 __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& it, int g, int tile, bool append, char* smem,
-                                           float (*Ms)[16], float (*Ls)[16]) {
+                                           char* qs, float (*Ms)[16], float (*Ls)[16]) {
     constexpr int TR = 16;                 // rows
     constexpr int KJ = D / 16;             // 16-byte reads of a K row per lane
     constexpr int VC = D / 64;             // 16-byte reads of a V row per lane
@@ -86,28 +88,23 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
     const int kv_limit = P + tok0 + div_g(h0 + rows_here - 1) + 1;  // keys [0, kv_limit) are visible to some row
     const int ntiles = (kv_limit + KT - 1) / KT;
     const int nsteps = ntiles > w ? (ntiles - w + NW - 1) / NW : 0;  // this wave takes tiles w, w + NW, ...
-    const int my_row = h0 + min(l16, rows_here - 1);  // rows past the end repeat the last one and are not stored
-    const int my_tok = tok0 + div_g(my_row);
-    const int my_head = g * G + my_row - div_g(my_row) * G;
-    const int my_vis = P + my_tok + 1;
+    const int my_vis = P + tok0 + div_g(h0 + min(l16, rows_here - 1)) + 1;  // rows past the end repeat the last one and are not stored
     const int vis_min = P + tok0 + 1;  // tiles below need no mask
 
-    // block ids of this wave's tiles, 64 steps at a time, one per lane
-    int blk_base = 0;
-    int blk_vec = nsteps > 0 ? table[min(w + lane * NW, ntiles - 1)] : 0;
-
-    f32x4 qreg[KJ];
+    // block ids of this wave's tiles, 64 steps at a time, one per lane; and Q, which every wave needs, copied to LDS once and
+    // shared (swizzled as K is): the first copies wait for neither
+    int blk_base = 0, blk_vec;
     {
-        const float* qp = q + ((long long)(s0 + my_tok) * a.q_heads + my_head) * D + kg * 4;
+        constexpr int QI = TR / RPI, NQ = QI > NW ? QI / NW : 1;  // with fewer pieces than waves some bring the same one
+        const void* src[NQ];
 #pragma unroll
-        for (int j = 0; j < KJ; ++j) qreg[j] = *reinterpret_cast<const f32x4*>(qp + j * 16);
+        for (int x = 0; x < NQ; ++x) {
+            const int r = RPI * ((w + x * NW) % QI) + lane / CPR, row = h0 + min(r, rows_here - 1), tok = div_g(row);
+            src[x] = q + ((long long)(s0 + tok0 + tok) * a.q_heads + g * G + (row - tok * G)) * D + ((lane % CPR) ^ r) * 4;
+        }
+        blk_vec = load_ahead_of_copies<NQ>(table + min(w + lane * NW, ntiles - 1), src,
+                                           (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)qs + w % QI * 1024, NW * 1024);
     }
-
-    // every ordinary load has completed before the copies start to be counted
-    asm volatile("" ::"v"(blk_vec));
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) asm volatile("" ::"v"(qreg[j]));
-    wait_vmcnt<0>();
 
     // Copies: lane i of instruction n brings row RPI n + i / CPR of the tile.  K rows are stored with their chunk
     // index XORed with the row (on the global side), so that the 16 keys of an operand read hit different banks.
@@ -150,10 +147,22 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
             }
         }
     };
+    if (nsteps > 0) {
+        copy_tile(0, true);
+        copy_tile(0, false);
+        wait_vmcnt<2 * NI>();  // this wave's part of Q
+    } else {
+        wait_vmcnt<0>();
+    }
     int koff[KJ];  // this lane's K reads
 #pragma unroll
     for (int j = 0; j < KJ; ++j) koff[j] = l16 * ROWB + (((4 * j + kg) ^ l16) << 4);
     const int voff = kg * 4 * ROWB + l16 * 16;
+
+    block_barrier();  // every wave's part of Q has landed
+    f32x4 qreg[KJ];
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) qreg[j] = *reinterpret_cast<lds_f32x4*>((lds_char*)qs + koff[j]);
 
     f32x4 oacc[VC][4];
 #pragma unroll
@@ -247,8 +256,6 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
         if (MORE) copy_tile(step + 1, false);
     };
     if (nsteps > 0) {
-        copy_tile(0, true);
-        copy_tile(0, false);
         for (int step = 0; step + 1 < nsteps; ++step) do_tile(step, std::true_type{});
         do_tile(nsteps - 1, std::false_type{});
     }
@@ -311,14 +318,14 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
 
 template <int D, int NW, class Work>
 __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work wk) {
-    __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * KT * D * 4];
+    __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * KT * D * 4], qs[16 * D * 4];
     __shared__ float Ms[NW][16], Ls[NW][16];
     touch_args(a, wk);
     int g, entry;
     split_block_id(a, blockIdx.x, &g, &entry);
     entry += wk.entry0;
     const WorkItem it = find_item(wk, entry, a.group, 16);
-    plain_rows<D, NW>(a, it, g, it.tile, true, smem, Ms, Ls);
+    plain_rows<D, NW>(a, it, g, it.tile, true, smem, qs, Ms, Ls);
 }
 
 // ---- the split products
@@ -673,11 +680,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
     if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) *again = 1;
     block_barrier();
     if (*reinterpret_cast<volatile int*>(again) != 0) {
-        float(*const Ms)[16] = reinterpret_cast<float(*)[16]>(qs);
+        float(*const Ms)[16] = reinterpret_cast<float(*)[16]>(qs + 16 * ROWB);  // behind 16 rows of Q
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {
             __syncthreads();
-            if (2LL * it.tile * 16 + half * 16 < (long long)N * G) plain_rows<D, NW>(a, it, g, 2 * it.tile + half, false, smem, Ms, Ms + NW);
+            if (2LL * it.tile * 16 + half * 16 < (long long)N * G) plain_rows<D, NW>(a, it, g, 2 * it.tile + half, false, smem, qs, Ms, Ms + NW);
         }
         return;
     }
