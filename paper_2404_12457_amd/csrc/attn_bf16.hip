@@ -38,14 +38,18 @@
 // What bounds it, and which product.  With every CU busy the power limit holds the clock at 1.5 to
 // 2.1 GHz, and then a product's energy counts more than its cycles: on random operands a loop of
 // v_mfma_f32_16x16x32_bf16 sustains 1852 TFLOP/s at 2.07 GHz where 32x32x16, which moves the
-// accumulators through the registers twice as often per flop, sustains 1640 at 1.77.  At head_dim 128
-// the kernel uses 16x16x32 (KG = 4: two blocks of 16 rows per wave, a row in four lanes): 4 x (4096 +
-// 128) tokens of 64/8 heads 69.9 -> 66.3 us, 16 x (256-4096 + 64-768) of 32/8 302 -> 286, four whole
-// prompts of 2200-3500 252 -> 244.  Per cycle it is the slower one (16.5-17 instead of 16 in a loop),
-// and at head_dim 64, where a step has half the products for the same softmax and its launches mostly
-// run at 2.1 GHz and above, 32x32x16 (KG = 2: one block of 32 rows, a row in two lanes) stays ahead:
-// 320 items of 450-1900 keys 21.5 us against 22.7; only with the chip full of long items it is not
-// (2048 of 4224 keys: 81 us against 78).
+// accumulators through the registers twice as often per flop, sustains 1640 at 1.77.  Per cycle it is
+// the slower one (16.5-17 instead of 16 in a loop), which shows while a launch is too short or too
+// small for the limit to take hold.  So at head_dim 128 launches of three items per CU and more, or
+// of 12000 keys (times 32 rows) per CU and more, 50 GFLOP in all, take 16x16x32 (KG = 4: two blocks
+// of 16 rows per wave, a row in four lanes): 4 x (4096 + 128) tokens of 64/8 heads 69.9 us with
+// 32x32x16, 66.3 with 16x16x32, 16 x (256-4096 + 64-768) of 32/8 302 and 286, four whole prompts of
+// 2200-3500 252 and 244; medians of 40 batches above the line 0.99.  Below it 32x32x16 (KG = 2: one
+// block of 32 rows, a row in two lanes) takes 0.98 of the time (medians of 38 batches): 64/8 heads,
+// 200-592 + 486 tokens 17.8 against 18.5, prompts of 181-545 tokens without a prefix 23.1 against 24.1.
+// At head_dim 64, where a step has half the products for the same softmax, 320 items of 450-1900 keys
+// take 21.5 us against 22.7, and only with the chip full of long items is it the other way round (2048
+// of 4224 keys: 81 us against 78).
 #include "attn_bf16_common.h"
 #include "attn_work.h"
 
@@ -65,12 +69,12 @@ __device__ __forceinline__ void static_for(const F& f) {
 __device__ __forceinline__ f32x16 product(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ f32x4 product(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
-template <int D, int NG, bool SPLIT, class Work>
+template <int D, int NG, int KG, bool SPLIT, class Work>
 __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
     static_assert(!SPLIT || NG == 1, "copies of an item are one wave group each");
     constexpr int RING = 2;             // stages per wave group
-    // Which product: v_mfma_f32_16x16x32_bf16 (KG = 4) or 32x32x16 (KG = 2); a lane is row lane % BR and group lane / BR
-    constexpr int KG = D == 128 ? 4 : 2;  // lanes per row, each with every KG-th run of four keys or columns
+    // Which product: v_mfma_f32_16x16x32_bf16 (KG = 4) or 32x32x16 (KG = 2).  A lane is row lane % BR and group lane / BR: KG
+    // lanes per row, each with every KG-th run of four keys or columns.
     constexpr int BR = 64 / KG;         // rows, keys and columns of a product
     constexpr int CK = 8 * KG;          // its contraction
     constexpr int NE = 16 / (KG * KG / 4);  // accumulators per lane
@@ -622,24 +626,31 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     }
 }
 
-template <int D, int NG, bool SPLIT, class Work>
+template <int D, int NG, int KG, bool SPLIT, class Work>
 void launch_one(const AttnLaunch& a, const Work& wk, int entries, hipStream_t s) {
     const dim3 grid((unsigned)entries * a.kv_heads), block(256 * NG);
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NG, SPLIT, Work>), grid, block, 0, s, a, wk);
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NG, KG, SPLIT, Work>), grid, block, 0, s, a, wk);
 }
 template <class Work>
-void launch_list(const AttnLaunch& a, const Work& wk, int entries, int variant, hipStream_t s) {
-    const bool d64 = a.head_dim == 64;
-    if (wk.splits > 1) d64 ? launch_one<64, 1, true>(a, wk, entries, s) : launch_one<128, 1, true>(a, wk, entries, s);
-    else if (variant == kAttnVariantTwoGroups) d64 ? launch_one<64, 2, false>(a, wk, entries, s) : launch_one<128, 2, false>(a, wk, entries, s);
-    else d64 ? launch_one<64, 1, false>(a, wk, entries, s) : launch_one<128, 1, false>(a, wk, entries, s);
+void launch_list(const AttnLaunch& a, const Work& wk, int entries, int variant, bool quarters, hipStream_t s) {
+    const bool two = variant == kAttnVariantTwoGroups;
+    if (a.head_dim == 64) {
+        if (wk.splits > 1) launch_one<64, 1, 2, true>(a, wk, entries, s);
+        else two ? launch_one<64, 2, 2, false>(a, wk, entries, s) : launch_one<64, 1, 2, false>(a, wk, entries, s);
+    } else if (wk.splits > 1) {
+        launch_one<128, 1, 2, true>(a, wk, entries, s);
+    } else if (quarters) {
+        two ? launch_one<128, 2, 4, false>(a, wk, entries, s) : launch_one<128, 1, 4, false>(a, wk, entries, s);
+    } else {
+        two ? launch_one<128, 2, 2, false>(a, wk, entries, s) : launch_one<128, 1, 2, false>(a, wk, entries, s);
+    }
 }
 
 }  // namespace
 
-hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, hipStream_t s) {
+hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, bool quarters, hipStream_t s) {
     if (entries <= 0) return hipSuccess;
-    wk.n_reqs <= kAttnReqStep ? launch_list(a, short_list(wk), entries, variant, s) : launch_list(a, wk, entries, variant, s);
+    wk.n_reqs <= kAttnReqStep ? launch_list(a, short_list(wk), entries, variant, quarters, s) : launch_list(a, wk, entries, variant, quarters, s);
     return hipGetLastError();
 }
 

@@ -237,6 +237,7 @@ struct Bf16Plan {
     int splits = 1;
     int waves = 8;                             // per workgroup of attn_bf16_rows_kernel
     int variant = ragc::kAttnVariantOneGroup;  // of attn_bf16_kernel
+    bool quarters = false;                     // of attn_bf16_kernel: 16x16x32 products
     int64_t workspace = 0;
 };
 
@@ -308,6 +309,9 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
     };
     const auto rows128 = [&](int64_t splits, int variant) {
         plan->variant = splits > 1 ? ragc::kAttnVariantOneGroup : variant;
+        // Launches that the power limit holds back take the product of less energy per flop, others the one of fewer cycles
+        // (attn_bf16.hip has both sides).
+        plan->quarters = d128 && splits == 1 && (wgs >= 3 * cus || sum_keys * pool->kv_heads >= 12000 * cus);
         return make(false, splits, items);
     };
     // Copies that give every CU a 128-row item with at least three 64-key tiles.  Those of 32-row items (below) never take
@@ -431,7 +435,7 @@ int run_list(const ragc::AttnLaunch& a, const HostMeta& h, const std::vector<int
 
 int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& plan, hipStream_t s) {
     return run_list(a, h, plan.order, plan.rows, plan.splits, [&](const ragc::AttnWork& wk, int entries) {
-        hipError_t e = plan.rows_kernel ? ragc::launch_attn_bf16_rows(a, wk, entries, plan.waves, s) : ragc::launch_attn_bf16(a, wk, entries, plan.variant, s);
+        hipError_t e = plan.rows_kernel ? ragc::launch_attn_bf16_rows(a, wk, entries, plan.waves, s) : ragc::launch_attn_bf16(a, wk, entries, plan.variant, plan.quarters, s);
         if (e == hipSuccess && wk.splits > 1) e = ragc::launch_attn_bf16_merge(a, wk, entries, plan.rows, s);
         return e;
     });

@@ -109,7 +109,8 @@ enum AttnVariant {
     kAttnVariantCount = 2
 };
 // entries: items times wk.splits, from wk.entry0 on; split items are kAttnVariantOneGroup
-hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, hipStream_t s);
+// quarters: at head_dim 128, items not split, take the 16x16x32 products (a row in four lanes) instead of 32x32x16
+hipError_t launch_attn_bf16(const AttnLaunch& a, const AttnWork& wk, int entries, int variant, bool quarters, hipStream_t s);
 // waves: 4 or 8 per workgroup; split items have 8
 hipError_t launch_attn_bf16_rows(const AttnLaunch& a, const AttnWork& wk, int entries, int waves, hipStream_t s);
 // second pass after a launch of split items of `rows` rows: combines the partial results into `out`

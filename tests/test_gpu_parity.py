@@ -820,3 +820,19 @@ def test_cached_steps_end_at_every_block_of_a_tile(H, force_plan, d, variant, sp
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
+
+
+@pytest.mark.parametrize("h,variant", [(48, 0), (48, 1), (44, 0), (44, 1)])
+def test_large_launches_of_head_dim_128(H, force_plan, h, variant):
+    """From three 128-row items per CU on (768 here) a row is in four lanes, below in two: 48 and 44 heads of 17 items, the
+    prefix ending around the 16-token blocks of a tile, new rows around the 16- and 32-row blocks of a wave."""
+    lens = [(p, n) for p, n in zip((0, 15, 16, 17, 31, 32, 47, 48, 49, 63, 64, 65, 127, 130, 0, 700, 4224),
+                                   (1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 96, 97, 128, 113, 100))]
+    w = W.make_small("bf16", h, h, 128, lens, seed=9100 + h, q_gain=2.0)
+    force_plan(variant, 0)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, h) == (128, 8 if variant else 4, 1)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
