@@ -186,8 +186,6 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             loff[c] = (row16 * row_stride + chunk * 8) * 2 - c * 1024;
         }
     };
-    set_loff(D);
-    bool loff_fresh = false;
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     // The copy of one step is prepared (addresses) right after the barrier and its DMA
     // instructions are then slipped between the MFMAs of S^T = K.Q^T, where their issue cost
@@ -214,6 +212,8 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
     const uint32_t copy_dst = smem_addr + grp * RING * STAGEB + wq * 16 * ROWB;
     const int pool_tiles = P >= wq * 16 + 16 ? (P - wq * 16 - 16) / TN + 1 - t_lo - grp : 0;
     const int pool_steps = pool_tiles > 0 ? (pool_tiles + NG - 1) / NG : 0;
+    bool loff_fresh = pool_steps <= 0;  // no copy of a whole pool block comes before the fresh ones
+    set_loff(loff_fresh ? Hkv * D : D);
     auto prepare = [&](int step) {
         if (step - blk_base >= 64) {
             blk_base = step;
