@@ -221,7 +221,8 @@ int64_t ragc_prefill_attn_workspace(const ragc_kv_pool* pool, const ragc_batch* 
  * where t = new_start[r]+i, kv head = h / (q_heads / kv_heads), K_j/V_j come from the
  * pool for j < prefix_len[r] and from k_new/v_new (row new_start[r]+j-prefix_len[r])
  * otherwise.  Softmax and accumulation are fp32; for bf16 the probabilities are
- * rounded to bf16 before the PV product and the output is rounded to nearest even.
+ * rounded to bf16 before the PV product and the output is rounded to nearest even; for fp32
+ * nothing is rounded to less, whatever the magnitudes, but a V below 2^-134 may count as 0.
  *   q, out        [device] [sum new_len][q_heads][head_dim]
  *   k_new, v_new  [device] [sum new_len][kv_heads][head_dim]
  *   workspace     [device] >= ragc_prefill_attn_workspace() bytes for the same flags, 256-byte

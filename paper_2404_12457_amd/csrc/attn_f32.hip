@@ -43,7 +43,8 @@ namespace {
 
 constexpr int KT = kBlock;     // keys per tile
 constexpr float kRaise = 8.f;  // log2 units a row's reference exponent may lag behind its maximum
-constexpr float kTinyOut = 0x1p-100f;  // below, third parts of V may have been denormal
+constexpr float kTiny = 0x1p-100f;  // of operands below 2^-110, parts are below the smallest bf16 number
+constexpr float kLift = 0x1p24f;    // of the probabilities, which are normal down to 2^-126: all three parts are then above it
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};  // the parts of the six products, smallest first
@@ -337,11 +338,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_f32_kernel(AttnLaunch a, Work
 //                              holds V[8 hf + j][64 u + 2 l32 + t] for accumulator 2 u + t
 // and a lane ends up with pairs of output columns of its row.
 //
-// Where an output is not finite, or tiny -- an infinity or NaN in K or V, or a number that rounds to
-// infinity, which no split survives, or magnitudes whose third parts would be denormal -- the
-// workgroup computes its rows again with fp32 products: as if it had never split.
+// What no split into bf16 numbers keeps is computed again by the workgroup, all its rows with fp32 products, as if it had never
+// split.  Products, sums and conversions keep denormals here (the exponential alone does not), so a part is lost only below the
+// smallest bf16 number, 2^-133: at most 2^-134 of an operand, and nothing above 2^-110.  It shows
+//   - by an output that is not finite: infinities and NaN, or K or V that round to infinity;
+//   - by an output below 2^-100: V as small, whose 2^-134 count there;
+//   - by Q: 2^-134 of K count in a score only where Q (times softmax_scale) is above 2^96, and Q itself loses below 2^-110.
+// Probabilities go down to 2^-126 next to any V, so they are lifted by 2^24 before their split, and their sums with them.  What
+// does not show is a V below 2^-134, of which nothing is left: it counts as 0.  An output of 0 says nothing, as it is what the
+// columns that pad a head give; to look through V for it doubled the time of such heads.
+// The looks at Q and at the outputs take 0.1 us of a workgroup, the lift half a percent of a long range: 30 requests of 16-34 + 35-71
+// tokens, 28/4 heads, 33.7 us against 33.3 without all of it, 2 of 3000 + 300, 32/8 heads, 226 against 225.
 
-// x = p[0] + p[1] + p[2] exactly (while the last part is above the denormals and x rounds to a finite bf16)
+// x = p[0] + p[1] + p[2] exactly (from 2^-110 on, while x rounds to a finite bf16)
 // x - (its bf16 part) is one product of two with a constant, for which no bf16 has to be widened first.  The constants are kept
 // out of the compiler's sight: it would encode {-1, 0} as the inline operand -1.0, which the hardware reads as {0, -1}.
 struct SplitBy {
@@ -363,6 +372,23 @@ __device__ __forceinline__ void split3(const SplitBy& by, const float* x, bf16x8
     }
 }
 
+// The least magnitude, and the sum of all (infinite or NaN where one is): both in the vector registers, as a flag per number
+// is a vector compare and a scalar or.  With flags the check of Q and of the outputs cost a short call a tenth of its time.
+struct Sizes {
+    float least = INFINITY, sum = 0.f;
+    __device__ __forceinline__ void add(const f32x4& x) {
+        least = fminf(fminf(least, fminf(fabsf(x[0]), fabsf(x[1]))), fminf(fabsf(x[2]), fabsf(x[3])));
+        sum += (fabsf(x[0]) + fabsf(x[1])) + (fabsf(x[2]) + fabsf(x[3]));
+    }
+};
+template <int N>
+__device__ __forceinline__ bool any_tiny(const f32x4* x) {
+    uint32_t least = UINT32_MAX;
+#pragma unroll
+    for (int i = 0; i < N * 4; ++i) least = min(least, __float_as_uint(fabsf(x[i / 4][i % 4])) - 1);  // 0 comes out largest
+    return least < __float_as_uint(kTiny) - 1;
+}
+
 template <int D, int NW, class Work>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kernel(AttnLaunch a, Work wk) {
     constexpr int TR = kAttnF32SplitRows;
@@ -379,7 +405,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
     char* const qs = smem + NW * 2 * PLANEB;
     float2(*const MLs)[TR] = reinterpret_cast<float2(*)[TR]>(qs);
     static_assert(NW * TR * 8 + 4 <= TR * ROWB, "states and the flag fit the Q rows");
-    int* const again = reinterpret_cast<int*>(qs + TR * ROWB - 4);
+    typedef volatile __attribute__((address_space(3))) int lds_flag;  // a generic pointer's accesses would wait for the copies
+    lds_flag* const flag = (lds_flag*)(qs + TR * ROWB - 4);
 
     touch_args(a, wk);
     const int Hkv = a.kv_heads;
@@ -502,8 +529,21 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
             read_k((lds_char*)qs + rb * 16 * ROWB, j, x);
             split3(by, x, qp[rb][j]);
         }
+    constexpr int OUT = TR * CPR / (64 * NW);  // chunks of Q, and of the output, per thread
+    const float sc = a.scale_log2e;
+    f32x4 qx[OUT];
+#pragma unroll
+    for (int u = 0; u < OUT; ++u) qx[u] = *reinterpret_cast<lds_f32x4*>((lds_char*)qs + (tid + u * 64 * NW) * 16);
     block_barrier();  // the Q rows have been read: their place in LDS is free
-    if (tid == 0) *again = 0;
+    if (tid == 0) *flag = 0;
+    bool odd;  // this wave has seen what the split does not keep
+    {
+        Sizes size;
+#pragma unroll
+        for (int u = 0; u < OUT; ++u) size.add(qx[u]);
+        odd = __builtin_amdgcn_ballot_w64(fmaxf(size.sum, 1.f) * sc > 0x1p96f) != 0;
+        if (__builtin_amdgcn_ballot_w64(size.least < kTiny) != 0) odd |= __builtin_amdgcn_ballot_w64(any_tiny<OUT>(qx)) != 0;
+    }
 
     f32x16 oacc[DT];
 #pragma unroll
@@ -511,7 +551,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
 #pragma unroll
         for (int i = 0; i < 16; ++i) oacc[t][i] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;  // l: this lane's keys only
-    const float sc = a.scale_log2e;
 
     auto do_tile = [&](int step, auto more_c) {
         constexpr bool MORE = decltype(more_c)::value;  // another tile follows
@@ -578,7 +617,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
         const float m_sub = m_run == -INFINITY ? 0.f : m_run;  // a row without a visible key yet: exp2(-inf - 0) = 0
         float p[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_sub);
+        for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_sub) * kLift;
         l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
         bf16x8 pp[3];
         split3(by, p, pp);
@@ -645,9 +684,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
         }
     __syncthreads();
     float* __restrict__ out = static_cast<float*>(a.out);
-    constexpr int OUT = TR * CPR / (64 * NW);  // chunks per thread
     f32x4 res[OUT];
-    bool odd = false;
+    Sizes size;
 #pragma unroll
     for (int u = 0; u < OUT; ++u) {
         const int r = (tid + u * 64 * NW) / CPR, c4 = tid % CPR;
@@ -668,18 +706,15 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 3 : 2) void attn_f32_split_kerne
             for (int e = 0; e < 4; ++e) o[e] += ox[e] * wgt;
         }
         const float inv = 1.f / l;
-        float most = 0.f, sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            res[u][e] = o[e] * inv;
-            most = fmaxf(most, fabsf(res[u][e]));
-            sum += fabsf(res[u][e]);
-        }
-        odd = odd || !(sum < INFINITY) || (most < kTinyOut && most > 0.f);
+        for (int e = 0; e < 4; ++e) res[u][e] = o[e] * inv;
+        size.add(res[u]);
     }
-    if (__builtin_amdgcn_ballot_w64(odd) != 0 && lane == 0) *again = 1;
+    odd |= __builtin_amdgcn_ballot_w64(!(size.sum < INFINITY)) != 0;
+    if (__builtin_amdgcn_ballot_w64(size.least < kTiny) != 0) odd |= __builtin_amdgcn_ballot_w64(any_tiny<OUT>(res)) != 0;
+    if (odd && lane == 0) *flag = 1;
     block_barrier();
-    if (*reinterpret_cast<volatile int*>(again) != 0) {
+    if (*flag != 0) {
         float(*const Ms)[16] = reinterpret_cast<float(*)[16]>(qs + 16 * ROWB);  // behind 16 rows of Q
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {

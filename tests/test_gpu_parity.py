@@ -807,6 +807,53 @@ def test_fp32_split_products_keep_what_no_split_survives(H, h, d, n, what):
         assert np.all(np.abs(np.where(ok, got[t], 0) - np.where(ok, want, 0)) <= 1e-4 * scale), t  # the bound of test_small_cases, where |V| is 1
 
 
+def _far_apart(what, w):
+    """q, k, v, scale of a batch without a prefix, whose operands are far from 1 while its scores and outputs are not."""
+    q, k, v = (np.array(x, np.float32) for x in (w.q, w.k_new, w.v_new))
+    scale = np.float32(w.softmax_scale)
+    f = np.float32
+    if what == "tiny_k": q, k = q * f(1e36), k * f(1e-36)
+    if what == "tinier_k": q, k = q * f(1e37), k * f(1e-37)
+    if what == "tiny_q": q, k = q * f(1e-36), k * f(1e36)
+    if what == "tiny_q_of_one_row": q[7, 1] *= f(1e-36); k[:8, 1] *= f(1e36)
+    if what == "tiny_products": q, k, scale = q * f(1e-18), k * f(1e-18), scale * f(1e36)
+    if what == "one_tiny_column": v[:, :, 9] *= f(1e-36)
+    if what == "one_denormal_column": v[:, :, 9] = np.sign(v[:, :, 9]) * f(1e-39)
+    if what == "first_row_denormal": v[0, :, 9] = f(1e-39)  # token 0 sees nothing else
+    if what == "zero_column": v[:, :, 9] = 0
+    if what == "far_v":  # token 50: probabilities of 2^-124, V of 2^127; the other scores are all about 0
+        q, k = q * f(0.05), k.copy()
+        q[:, :, 0], k[:, :, 0] = 10, 0
+        k[50, :, 0] = -86 / (10 * scale)
+        v[50] = np.sign(v[50]) * f(2e38)
+    if what == "least_column": v[:, :, 9] = np.sign(v[:, :, 9]) * f(2e-41)
+    return q, k, v, scale
+
+
+@pytest.mark.parametrize("h,d,n", [(32, 128, 165), (16, 64, 300)], ids=["d128", "d64"])
+@pytest.mark.parametrize("what", ["tiny_k", "tinier_k", "tiny_q", "tiny_q_of_one_row", "tiny_products", "one_tiny_column",
+                                  "one_denormal_column", "least_column", "first_row_denormal", "zero_column", "far_v"])
+def test_fp32_split_products_of_operands_far_from_one(H, h, d, n, what):
+    """Operands of which a split loses parts below the smallest normal float, or whose products are there: every column of
+    every head within the bound that fp32 has everywhere (1e-4), taken relative to the column's largest output."""
+    w = W.make_small("f32", h, h, d, [(0, n)], seed=8950, q_gain=2.0)
+    q, k, v, scale = _far_apart(what, w)
+    dw = H.DeviceWorkload(w)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, h)[0] == 32
+    for t, x in ((dw.q, q), (dw.k_new, k), (dw.v_new, v)):
+        t.copy_(torch.from_numpy(x).reshape(t.shape))
+    B.ragc_prefill_attn(dw.pool, dw.batch, dw.q, dw.k_new, dw.v_new, dw.out, h, float(scale), 0, None, 0,
+                        torch.cuda.current_stream().cuda_stream)
+    got = dw.out.double().cpu().numpy()
+    want = OA.prefill_attn(*(np.asarray(x, np.float64) for x in (q, k, v)), 0, float(scale))
+    err, size = np.abs(got - want).max(0), np.abs(want).max(0)
+    bound = 1e-4 * size
+    if what == "least_column": bound[:, 9] = 2.0**-134  # what counts as 0
+    assert np.all(err <= bound), float((err / np.maximum(size, 1e-300)).max())
+    if what != "least_column":
+        assert np.array_equal(got[0], v[0])  # the one token that token 0 sees
+
+
 @pytest.mark.parametrize("d,variant,splits", [(128, 0, 0), (128, 1, 0), (128, 0, 3), (64, 0, 0), (64, 1, 0), (64, 0, 3)])
 def test_cached_steps_end_at_every_block_of_a_tile(H, force_plan, d, variant, splits):
     """128-row items: the prefix ends before, at and behind each of the four 16-token blocks of a 64-key tile (one wave copies
