@@ -8,7 +8,9 @@ addresses.  Host id arrays are numpy int32 arrays.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Optional, Tuple
 
 import numpy as np
@@ -48,11 +50,7 @@ class RagcError(RuntimeError):
 
 
 _lib = None
-
-try:
-    from . import _calls  # ragc_prefill_attn and ragc_kv_append without ctypes
-except ImportError:
-    _calls = None
+_calls = None  # C extension: ragc_prefill_attn and ragc_kv_append without ctypes, see the end of this file
 
 
 def load() -> ctypes.CDLL:
@@ -61,8 +59,6 @@ def load() -> ctypes.CDLL:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2404_12457_amd.build` "
                                "(the HIP library is the only implementation; there is no fallback)")
-        if _calls is None:
-            raise RuntimeError("_calls.so is missing: build it with `python -m paper_2404_12457_amd.build`")
         lib = ctypes.CDLL(LIB_PATH)
         P, I32, I64, U32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32
         lib.ragc_version.restype = ctypes.c_int
@@ -88,7 +84,10 @@ def load() -> ctypes.CDLL:
         lib.ragc_kv_gather.restype = ctypes.c_int
         lib.ragc_kv_gather.argtypes = [P, P, I32, I32, P, P, P]
         _lib = lib
-        _calls.bind(lib, ctypes.cast(lib.ragc_prefill_attn, P).value, ctypes.cast(lib.ragc_kv_append, P).value)
+        if _calls is None:
+            _load_calls(warn=True)  # built since this module was imported
+        if _calls is not None:
+            _calls.bind(lib, ctypes.cast(lib.ragc_prefill_attn, P).value, ctypes.cast(lib.ragc_kv_append, P).value)
     return _lib
 
 
@@ -187,6 +186,21 @@ def ragc_kv_gather(pool, batch, req: int, length: int, k_out, v_out, stream: int
 
 
 _ctypes_calls = ragc_prefill_attn, ragc_kv_append  # what _calls turns to for anything but plain arguments
-if _calls is not None:
-    _calls.setup(globals(), ragc_kv_pool, ragc_batch, _check, ragc_prefill_attn, ragc_kv_append)
-    ragc_prefill_attn, ragc_kv_append = _calls.ragc_prefill_attn, _calls.ragc_kv_append
+
+
+def _load_calls(warn: bool) -> None:
+    """The two calls through the C extension, if it is there; without it the same functions go through ctypes, 1 us slower."""
+    global _calls, ragc_prefill_attn, ragc_kv_append
+    importlib.invalidate_caches()  # it may have been built a moment ago
+    try:
+        calls = importlib.import_module("._calls", __package__)
+    except ImportError as e:
+        if warn:
+            warnings.warn(f"calls go through ctypes: {e}; `python -m paper_2404_12457_amd.build` builds the C extension", RuntimeWarning, 3)
+        return
+    calls.setup(globals(), ragc_kv_pool, ragc_batch, _check, *_ctypes_calls)
+    ragc_prefill_attn, ragc_kv_append = calls.ragc_prefill_attn, calls.ragc_kv_append
+    _calls = calls
+
+
+_load_calls(warn=False)

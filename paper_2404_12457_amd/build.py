@@ -1,5 +1,5 @@
 """Build libragc.so (the C-ABI library) and libragc_calib.so (the benchmark's calibration
-kernels) for gfx950 with hipcc, and _calls.so (argument marshalling for Python), in-tree.
+kernels) for gfx950 with hipcc, and the extension _calls (argument marshalling for Python), in-tree.
 
     python -m paper_2404_12457_amd.build
 
@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libragc.so")
 CALIB_LIB = os.path.join(HERE, "libragc_calib.so")
-CALLS = os.path.join(HERE, "_calls.so")  # CPython extension, host code only
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))  # for this interpreter, host code only
 SOURCES = ["ragc_api.cpp", "ragc_ctl.cpp", "kv_ops.hip", "attn_f32.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
@@ -48,8 +48,12 @@ def build(extra_flags=(), verbose: bool = False) -> str:
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES + ["calib.hip"]))
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs[:-1]], check=True)
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", CALIB_LIB, objs[-1]], check=True)
-    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
-                    os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS], check=True)
+    headers = sysconfig.get_paths()["include"]
+    if os.path.exists(os.path.join(headers, "Python.h")):
+        subprocess.run(["hipcc", "-x", "c++", "-no-hip-rt", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", headers,
+                        os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS], check=True)
+    else:
+        sys.stderr.write(f"no Python.h in {headers}: {os.path.basename(CALLS)} is left out, calls go through ctypes\n")
     if verbose:
         print("built", LIB, "and", CALIB_LIB)
     return LIB

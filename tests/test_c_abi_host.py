@@ -3,6 +3,9 @@ every symbol the header declares, and rejects bad arguments before touching the
 device."""
 import os
 import re
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -14,9 +17,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def lib():
-    if not os.path.exists(B.LIB_PATH):
-        from paper_2404_12457_amd import build
+    from paper_2404_12457_amd import build
 
+    if not (os.path.exists(B.LIB_PATH) and os.path.exists(build.CALLS)):
         build.build()
     return B.load()
 
@@ -343,3 +346,47 @@ def test_append_marshalled_in_c_behaves_as_through_ctypes(lib):
                          ((_pool(), batch, None, A), {}), ((None, batch, A, A), {}), ((_pool(), A), {}), ((_pool(), batch, A, A, 1.5), {}),
                          ((_pool(), batch, A, A), dict(flags=1))]:
         assert _outcome(B.ragc_kv_append, *args, **kwargs) == _outcome(B._ctypes_calls[1], *args, **kwargs)
+
+
+AFTER_IMPORT = """
+import shutil, sys, warnings
+import numpy as np
+from paper_2404_12457_amd import binding as B, build
+try:
+    B.load()
+    sys.exit("loaded without a library")
+except RuntimeError as e:
+    assert "no fallback" in str(e), e
+early = B.ragc_kv_append
+shutil.copy(sys.argv[1], B.LIB_PATH)
+if sys.argv[2] == "built":
+    shutil.copy(sys.argv[3], build.CALLS)
+elif sys.argv[2] == "broken":
+    open(build.CALLS, "wb").write(b"no library")
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    B.load()
+zero = np.zeros(1, np.int32)
+batch = B.make_batch(0, 1, 65536, 65536, 65536, 65536, zero, zero, zero)
+pool = B.make_pool(65536, 65536, 4, 2, 64, B.RAGC_DTYPE_F32)
+assert B.ragc_prefill_attn(pool, batch, 65536, 65536, 65536, 65536, 2, 0.5) == 0
+assert B.ragc_kv_append(pool, batch, 65536, 65536) == early(pool, batch, 65536, 65536) == 0
+print(type(B.ragc_prefill_attn).__name__, *[str(w.message) for w in seen])
+"""
+
+
+@pytest.mark.parametrize("calls", ["built", "absent", "broken"])
+def test_libraries_that_appear_after_the_import(lib, tmp_path, calls):
+    """Importing the binding of a tree that is not built yet, building, loading, all in one process; and a tree whose C
+    extension is missing or does not load: the calls go through ctypes, and a warning says why."""
+    from paper_2404_12457_amd import build
+
+    package = tmp_path / "paper_2404_12457_amd"
+    package.mkdir()
+    for name in ("__init__.py", "binding.py", "build.py"):
+        shutil.copy(os.path.join(os.path.dirname(B.__file__), name), package)
+    r = subprocess.run([sys.executable, "-c", AFTER_IMPORT, B.LIB_PATH, calls, build.CALLS], cwd=tmp_path, capture_output=True, text=True,
+                       env={k: v for k, v in os.environ.items() if k != "PYTHONPATH"}, timeout=100)
+    assert r.returncode == 0, r.stderr
+    want = {"built": ("builtin_function_or_method",), "absent": ("function", "_calls"), "broken": ("function", os.path.basename(build.CALLS))}
+    assert all(x in r.stdout for x in want[calls]) and ("ctypes" in r.stdout) == (calls != "built"), r.stdout
