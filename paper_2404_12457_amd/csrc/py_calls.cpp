@@ -144,8 +144,10 @@ PyObject* bind(PyObject*, PyObject* args) {
 }
 
 PyMethodDef methods[] = {
-    {"ragc_prefill_attn", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(attn)), METH_FASTCALL | METH_KEYWORDS, nullptr},
-    {"ragc_kv_append", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(append)), METH_FASTCALL | METH_KEYWORDS, nullptr},
+    {"ragc_prefill_attn", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(attn)), METH_FASTCALL | METH_KEYWORDS,
+     "ragc_prefill_attn(pool, batch, q, k_new, v_new, out, q_heads, softmax_scale, flags=0, workspace=None, workspace_bytes=0, stream=0)\n--\n\n"},
+    {"ragc_kv_append", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(append)), METH_FASTCALL | METH_KEYWORDS,
+     "ragc_kv_append(pool, batch, k_new, v_new, stream=0)\n--\n\n"},
     {"setup", setup, METH_VARARGS, nullptr},
     {"bind", bind, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};

@@ -1,6 +1,7 @@
 """Host-side checks of the C-ABI library that need no GPU: it loads, exports
 every symbol the header declares, and rejects bad arguments before touching the
 device."""
+import inspect
 import os
 import re
 import shutil
@@ -346,6 +347,12 @@ def test_append_marshalled_in_c_behaves_as_through_ctypes(lib):
                          ((_pool(), batch, None, A), {}), ((None, batch, A, A), {}), ((_pool(), A), {}), ((_pool(), batch, A, A, 1.5), {}),
                          ((_pool(), batch, A, A), dict(flags=1))]:
         assert _outcome(B.ragc_kv_append, *args, **kwargs) == _outcome(B._ctypes_calls[1], *args, **kwargs)
+
+
+def test_calls_marshalled_in_c_show_their_arguments(lib):
+    for f, g in zip((B.ragc_prefill_attn, B.ragc_kv_append), B._ctypes_calls):
+        got, want = inspect.signature(f).parameters, inspect.signature(g).parameters
+        assert [(p.name, p.default) for p in got.values()] == [(p.name, p.default) for p in want.values()]
 
 
 AFTER_IMPORT = """
