@@ -197,6 +197,15 @@ int ragc_batch_validate(const ragc_kv_pool* pool, const ragc_batch* batch, int32
  * workspace size, so query ragc_prefill_attn_workspace under the same setting. */
 int ragc_debug_set_attn_plan(int32_t variant, int32_t splits);
 
+/* Test hook, process-wide as the one above: rows of the matrix-core products of 128-row work items
+ * at head_dim 128 that are not split.  0 = library's choice, 16 or 32. */
+int ragc_debug_set_attn_product(int32_t rows);
+
+/* Test hook: those rows for this batch with these flags, under both overrides, as a value of 16 or
+ * 32; 0 where none of the batch's work items are of that kind.  Only the host arrays of `batch` are
+ * read.  Returns a negative ragc_status on error. */
+int ragc_debug_get_attn_product(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads, uint32_t flags);
+
 /* Test hook: the layout ragc_prefill_attn would choose for this batch with these flags (under
  * the override above, if any).  plan[0]: rows per work item (fp32: 16 or 32; bf16: 32 or 128),
  * plan[1]: waves per workgroup, plan[2]: copies of every work item along the keys (1: not

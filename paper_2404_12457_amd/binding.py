@@ -27,7 +27,8 @@ RAGC_SWAP_TO_DEVICE, RAGC_SWAP_TO_HOST = 0, 1
 
 EXPORTS = ["ragc_version", "ragc_last_error", "ragc_kv_bytes_per_token", "ragc_prefill_attn_workspace",
            "ragc_prefill_attn", "ragc_prefill_attn_static", "ragc_kv_append", "ragc_kv_swap", "ragc_kv_gather",
-           "ragc_batch_validate", "ragc_debug_set_attn_plan", "ragc_debug_get_attn_plan"]
+           "ragc_batch_validate", "ragc_debug_set_attn_plan", "ragc_debug_get_attn_plan",
+           "ragc_debug_set_attn_product", "ragc_debug_get_attn_product"]
 
 
 class ragc_kv_pool(ctypes.Structure):
@@ -77,6 +78,10 @@ def load() -> ctypes.CDLL:
         lib.ragc_debug_set_attn_plan.argtypes = [I32, I32]
         lib.ragc_debug_get_attn_plan.restype = ctypes.c_int
         lib.ragc_debug_get_attn_plan.argtypes = [P, P, I32, U32, P]
+        lib.ragc_debug_set_attn_product.restype = ctypes.c_int
+        lib.ragc_debug_set_attn_product.argtypes = [I32]
+        lib.ragc_debug_get_attn_product.restype = ctypes.c_int
+        lib.ragc_debug_get_attn_product.argtypes = [P, P, I32, U32]
         lib.ragc_kv_append.restype = ctypes.c_int
         lib.ragc_kv_append.argtypes = [P, P, P, P, P]
         lib.ragc_kv_swap.restype = ctypes.c_int
@@ -165,6 +170,15 @@ def ragc_debug_get_attn_plan(pool, batch, q_heads: int, flags: int = 0) -> Tuple
     plan = (ctypes.c_int32 * 3)()
     _check(load().ragc_debug_get_attn_plan(_ref(pool), _ref(batch), q_heads, flags, ctypes.addressof(plan)))
     return tuple(plan)
+
+
+def ragc_debug_set_attn_product(rows: int = 0) -> int:
+    return _check(load().ragc_debug_set_attn_product(rows))
+
+
+def ragc_debug_get_attn_product(pool, batch, q_heads: int, flags: int = 0) -> int:
+    """rows of the products of 128-row work items at head_dim 128, 0 if the batch has none"""
+    return _check(load().ragc_debug_get_attn_product(_ref(pool), _ref(batch), q_heads, flags))
 
 
 def ragc_kv_append(pool, batch, k_new, v_new, stream: int = 0) -> int:

@@ -19,6 +19,7 @@ thread_local char g_err[512] = "";
 // test overrides of the launch plan (ragc_debug_set_attn_plan); -1 / 0 = the library decides
 std::atomic<int> g_force_variant{-1};
 std::atomic<int> g_force_splits{0};
+std::atomic<int> g_force_product{0};
 }
 
 namespace ragc {
@@ -311,7 +312,9 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
         plan->variant = splits > 1 ? ragc::kAttnVariantOneGroup : variant;
         // Launches that the power limit holds back take the product of less energy per flop, others the one of fewer cycles
         // (attn_bf16.hip has both sides).
-        plan->quarters = d128 && splits == 1 && (wgs >= 3 * cus || sum_keys * pool->kv_heads >= 12000 * cus);
+        const int force_product = g_force_product.load(std::memory_order_relaxed);
+        plan->quarters = d128 && splits == 1 &&
+                         (force_product ? force_product == 16 : wgs >= 3 * cus || sum_keys * pool->kv_heads >= 12000 * cus);
         return make(false, splits, items);
     };
     // Copies that give every CU a 128-row item with at least three 64-key tiles.  Those of 32-row items (below) never take
@@ -628,6 +631,25 @@ int ragc_debug_get_attn_plan(const ragc_kv_pool* pool, const ragc_batch* batch, 
     plan[1] = p.rows_kernel ? p.waves : p.variant == ragc::kAttnVariantTwoGroups ? 8 : 4;
     plan[2] = p.splits;
     return RAGC_OK;
+}
+
+int ragc_debug_set_attn_product(int32_t rows) {
+    g_err[0] = 0;
+    if (rows != 0 && rows != 16 && rows != 32) return fail(RAGC_ERR_SHAPE, "products of %d rows unknown", rows);
+    g_force_product.store(rows, std::memory_order_relaxed);
+    return RAGC_OK;
+}
+
+int ragc_debug_get_attn_product(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t q_heads, uint32_t flags) {
+    int32_t plan[3];
+    if (int rc = ragc_debug_get_attn_plan(pool, batch, q_heads, flags, plan)) return rc;
+    if (pool->dtype != RAGC_DTYPE_BF16 || pool->head_dim != 128 || plan[0] != ragc::kAttnRowsPerItem || plan[2] != 1) return 0;
+    BatchInfo info;
+    HostMeta h;
+    if (int rc = check_batch(pool, batch, false, false, &h, &info)) return rc;
+    Bf16Plan p;
+    if (int rc = plan_bf16(pool, batch, h, q_heads / pool->kv_heads, flags, &p)) return rc;
+    return p.quarters ? 16 : 32;
 }
 
 int ragc_batch_validate(const ragc_kv_pool* pool, const ragc_batch* batch, int32_t writes_new_tokens) {

@@ -219,6 +219,37 @@ def test_plan_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
     assert _plan(p, n, hq, hkv, d) == want
 
 
+def _product(p, n, hq, hkv, d=128, dtype=B.RAGC_DTYPE_BF16):
+    b, keep = _batch(p, n, stride=max((x + y + 15) // 16 for x, y in zip(p, n)) or 1)
+    return B.ragc_debug_get_attn_product(_pool(num_blocks=1 << 20, kv_heads=hkv, head_dim=d, dtype=dtype), b, hq)
+
+
+@pytest.mark.parametrize("p,n,hq,hkv,d,want", [
+    ((0,) * 96, (32,) * 96, 32, 8, 128, 16),              # 768 items of 128 rows
+    ((0,) * 95, (32,) * 95, 32, 8, 128, 32),              # 760
+    ((2744,) * 4, (256,) * 4, 32, 8, 128, 16),            # 256 items, four 32-row ones each: 12000 keys per CU
+    ((2743,) * 4, (256,) * 4, 32, 8, 128, 32),            # 11996
+    ((5744,) * 4, (256,) * 4, 32, 8, 64, 0),              # head_dim 64
+    ((1024,), (100,), 32, 32, 128, 0),                    # 32-row items
+    ((4445,) * 3, (46,) * 3, 64, 8, 128, 0),              # split items
+    ((10, 0), (0, 0), 8, 8, 128, 0),
+])
+def test_product_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
+    assert _product(p, n, hq, hkv, d) == want
+    assert _product(p, n, hq, hkv, d, dtype=B.RAGC_DTYPE_F32) == 0
+    try:
+        for rows in (16, 32):
+            assert B.ragc_debug_set_attn_product(rows) == 0
+            assert _product(p, n, hq, hkv, d) == (rows if want else 0)
+        for bad in (-1, 1, 64):
+            with pytest.raises(B.RagcError):
+                B.ragc_debug_set_attn_product(bad)
+        with pytest.raises(B.RagcError):
+            _product(p, n, hq + 1, hkv + hkv, d)
+    finally:
+        B.ragc_debug_set_attn_product(0)
+
+
 def test_fp32_plan(lib):
     assert _plan((300,), (64,), 32, 8, dtype=B.RAGC_DTYPE_F32) == (16, 8, 1)    # 128 workgroups
     assert _plan((300,), (129,), 32, 8, dtype=B.RAGC_DTYPE_F32) == (16, 4, 1)   # 264

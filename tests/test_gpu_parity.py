@@ -30,12 +30,14 @@ def H():
 
 @pytest.fixture
 def force_plan(H):
-    """Override the library's choice of kernel variant / number of key copies for one test."""
-    def set_plan(variant=-1, splits=0):
+    """Override the library's choice of kernel variant / number of key copies / rows of a product for one test."""
+    def set_plan(variant=-1, splits=0, product=0):
         B.ragc_debug_set_attn_plan(-1 if variant is None else variant, 0 if splits is None else splits)
+        B.ragc_debug_set_attn_product(product)
 
     yield set_plan
     B.ragc_debug_set_attn_plan(-1, 0)
+    B.ragc_debug_set_attn_product(0)
 
 
 def _bits(t):
@@ -651,6 +653,28 @@ def test_batches_between_the_two_bf16_kernels_match_oracle(H, hq, hkv, d, lens):
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
 
 
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (21, 3)])
+@pytest.mark.parametrize("variant,product", [(0, 16), (1, 16), (0, 32), (1, 32)])
+@pytest.mark.parametrize("gain", [0.0, 2.0, 8.0, 40.0])
+def test_both_products_follow_the_scores(H, variant, product, hq, hkv, gain, force_plan):
+    """As above on products of 16 and of 32 rows, with groups of seven too (tokens straddle the blocks of a wave), prefixes and
+    new rows at every edge of a tile, and more key tiles than one window of block ids holds; the append byte for byte."""
+    lens = [(0, 140), (63, 70), (64, 33), (500, 40), (1, 1), (1000, 65), (15, 17), (31, 16), (48, 47), (8300, 9), (700, 0)]
+    w = W.make_small("bf16", hq, hkv, 128, lens, seed=8150 + int(gain), q_gain=gain)
+    force_plan(variant, 0, product)
+    _check_with_append(H, w)
+    dw = H.DeviceWorkload(w)
+    assert B.ragc_debug_get_attn_product(dw.pool, dw.batch, hq) == product
+
+
+@pytest.mark.parametrize("variant,product", [(0, 16), (1, 16)])
+@pytest.mark.parametrize("new", [9, 40, 130])
+def test_nan_keys_reach_every_row_that_sees_them_on_products_of_16_rows(H, variant, product, new, force_plan):
+    force_plan(variant, 0, product)
+    dw = _check_nan_keys(H, "bf16", 128, new)
+    assert B.ragc_debug_get_attn_product(dw.pool, dw.batch, 8) == 16
+
+
 @pytest.mark.parametrize("dtype,d,variant,splits", [
     ("bf16", 128, None, None), ("bf16", 64, None, None), ("bf16", 128, 0, 16), ("bf16", 64, 1, 7), ("bf16", 128, 0, 1), ("bf16", 64, 1, 1),
     ("f32", 128, None, None), ("f32", 64, None, None)])
@@ -660,6 +684,10 @@ def test_nan_keys_reach_every_row_that_sees_them_and_no_other(H, dtype, d, varia
     short range -- and in one fresh token: the rows of that head's group that see such a key are NaN in full, all
     others match the oracle.  The next request has nothing but NaN keys in head 0."""
     force_plan(variant, splits)
+    _check_nan_keys(H, dtype, d, new)
+
+
+def _check_nan_keys(H, dtype, d, new):
     hq, hkv = 8, 2
     lens = [(200, new), (1100, new), (40, new), (0, new), (64, 1)]
     w = W.make_small(dtype, hq, hkv, d, lens, seed=8300 + d + new)
@@ -681,6 +709,7 @@ def test_nan_keys_reach_every_row_that_sees_them_and_no_other(H, dtype, d, varia
     assert np.all(np.isnan(got[affected]))
     assert np.all(np.isfinite(got[~affected]))
     assert np.max(np.abs(got[~affected] - want[~affected])) <= U.TOL[dtype]
+    return dw
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(4, 4, 64), (8, 2, 128)])
@@ -854,31 +883,35 @@ def test_fp32_split_products_of_operands_far_from_one(H, h, d, n, what):
         assert np.array_equal(got[0], v[0])  # the one token that token 0 sees
 
 
-@pytest.mark.parametrize("d,variant,splits", [(128, 0, 0), (128, 1, 0), (128, 0, 3), (64, 0, 0), (64, 1, 0), (64, 0, 3)])
-def test_cached_steps_end_at_every_block_of_a_tile(H, force_plan, d, variant, splits):
+@pytest.mark.parametrize("d,variant,splits,product", [(128, 0, 0, 32), (128, 1, 0, 32), (128, 0, 0, 16), (128, 1, 0, 16), (128, 0, 3, 0),
+                                                      (64, 0, 0, 0), (64, 1, 0, 0), (64, 0, 3, 0)])
+def test_cached_steps_end_at_every_block_of_a_tile(H, force_plan, d, variant, splits, product):
     """128-row items: the prefix ends before, at and behind each of the four 16-token blocks of a 64-key tile (one wave copies
     each), in the first tile and behind more tiles than one window of block ids holds; rows in blocks of 16 and 32."""
     lens = [(p, 33 + p % 7) for p in (0, 15, 16, 17, 31, 32, 47, 48, 49, 63, 64, 65, 127, 4223, 4224, 4240, 8300)]
     w = W.make_small("bf16", 8, 2, d, lens, seed=9000 + d, q_gain=2.0)
-    force_plan(variant, splits)
+    force_plan(variant, splits, product)
     dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
     assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, 8)[0] == 128
+    assert B.ragc_debug_get_attn_product(dw.pool, dw.batch, 8) == product
     pk, pv = w.pool_image()
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
 
 
-@pytest.mark.parametrize("h,variant", [(48, 0), (48, 1), (44, 0), (44, 1)])
-def test_large_launches_of_head_dim_128(H, force_plan, h, variant):
+@pytest.mark.parametrize("h,group,variant", [(48, 1, 0), (48, 1, 1), (44, 1, 0), (44, 1, 1), (32, 3, 0), (32, 3, 1)])
+def test_large_launches_of_head_dim_128(H, force_plan, h, group, variant):
     """From three 128-row items per CU on (768 here) a row is in four lanes, below in two: 48 and 44 heads of 17 items, the
-    prefix ending around the 16-token blocks of a tile, new rows around the 16- and 32-row blocks of a wave."""
+    prefix ending around the 16-token blocks of a tile, new rows around the 16- and 32-row blocks of a wave; in groups of
+    three, whose tokens straddle the blocks of a wave, 34 items of 32 kv heads."""
     lens = [(p, n) for p, n in zip((0, 15, 16, 17, 31, 32, 47, 48, 49, 63, 64, 65, 127, 130, 0, 700, 4224),
                                    (1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 96, 97, 128, 113, 100))]
-    w = W.make_small("bf16", h, h, 128, lens, seed=9100 + h, q_gain=2.0)
+    w = W.make_small("bf16", h * group, h, 128, lens, seed=9100 + h, q_gain=2.0)
     force_plan(variant, 0)
     dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
-    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, h) == (128, 8 if variant else 4, 1)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, h * group) == (128, 8 if variant else 4, 1)
+    assert B.ragc_debug_get_attn_product(dw.pool, dw.batch, h * group) == (32 if h == 44 else 16)
     pk, pv = w.pool_image()
     OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
     assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "bf16")))
