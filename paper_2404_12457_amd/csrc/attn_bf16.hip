@@ -204,16 +204,17 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             pend = 0;
         }
     };
-    // Steps whose block of this wave is cached as a whole -- most of them -- take one branch, a lane read and a few scalar sums,
-    // as all of it stands between the barrier and the first product of a step (with the three cases told apart and the
-    // address made anew in 64 bits at each: 8 x (4096 + 128) tokens of 64/8 heads 141.7 us against 135.1).
+    // All of `prepare` stands between the barrier and the first product of a step.  For a block that is cached as a whole -- most
+    // of them -- it is one branch, laid out as the way straight ahead, a lane read and a few scalar sums: the base of the head is
+    // made once (made anew in 64 bits at each step: 8 x (4096 + 128) tokens of 64/8 heads 137.6 us against 135.1).  Counting these
+    // steps beforehand, three scalar instructions less in each, is no faster (137.3), and what it takes before the first copy and
+    // in scalar registers, some of them spilled, costs prompts of one tile 1-3 % (512 items of head_dim 64 9.07 us against 8.83,
+    // 400 of 9-11 tokens, 32/8 heads of 128, 13.66 against 13.39).
     const uint64_t block_bytes = (uint64_t)a.block_stride * 2;
     const uint64_t head_k = uniform_u64(pool_k + (long long)g * kBlock * D), head_v = uniform_u64(pool_v + (long long)g * kBlock * D);
     const uint32_t copy_dst = smem_addr + grp * RING * STAGEB + wq * 16 * ROWB;
-    const int pool_tiles = P >= wq * 16 + 16 ? (P - wq * 16 - 16) / TN + 1 - t_lo - grp : 0;
-    const int pool_steps = pool_tiles > 0 ? (pool_tiles + NG - 1) / NG : 0;
-    bool loff_fresh = pool_steps <= 0;  // no copy of a whole pool block comes before the fresh ones
-    set_loff(loff_fresh ? Hkv * D : D);
+    set_loff(D);
+    bool loff_fresh = false;
     auto prepare = [&](int step) {
         if (step - blk_base >= 64) {
             blk_base = step;
@@ -222,19 +223,17 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             asm volatile("" ::"v"(blk_vec));  // the compiler's wait for this load stays inside the branch
         }
         const int blk = __builtin_amdgcn_readlane(blk_vec, step - blk_base);
+        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
+        const int kbase = tg * TN + wq * 16;
         const uint32_t dst = copy_dst + step % RING * STAGEB;
-        if (__builtin_expect(step < pool_steps, 1)) {
+        if (__builtin_expect(kbase + 16 <= P, 1)) {
             // one pool block, uniform base + per-lane constant
             const uint64_t boff = (uint32_t)blk * block_bytes;
             pend_kb = head_k + boff;
             pend_vb = head_v + boff;
             pend_dst = dst;
             pend = 1;
-            return;
-        }
-        const int tg = min(t_lo + step * NG + grp, ntiles - 1);  // a group without a tile re-reads the last one (same count of loads)
-        const int kbase = tg * TN + wq * 16;
-        if (kbase >= P && kbase + 16 <= kv_limit) {
+        } else if (kbase >= P && kbase + 16 <= kv_limit) {
             // 16 fresh rows, all inside the horizon
             const long long boff = (((long long)(s0 + kbase - P)) * Hkv + g) * D * 2;
             pend_kb = uniform_u64(reinterpret_cast<const char*>(k_new) + boff);
