@@ -40,13 +40,15 @@
 // v_mfma_f32_16x16x32_bf16 sustains 1852 TFLOP/s at 2.07 GHz where 32x32x16, which moves the
 // accumulators through the registers twice as often per flop, sustains 1640 at 1.77.  Per cycle it is
 // the slower one (16.5-17 instead of 16 in a loop), which shows while a launch is too short or too
-// small for the limit to take hold.  So at head_dim 128 launches of three items per CU and more, or
-// of 12000 keys (times 32 rows) per CU and more, 50 GFLOP in all, take 16x16x32 (KG = 4: two blocks
-// of 16 rows per wave, a row in four lanes): 4 x (4096 + 128) tokens of 64/8 heads 69.9 us with
-// 32x32x16, 66.3 with 16x16x32, 16 x (256-4096 + 64-768) of 32/8 302 and 286, four whole prompts of
-// 2200-3500 252 and 244; medians of 40 batches above the line 0.99.  Below it 32x32x16 (KG = 2: one
-// block of 32 rows, a row in two lanes) takes 0.98 of the time (medians of 38 batches): 64/8 heads,
-// 200-592 + 486 tokens 17.8 against 18.5, prompts of 181-545 tokens without a prefix 23.1 against 24.1.
+// small for the limit to take hold.  So at head_dim 128 launches of 12000 keys (times 32 rows) per CU
+// and more, 50 GFLOP in all, or of 1500 where there are three items per CU and more, take 16x16x32
+// (KG = 4: two blocks of 16 rows per wave, a row in four lanes): on a warm card 4 x (4096 + 128) tokens
+// of 64/8 heads 68.6 us with 32x32x16 and 66.6 with 16x16x32, eight of them 141.6 and 136, 16 x (256-4096 +
+// 64-768) of 32/8 heads 293 and 289.5, four whole prompts of 2200-3500 245 and 240; ragged batches of two
+// to three items per CU go either way, by up to 4 %.  Others take 32x32x16 (KG = 2: one block of 32 rows, a
+// row in two lanes): below 12000 0.98 of the time (medians of 38 batches; 64/8 heads, 200-592 + 486 tokens
+// 17.8 us against 18.5); with three items per CU 0.97-1.00 up to 1300 (1360 items of 9-37 tokens without a
+// prefix 21.2 against 21.9), but 0.99-1.03 from 1500 to 12000 (1866 of 180-365 tokens 54.2 against 53.0).
 // At head_dim 64, where a step has half the products for the same softmax, 320 items of 450-1900 keys
 // take 21.5 us against 22.7, and only with the chip full of long items is it the other way round (2048
 // of 4224 keys: 81 us against 78).

@@ -314,7 +314,7 @@ int plan_bf16(const ragc_kv_pool* pool, const ragc_batch* batch, const HostMeta&
         // (attn_bf16.hip has both sides).
         const int force_product = g_force_product.load(std::memory_order_relaxed);
         plan->quarters = d128 && splits == 1 &&
-                         (force_product ? force_product == 16 : wgs >= 3 * cus || sum_keys * pool->kv_heads >= 12000 * cus);
+                         (force_product ? force_product == 16 : sum_keys * pool->kv_heads >= (wgs >= 3 * cus ? 1500 : 12000) * cus);
         return make(false, splits, items);
     };
     // Copies that give every CU a 128-row item with at least three 64-key tiles.  Those of 32-row items (below) never take

@@ -225,8 +225,10 @@ def _product(p, n, hq, hkv, d=128, dtype=B.RAGC_DTYPE_BF16):
 
 
 @pytest.mark.parametrize("p,n,hq,hkv,d,want", [
-    ((0,) * 96, (32,) * 96, 32, 8, 128, 16),              # 768 items of 128 rows
-    ((0,) * 95, (32,) * 95, 32, 8, 128, 32),              # 760
+    ((93,) * 96, (32,) * 96, 32, 8, 128, 16),             # 768 items of 128 rows, four 32-row ones each: 1500 keys per CU
+    ((92,) * 96, (32,) * 96, 32, 8, 128, 32),             # 1488
+    ((0,) * 96, (32,) * 96, 32, 8, 128, 32),              # prompts of one tile
+    ((93,) * 95, (32,) * 95, 32, 8, 128, 32),             # 760 items
     ((2744,) * 4, (256,) * 4, 32, 8, 128, 16),            # 256 items, four 32-row ones each: 12000 keys per CU
     ((2743,) * 4, (256,) * 4, 32, 8, 128, 32),            # 11996
     ((5744,) * 4, (256,) * 4, 32, 8, 64, 0),              # head_dim 64
