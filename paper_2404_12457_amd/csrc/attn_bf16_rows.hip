@@ -36,9 +36,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     constexpr int KSTEPS = D / 16;
     constexpr int DT = D / 32;
     constexpr int OCH = D / 4;        // 16-byte chunks of a fp32 output row
+    constexpr int OWN = 8;            // up to so many rows of Q a wave brings for itself
     static_assert(TR * D * 4 == 2 * PLANEB, "a wave's output fills its tile buffers");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * PLANEB];
-    __shared__ __attribute__((aligned(1024))) char qs[TR * ROWB];
+    __shared__ __attribute__((aligned(1024))) char qs[(NW * OWN > TR ? NW * OWN : TR) * ROWB];
     __shared__ float2 MLs[NW][TR];  // (max, sum) of every wave and row
 
     touch_args(a, wk);
@@ -80,24 +81,33 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     auto id_at = [&](int step) { return table + min(tile_of(step + (lane >> 1)) * 2 + (lane & 1), nblk - 1); };
     int blk_base = 0, blk_vec;
 
-    // Q: every wave needs all rows.  Of more than eight they are copied to LDS once and shared, 1 KiB per instruction: read by
-    // every wave from memory they were 64 KiB per workgroup, half as much as the first tiles behind them (one request of 1024
-    // + 100 tokens 11.05 -> 10.6 us, 3000 + 64 of 2 heads, split, 12.9 -> 11.6).  Up to eight, the rows of a decode step, are
-    // 16 KiB and stay with the waves, behind their first tiles: no wave waits for the others (4 of 4096 keys 16.7 us, with
-    // shared rows 17.6).
-    const bool share_q = rows_here > 8;
-    if (share_q) {
+    // Q: every wave needs all rows, copied to LDS behind its block ids and ahead of its first tile, 1 KiB per instruction.  Of
+    // more than eight rows each wave brings a part for all: read by every wave from memory they were 64 KiB per workgroup, half
+    // as much as the first tiles (one request of 1024 + 100 tokens 11.05 -> 10.6 us, 3000 + 64 of 2 heads, split, 12.9 ->
+    // 11.6).  Up to eight, the rows of a decode step, are 16 KiB, and each wave brings its own: no wave waits for the others
+    // (shared rows cost 4 of 4096 keys 0.9 us of 17.6), and Q does not wait for the first tiles (read into registers behind
+    // them: 73 decode steps of 105 keys, 32/8 heads, 13.9 us against 12.65, 16 of 91-275 8.0 against 7.3, 4 of 4096, 64/8
+    // heads, 19.3 against 19.0).
+    const bool share_q = rows_here > OWN;
+    {
         constexpr int QI = TR / RPI, NQ = QI > NW ? QI / NW : 1;  // with fewer pieces than waves some bring the same one
-        const void* src[NQ];
+        constexpr int NQ_OWN = OWN / RPI;
+        auto q_src = [&](int r) {
+            const int row = row0 + min(r, rows_here - 1), tok = div_g(row);
+            return q + ((long long)(s0 + tok) * Hq + g * G + (row - tok * G)) * D + ((lane % CPR) ^ swz<D>(r)) * 8;
+        };
+        const uint32_t q_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)qs;
+        if (share_q) {
+            const void* src[NQ];
 #pragma unroll
-        for (int x = 0; x < NQ; ++x) {
-            const int r = RPI * ((w + x * NW) % QI) + lane / CPR, row = row0 + min(r, rows_here - 1), tok = div_g(row);
-            src[x] = q + ((long long)(s0 + tok) * Hq + g * G + (row - tok * G)) * D + ((lane % CPR) ^ swz<D>(r)) * 8;
+            for (int x = 0; x < NQ; ++x) src[x] = q_src(RPI * ((w + x * NW) % QI) + lane / CPR);
+            blk_vec = load_ahead_of_copies<NQ>(id_at(0), src, q_addr + w % QI * 1024, NW * 1024);
+        } else {
+            const void* src[NQ_OWN];
+#pragma unroll
+            for (int x = 0; x < NQ_OWN; ++x) src[x] = q_src(RPI * x + lane / CPR);
+            blk_vec = load_ahead_of_copies<NQ_OWN>(id_at(0), src, q_addr + w * (OWN * ROWB), 1024);
         }
-        blk_vec = load_ahead_of_copies<NQ>(id_at(0), src, (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)qs + w % QI * 1024, NW * 1024);
-    } else {
-        blk_vec = *id_at(0);
-        asm volatile("" ::"v"(blk_vec));  // the wait for this load stays inside the branch
     }
 
     // ---- copies: lane i of an instruction brings row RPI c + i / CPR of a block, chunk (i % CPR) ^ swz(row)
@@ -143,8 +153,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
     if (nsteps > 0) {
         copy_tile(0, true);
         copy_tile(0, false);
-        if (share_q) wait_vmcnt<2 * NI>();  // this wave's part of Q
-    } else if (share_q) {
+        wait_vmcnt<2 * NI>();  // this wave's part of Q
+    } else {
         wait_vmcnt<0>();
     }
 
@@ -161,20 +171,13 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_bf16_rows_kernel(AttnLaunch a
             voff[h2][dt] = row * ROWB + ((((elem >> 3)) ^ swz<D>(row)) << 4) + (elem & 7) * 2;
         }
 
+    if (share_q) block_barrier();  // every wave's part of Q has landed
+    lds_char* const qbuf = (lds_char*)qs + (share_q ? 0 : w * (OWN * ROWB));
+    const int q_row = share_q ? l32 : min(l32, OWN - 1);
     bf16x8 qreg[KSTEPS];
-    if (share_q) {
-        block_barrier();  // every wave's part of Q has landed
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-            qreg[ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((lds_char*)qs + koff[ks]);
-    } else {
-        const __bf16* qp = q + ((long long)(s0 + my_tok) * Hq + g * G + (my_row - my_tok * G)) * D + hf * 8;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-        // every ordinary load has completed before the loop's copies are counted
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) asm volatile("" ::"v"(qreg[ks]));
-    }
+    for (int ks = 0; ks < KSTEPS; ++ks)
+        qreg[ks] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(qbuf + q_row * ROWB + (((2 * ks + hf) ^ swz<D>(q_row)) << 4));
 
     f32x16 oacc[DT];
 #pragma unroll

@@ -608,6 +608,18 @@ def test_short_row_kernel_at_its_edges(H, hq, hkv, d, lens, flags):
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "bf16")))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("variant,splits", [(0, 1), (1, 1), (1, 5)])
+@pytest.mark.parametrize("group", [1, 7, 8, 9, 32])
+def test_rows_of_q_up_to_eight_and_more(H, d, variant, splits, group, force_plan):
+    """32-row items of one to 32 rows (up to eight each wave has its own copy of Q, above one is shared), four and eight
+    waves, some of them without a key tile, one copy and more copies than a short request has tiles."""
+    lens = [(0, 1), (31, 1), (97, 1), (300, 1), (1500, 1)] + [(70, 8 // group)] * (group in (1, 7)) + [(70, 9)] * (group == 1)
+    w = W.make_small("bf16", 2 * group, 2, d, lens, seed=7950 + group + d, q_gain=2.0)
+    force_plan(variant, splits)
+    _check_with_append(H, w)
+
+
 @pytest.mark.parametrize("dtype,hkv,d", [("bf16", 1, 64), ("bf16", 3, 128), ("f32", 8, 128), ("f32", 2, 64), ("bf16", 40, 64)])
 @pytest.mark.parametrize("reqs", [1, 63, 64, 65, 130])
 def test_append_kernel_at_its_edges(H, dtype, hkv, d, reqs):
