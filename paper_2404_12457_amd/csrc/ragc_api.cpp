@@ -451,9 +451,12 @@ int run_bf16_plan(const ragc::AttnLaunch& a, const HostMeta& h, const Bf16Plan& 
 // The 32-row items, whose kernel multiplies on the bf16 cores, take 0.72-0.85 of the time of the 16-row items where those leave
 // no CU idle, and more where they do (125 of ~2000 keys: 52 us against 41) or where their rows would be half empty (320
 // against 480: 15.2 against 11.9).  Lines from 160 batches timed with every choice, in workgroups of 16 rows per CU:
-// head_dim 128, from 1.25 on (1.3: 0.76-0.93; 1.03-1.16: 1.0-1.2), while they are at most one per CU with at least 96 keys on
-// average (1.6: 1.06 and 1.09 below); head_dim 64, whose steps are shorter, from 1 to 2 with at least 200 keys (0.74-0.96) and
-// from 4.5 on (0.74-0.93); 2 to 4: 0.93-1.11.
+// head_dim 128, from 1.25 on (1.3: 0.76-0.93; 1.03-1.16: 1.0-1.2).  While they are at most one per CU, with at least 96 keys on
+// average (1.6: 1.06 and 1.09 below); above, where they need fewer rounds of two per CU (another 65 batches: 264 against 504
+// 14.7 us against 12.2, 288 against 504 of ~1270 keys 76 against 61, 544 against 1016 1.04, but 328 against 656 0.90).
+// head_dim 64, whose steps are shorter, from 1 to 2 with at least 200 keys (0.74-0.96), and from 4.5 on with at least 96 keys
+// (0.74-0.94), or where they need fewer rounds, three per CU and four (712 against 1240 of 14 keys 0.91; 864 against 1440 of 10
+// 1.14); 2 to 4: 0.93-1.11.
 struct F32Plan {
     int rows, waves;
 };
@@ -466,9 +469,13 @@ F32Plan plan_f32(const HostMeta& h, const std::vector<int32_t>& order, int group
         keys += t * ((int64_t)h.prefix_len[r] + h.new_len[r]);
     }
     const int64_t cus = cu_count(), wgs = tiles * kv_heads, split_wgs = split_tiles * kv_heads;
+    const auto fewer_rounds = [&](int64_t at_once, int64_t split_at_once) {
+        return (split_wgs + split_at_once - 1) / split_at_once < (wgs + at_once - 1) / at_once;
+    };
     const bool split = split_tiles * 5 <= tiles * 3 &&
-                       (head_dim == 128 ? wgs * 4 >= cus * 5 && (split_wgs > cus || keys >= 96 * tiles)
-                                        : wgs * 2 >= cus * 9 || (wgs > cus && split_wgs <= cus && keys >= 200 * tiles));
+                       (head_dim == 128 ? wgs * 4 >= cus * 5 && (split_wgs > cus ? fewer_rounds(2 * cus, 2 * cus) : keys >= 96 * tiles)
+                                        : (wgs * 2 >= cus * 9 && (keys >= 96 * tiles || fewer_rounds(4 * cus, 3 * cus))) ||
+                                              (wgs > cus && split_wgs <= cus && keys >= 200 * tiles));
     return {split ? ragc::kAttnF32SplitRows : ragc::kAttnF32Rows, (split ? split_wgs : wgs) > cus ? 4 : 8};
 }
 

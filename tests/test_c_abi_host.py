@@ -337,6 +337,20 @@ def test_fp32_plan_on_both_sides_of_its_lines(lib, p, n, hq, hkv, d, want):
     assert _plan(p, n, hq, hkv, d, dtype=B.RAGC_DTYPE_F32) == want
 
 
+@pytest.mark.parametrize("p,n,d,want", [
+    ((300,) * 3, (81,) * 3, 128, (16, 4, 1)),     # 504 workgroups of 16 rows and 264 of 32: one round of two per CU either way
+    ((300,) * 3, (85,) * 3, 128, (32, 4, 1)),     # 528 and 264: two rounds against one
+    ((300,) * 6, (81,) * 6, 128, (16, 4, 1)),     # 1008 and 528
+    ((300,) * 6, (85,) * 6, 128, (32, 4, 1)),     # 1056 and 528: three against two
+    ((0,) * 48, (16,) * 48, 64, (32, 4, 1)),      # head_dim 64, few keys: 1536 and 768: two rounds of four per CU against one of three
+    ((0,) * 49, (16,) * 49, 64, (16, 4, 1)),      # 1568 and 784
+    ((79,) * 49, (16,) * 49, 64, (16, 4, 1)),     # 95 keys
+    ((80,) * 49, (16,) * 49, 64, (32, 4, 1)),     # 96
+])
+def test_fp32_plan_counts_rounds(lib, p, n, d, want):
+    assert _plan(p, n, 32, 8, d, dtype=B.RAGC_DTYPE_F32) == want
+
+
 def _outcome(f, *args, **kwargs):
     try:
         return f(*args, **kwargs)
