@@ -588,6 +588,22 @@ def test_fp32_matrix_core_kernel_at_its_edges(H, hq, hkv, d, lens):
     assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "f32")))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hkv,waves", [(2, 8), (60, 4)])
+@pytest.mark.parametrize("group", [1, 4, 5])
+def test_fp32_rows_of_q_up_to_four_and_more(H, d, hkv, waves, group):
+    """fp32 items of one to 16 rows (up to four Q is read by each wave, above it is shared), four and eight waves, some of
+    them without a key tile, against the oracle and byte for byte in the append."""
+    lens = [(0, 1), (15, 1), (16, 1), (70, 1), (400, 1), (130, 3)]
+    w = W.make_small("f32", hkv * group, hkv, d, lens, seed=7750 + group + d, q_gain=2.0)
+    dw, _, _ = _check_all(H, w, B.RAGC_ATTN_APPEND_FUSED)
+    assert B.ragc_debug_get_attn_plan(dw.pool, dw.batch, w.q_heads)[:2] == (16, waves)
+    pk, pv = w.pool_image()
+    OP.append(pk, pv, w.block_table, w.prefix_len, w.new_len, w.new_start, w.k_new, w.v_new)
+    assert torch.equal(_bits(dw.pool_k), _bits(H.to_device(pk, "f32")))
+    assert torch.equal(_bits(dw.pool_v), _bits(H.to_device(pv, "f32")))
+
+
 @pytest.mark.parametrize("hq,hkv,d,lens,flags", [
     (8, 2, 128, [(20000, 1), (9000, 3), (8191, 2)], B.RAGC_ATTN_NO_SPLIT),        # block ids of a wave: several windows
     (8, 2, 128, [(20000, 1), (17, 3)], 0),                                        # split keys; more copies than the short request has tiles
