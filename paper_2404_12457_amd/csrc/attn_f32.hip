@@ -163,8 +163,7 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
     };
     if (nsteps > 0) {
         copy_tile(0, true);
-        copy_tile(0, false);
-        wait_vmcnt<2 * NI>();  // this wave's part of Q
+        wait_vmcnt<NI>();  // this wave's part of Q
     } else {
         wait_vmcnt<0>();
     }
@@ -178,6 +177,11 @@ __device__ __forceinline__ void plain_rows(const AttnLaunch& a, const WorkItem& 
 #pragma unroll
         for (int j = 0; j < KJ; ++j) qreg[j] = *reinterpret_cast<lds_f32x4*>((lds_char*)qs + koff[j]);
     }
+
+    // V of the first tile behind the barrier: a wave whose tile takes a source per row issues its copies for half a microsecond,
+    // and all waves would wait for it (23 requests of 53-161 + 5 tokens, 4 heads of 128: 10.4 us, so 9.7; 23 of 26-105 + 2, 64/8
+    // heads, 9.0 and 8.1).
+    if (nsteps > 0) copy_tile(0, false);
 
     f32x4 oacc[VC][4];
 #pragma unroll
