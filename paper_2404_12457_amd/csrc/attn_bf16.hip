@@ -73,7 +73,7 @@ __device__ __forceinline__ f32x4 product(bf16x8 a, bf16x8 b, f32x4 c) { return _
 
 template <int D, int NG, int KG, bool SPLIT, class Work>
 __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(AttnLaunch a, Work wk) {
-    static_assert(!SPLIT || NG == 1, "copies of an item are one wave group each");
+    static_assert(!SPLIT || (NG == 1 && KG == 2), "copies of an item are one wave group each, with 32x32x16 products");
     constexpr int RING = 2;             // stages per wave group
     // Which product: v_mfma_f32_16x16x32_bf16 (KG = 4) or 32x32x16 (KG = 2).  A lane is row lane % BR and group lane / BR: KG
     // lanes per row, each with every KG-th run of four keys or columns.
@@ -332,6 +332,8 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
             for (int rb = 0; rb < RB; ++rb) sacc[sub][rb] = accv(0.f);
         // Two K operands at a time, read two such groups ahead (a group is 64 cycles of products, about half the LDS latency).
         constexpr int GROUPS = KSTEPS * NSUB / 2;
+        static_assert(GROUPS % 2 == 0, "the copies, which may be skipped by a branch, stand behind even groups only: never "
+                                       "between the last products and the first read of their results");
         bf16x8 kbuf[3][2];
         auto read_k = [&](auto g_c) {
             constexpr int GI = decltype(g_c)::value;
@@ -573,20 +575,15 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void attn_bf16_kernel(At
         // one of S copies: O (unnormalised, fp32), max and sum of every row go to the workspace, [TM][D] floats of O, then
         // [TM][2] floats (max, sum).  Same turn through LDS as below, in two passes of D/2 floats per row.
         float* const part = static_cast<float*>(a.partial) + ((long long)(wk.part_base + entry) * Hkv + g) * (TM * (D + 2));
-        if (kg < RB) {
-            const float2 ml = {kg ? m_run[RB - 1] : m_run[0], kg ? l_tot[RB - 1] : l_tot[0]};
-            *reinterpret_cast<float2*>(part + TM * D + (wq * 32 + kg * BR + lrow) * 2) = ml;
-        }
+        if (kg == 0) *reinterpret_cast<float2*>(part + TM * D + (wq * 32 + lrow) * 2) = float2{m_run[0], l_tot[0]};
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
             for (int dbl = 0; dbl < DB / 2; ++dbl)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                    for (int i4 = 0; i4 < OC; ++i4)
-                        *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + (rb * BR + lrow) * OROWB + (dbl * BR + i4 * 4 * KG + kg * 4) * 4) =
-                            ochunk(pass * (DB / 2) + dbl, rb, i4);
+                for (int i4 = 0; i4 < OC; ++i4)
+                    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(patch + lrow * OROWB + (dbl * BR + i4 * 4 * KG + kg * 4) * 4) =
+                        ochunk(pass * (DB / 2) + dbl, 0, i4);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int p = 0; p < 32 / RPI; ++p) {

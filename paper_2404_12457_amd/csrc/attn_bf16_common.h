@@ -99,16 +99,17 @@ __device__ __forceinline__ float other_quarter(float x) {
     return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
 }
 
-// XOR pattern applied to the 16-byte chunk index of row `row` (depends on row & 15), for operands of 64 / KG rows.
+// XOR pattern applied to the 16-byte chunk index of row `row` (depends on row & 15), for operands of 64 / KG rows; KG = 4 at
+// head_dim 128 only.
 // KG = 2 (v_mfma_f32_32x32x16_bf16): an operand read takes one chunk of 32 rows, a transposing read four of every fourth.
 // KG = 4 (16x16x32): an operand read takes four chunks of 16 rows, lanes 0-3, 12-15 and 20-27 at a time (or the others of 32),
 // a transposing read two chunks of rows 0-7 or 8-15.  Both without bank conflicts: 64 KiB in 280 cycles per CU.
 template <int D, int KG = 2>
 __device__ __forceinline__ int swz(int row) {
+    static_assert(KG == 2 || (KG == 4 && D == 128), "swizzle");
     if (KG == 4) {
         const int b2 = (row >> 2) & 1, b3 = (row >> 3) & 1;
-        if (D == 128) return ((row & 3) << 2) | ((b2 ^ b3) << 1) | b3;
-        return ((b2 ^ b3) << 2) | (row & 2) | b3;
+        return ((row & 3) << 2) | ((b2 ^ b3) << 1) | b3;
     }
     if (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
     return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
