@@ -1,10 +1,11 @@
-// fp32 prefix-cached paged prefill attention on the fp32 matrix cores of gfx950.
+// fp32 prefix-cached paged prefill attention on the matrix cores of gfx950.
 //
 // out[t,h,:] = softmax_j(scale * q[t,h,:].K_j) V_j over j = 0..prefix+i, where the
 // first `prefix` keys are gathered from 16-token pool blocks through the request's
 // block table (paper Sec. 5.1: non-contiguous blocks referenced by tree nodes) and
 // the rest are the request's own fresh K/V (Sec. 3.2: only the request tokens are
-// computed).  Inputs, products, softmax and sums are fp32 throughout.
+// computed).  Inputs, softmax and sums are fp32; products are fp32 (16 rows), or of three-part
+// bf16 splits of both operands, six of the nine products of parts summed in fp32 (32 rows).
 //
 // Two kernels (the rule between them is plan_f32).  One workgroup = (request, kv head, 16 or 32 rows);
 // a row is a (new token, q head of the group) pair, token-major, so the heads of a GQA group share
